@@ -146,9 +146,8 @@ dg::DevPhys dg::device_physics(const dg_ctx* c) {
 namespace {
 
 dg::DevBasis dev_basis(const dg_ctx* c) {
-  dg::DevBasis b{};
+  dg::DevBasis b = c->basis;
   b.D = c->dD;
-  b.inv_w_end = 1.0 / c->w[0];
   return b;
 }
 
@@ -389,6 +388,8 @@ dg_status dg_init_mesh(const dg_mesh_desc* mesh, const dg_physics* phys, void* h
   c->n_wall_faces = dg::wall_faces(dev_mesh(c));
   dg::lgl_nodes_weights(c->N, c->xi, c->w);
   dg::lgl_diff_matrix(c->xi, c->D);
+  dg::lgl_line_basis(c->N, c->basis);
+  c->basis.inv_w_end = 1.0 / c->w[0];
   *out = c;
   return DG_OK;
 }

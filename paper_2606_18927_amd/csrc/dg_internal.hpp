@@ -40,10 +40,17 @@ struct DevPhys {
   double suth_S, suth_c;
 };
 
-// LGL tables of one N, held in device memory inside the workspace.
+// LGL tables of one N: D in device memory inside the workspace; the line
+// kernels' coefficients by value, so that they are scalar operands.
+// Q_im = w_i D_im (i != m) is antisymmetric and Q_{N-m,N-i} = Q_im, so the pairs
+// i < m, i + m <= N hold it: Q[i N - i (i - 1) + m - i - 1] (interior
+// diagonal entries vanish, Q_00 = -Q_NN = -1/2).
 struct DevBasis {
   const double* D;    // D[i * NP + m] = l_m'(xi_i)
   double inv_w_end;   // 1 / w_0 (= 1 / w_N)
+  double Q[16];
+  float Qf[16];
+  double inv_w[8];    // 1 / w_i
 };
 
 // RK stage coefficients of one launch.
@@ -65,6 +72,10 @@ hipError_t launch_rhs(int N, int precision, const DevMesh& m, const DevPhys& p,
 hipError_t launch_rk_stage(int N, int precision, const DevMesh& m, const DevPhys& p,
                            const DevBasis& b, const double* U, const void* ffv, double* G,
                            double* U_out, const Stage& st, int* status, hipStream_t s);
+// The right-hand side or RK stage with one lane per line (line_kernels.hip).
+hipError_t launch_line(int N, const DevMesh& m, const DevPhys& p, const DevBasis& b, const double* U,
+                       const double* ffv, double* out, double* U_out, const Stage& st, bool rk, int* status,
+                       hipStream_t s);
 // Stand-alone FP64 lifting, grad[3 q + d][e][node] (lift_kernels.hip).
 hipError_t launch_lift(int N, const DevMesh& m, const DevPhys& p, const DevBasis& b,
                        const double* U, double* grad, hipStream_t s);
@@ -121,6 +132,8 @@ hipError_t launch_triad(const double* b, const double* c, double s, double* a, l
 // Host LGL construction (lgl.cpp): Newton on (1 - x^2) P_N'(x), barycentric D.
 void lgl_nodes_weights(int N, std::vector<double>& xi, std::vector<double>& w);
 void lgl_diff_matrix(const std::vector<double>& xi, std::vector<double>& D);
+// The by-value coefficients of DevBasis for degree N (3, 5 or 7).
+void lgl_line_basis(int N, DevBasis& b);
 
 }  // namespace dg
 
@@ -143,6 +156,7 @@ struct dg_ctx {
   long long nE = 0, nn = 0, n_dof = 0;
 
   std::vector<double> xi, w, D, s[3];
+  dg::DevBasis basis{};       // line coefficients (D is filled in per call)
 
   // workspace
   char* ws = nullptr;

@@ -1316,6 +1316,7 @@ hipError_t rhs_n(const DevMesh& m, const DevPhys& p, const DevBasis& b, const do
         launch_k_rhs<N, R, RK, false, true>(m, p, b, U, ffv, out, U_out, st, status, s);
       return hipGetLastError();
     }
+    return launch_line(N, m, p, b, U, static_cast<const double*>(ffv), out, U_out, st, RK, status, s);
   } else {
     if (p.ec) {
       if (!p.mixed_ref) return hipErrorInvalidValue;  // rejected at init: needs the reference state

@@ -95,4 +95,51 @@ void lgl_diff_matrix(const std::vector<double>& xi, std::vector<double>& D) {
   }
 }
 
+// Q_im = w_i D_im = 2 / (N (N + 1) P_N(x_i) P_N(x_m) (x_i - x_m)) for i != m, from
+// nodes refined in extended precision, so that the rounded values keep the
+// exact antisymmetry.
+void lgl_line_basis(int N, DevBasis& b) {
+  const int NP = N + 1;
+  const long double nn1 = static_cast<long double>(N) * (N + 1);
+  std::vector<long double> x(NP), P(NP);
+  std::vector<double> xi, w;
+  lgl_nodes_weights(N, xi, w);
+  const auto legendre_ld = [N](long double t, long double& p, long double& dp) {
+    long double p0 = 1.0L, d0 = 0.0L;
+    p = t;
+    dp = 1.0L;
+    for (int k = 1; k < N; ++k) {
+      const long double p2 = ((2 * k + 1) * t * p - k * p0) / (k + 1), d2 = d0 + (2 * k + 1) * p;
+      p0 = p;
+      p = p2;
+      d0 = dp;
+      dp = d2;
+    }
+  };
+  for (int j = 0; j < NP; ++j) {
+    long double t = xi[j], p, dp;
+    for (int it = 0; it < 3 && j > 0 && j < N; ++it) {
+      legendre_ld(t, p, dp);
+      t -= dp * (1.0L - t * t) / (2.0L * t * dp - nn1 * p);
+    }
+    x[j] = t;
+  }
+  for (int j = 0; j <= N / 2; ++j) {
+    const long double a = 0.5L * (x[N - j] - x[j]);
+    x[j] = -a;
+    x[N - j] = a;
+  }
+  for (int j = 0; j < NP; ++j) {
+    long double dp;
+    legendre_ld(x[j], P[j], dp);
+    b.inv_w[j] = static_cast<double>(nn1 * P[j] * P[j] / 2.0L);
+  }
+  for (int i = 0; i <= N / 2; ++i)
+    for (int m = i + 1; m <= N - i; ++m) {
+      const long double q = 2.0L / (nn1 * P[i] * P[m] * (x[i] - x[m]));
+      b.Q[i * N - i * (i - 1) + m - i - 1] = static_cast<double>(q);
+      b.Qf[i * N - i * (i - 1) + m - i - 1] = static_cast<float>(q);
+    }
+}
+
 }  // namespace dg

@@ -140,9 +140,8 @@ extern "C" dg_status dg_eval_rhs_noalloc(dg_ctx* c, const double* U, double* Ut,
   m.tauw = c->wall_model ? reinterpret_cast<double*>(base + otau) : nullptr;
   m.geo = nullptr;
   const dg::DevPhys p = dg::device_physics(c);
-  dg::DevBasis b{};
+  dg::DevBasis b = c->basis;
   b.D = dD;
-  b.inv_w_end = 1.0 / c->w[0];
   void* ffv = base + offv;
   if (c->phys.viscous &&
       (st = hip(dg::launch_face_flux(c->N, c->phys.precision, m, p, b, U, ffv, c->stream), "face flux kernel")) !=

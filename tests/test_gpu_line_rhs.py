@@ -1,0 +1,71 @@
+"""The line-lane right-hand side (GPU) at the sizes where its work split can go
+wrong: fewer elements than XCDs, element counts that are no multiple of the
+workgroups (at N = 7 a workgroup works on several elements in turn, from 513
+elements on), every degree, walls of both kinds on each axis, with and without
+viscosity, Sutherland's law, the right-hand side alone and as an RK step.
+
+Criterion: per conserved variable, relative L2 error <= 1e-12 (FP64) against the
+FP64 oracle on the same seeded state.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle.dgsem import rhs, rk_step
+from oracle.mesh import Mesh
+from oracle.physics import Gas
+from paper_2606_18927_amd import dgsem
+
+from _cases import random_faces, random_state
+from _gpu import need_gpu, rel_l2, say, to_dev
+
+pytestmark = pytest.mark.gpu
+P = "periodic"
+BOUND = {"fp64": 1e-12}
+
+
+@pytest.mark.parametrize("N,n,bc,opts", [
+    (7, (1, 1, 1), (P, P, P), {}),
+    (7, (3, 1, 3), ("wall", P, "wallmodel"), {"suth": True}),
+    (7, (9, 8, 8), (P, "wall", P), {}),
+    (7, (3, 3, 1), (P, P, "wall"), {"viscous": False}),
+    (5, (1, 1, 1), (P, P, P), {}),
+    (5, (3, 3, 2), ("wallmodel", "wall", P), {"suth": True}),
+    (5, (2, 3, 3), (P, "wall", "wall"), {"viscous": False, "central": True}),
+    (3, (1, 1, 1), ("wall", P, P), {}),
+    (3, (5, 3, 7), (P, "wallmodel", "wall"), {"suth": True}),
+    (3, (9, 1, 2), (P, P, P), {"viscous": False}),
+])
+@pytest.mark.parametrize("flux,precision", [("kg_llf", "fp64")])
+def test_rhs_and_rk_step(N, n, bc, opts, flux, precision):
+    need_gpu()
+    say("case", N, n, bc, opts, flux, precision)
+    rng = np.random.default_rng(100 * N + n[0])
+    faces = tuple(random_faces(n[d], 0.0, 1.0 + d, rng) for d in range(3))
+    mesh = Mesh(N, faces, bc=bc, T_wall=1.1, wm_node=2)
+    suth = (1.0, 0.4) if opts.get("suth") else None
+    g = Gas(gamma=1.4, R=1.0 / (1.4 * 0.01), mu=0.01, Pr=0.72, sutherland=suth is not None, T_ref=1.0, S=0.4)
+    U = random_state(mesh, g.gamma, g.R, rng, vel_amp=1.0, p_mean=g.R, p_amp=0.05)
+    kw = {"viscous": opts.get("viscous", True), "central_only": opts.get("central", False), "flux": flux}
+    S = dgsem.Solver(dgsem.MeshSpec(N, faces, bc, 1.1, 2), g.gamma, g.R, g.mu, g.Pr, precision=precision,
+                     sutherland=suth, **kw)
+    Ud = to_dev(U.numpy())
+    ref = rhs(U, mesh, g, **kw).numpy()
+    e = rel_l2(S.eval_rhs(Ud).cpu().numpy(), ref)
+    say("rhs", e)
+    assert np.all(e < BOUND[precision])
+    # three steps: the increment, so that every stage (with and without G) counts
+    dt = 1e-3 / max(np.abs(ref[v]).max() / np.abs(U[v].numpy()).max() for v in range(5))
+    S.set_state(Ud)
+    S.rk_step(dt, 3)
+    S.sync()
+    want = rk_step(U, mesh, g, dt, 3, **kw).numpy() - U.numpy()
+    got = S.get_state().cpu().numpy().reshape(want.shape) - U.numpy()
+    # the increment is a difference of states: their rounding, eps |U| / |dU|, is
+    # part of it
+    tol = BOUND[precision] + 4 * 2.3e-16 * np.array(
+        [np.linalg.norm(U[v].numpy()) / np.linalg.norm(want[v]) for v in range(5)])
+    e = rel_l2(got, want)
+    say("rk", e, tol)
+    assert np.all(e < tol)
