@@ -25,20 +25,15 @@ struct Cfg<7> {
   static constexpr int EPB = 1, BS = 512, FACE_WAVES = 8;
 };
 
-// LDS block of one element and field: x-rows of RS entries (NP + PAD); with
-// SWZ (NP a power of two, no padding) node i of row j sits at slot i ^ j of
-// its row, so the NP rows that the lanes of a wave read at one x-position m
-// (an x-line sweep) start in different banks, while a y- or z-line sweep
-// still reads whole rows (a permutation of them).
-template <int N, int PAD = 1, bool SWZ = false>
+// LDS block of one element and field: x-rows padded by one entry.
+template <int N>
 struct Geo {
   static constexpr int NP = N + 1, NF = NP * NP, NN = NF * NP;
-  static constexpr int RS = NP + PAD;      // x-row stride of an LDS block
+  static constexpr int RS = NP + 1;        // x-row stride of an LDS block
   static constexpr int EB = RS * NP * NP;  // LDS entries per element and field
   static constexpr int DS = NP + 1;        // padded row stride of D in LDS
-  static_assert(!SWZ || (PAD == 0 && (NP & (NP - 1)) == 0), "the swizzle permutes unpadded rows of 2^n");
   __device__ static constexpr int lds(int i, int j, int k) {
-    return (SWZ ? (i ^ (j & (NP - 1))) : i) + RS * (j + NP * k);
+    return i + RS * (j + NP * k);
   }
 };
 
@@ -224,7 +219,6 @@ __device__ inline double viscosity_ratio(const DevPhys& ph, double T) {
   return ph.suth ? ph.suth_c * T * sqrt(T) / (T + ph.suth_S) : 1.0;
 }
 
-__device__ inline double vel(const Prim& P, int d) { return d == 0 ? P.u : (d == 1 ? P.v : P.w); }
 
 // Values a kernel reads or writes once (G, the neighbours' face viscous
 // fluxes, the updated state): non-temporal accesses, so that they do not
@@ -286,23 +280,6 @@ __device__ inline double hh_abs(double lam, double lam_L, double lam_R) {
   double delta = fmax(lam - lam_L, lam_R - lam);
   delta = delta > 0.0 ? delta : 0.0;
   return fabs(lam) < delta ? (lam * lam + delta * delta) / (2.0 * delta) : fabs(lam);
-}
-
-// Kennedy-Gruber two-point flux along d of states a, b = (rho, u, v, w, p, e).
-template <int d, typename R>
-__device__ inline void kg_flux(const R a[6], const R b[6], R f[5]) {
-  const R h = R(0.5);
-  const R rho = h * (a[0] + b[0]);
-  const R ud = h * (a[1 + d] + b[1 + d]);
-  const R p = h * (a[4] + b[4]);
-  const R e = h * (a[5] + b[5]);
-  const R mass = rho * ud;
-  f[0] = mass;
-  f[1] = mass * (h * (a[1] + b[1]));
-  f[2] = mass * (h * (a[2] + b[2]));
-  f[3] = mass * (h * (a[3] + b[3]));
-  f[1 + d] += p;
-  f[4] = mass * e + p * ud;
 }
 
 // Viscous flux along d: g[3 q + b] = d q / d x_b for q in (u, v, w, T);

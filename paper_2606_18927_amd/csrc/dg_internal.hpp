@@ -72,10 +72,23 @@ hipError_t launch_rhs(int N, int precision, const DevMesh& m, const DevPhys& p,
 hipError_t launch_rk_stage(int N, int precision, const DevMesh& m, const DevPhys& p,
                            const DevBasis& b, const double* U, const void* ffv, double* G,
                            double* U_out, const Stage& st, int* status, hipStream_t s);
-// The right-hand side or RK stage with one lane per line (line_kernels.hip).
-hipError_t launch_line(int N, const DevMesh& m, const DevPhys& p, const DevBasis& b, const double* U,
-                       const double* ffv, double* out, double* U_out, const Stage& st, bool rk, int* status,
-                       hipStream_t s);
+// The right-hand side or RK stage with line lanes (line_device.hpp), one source per
+// flux pair and precision.
+struct LineLaunch {
+  const double* U;
+  const void* ffv;
+  double* out;
+  double* U_out;
+  int* status;
+  const DevMesh* m;
+  const DevPhys* p;
+  const DevBasis* b;
+  const Stage* st;
+};
+hipError_t launch_line_kg_f64(int N, bool rk, const LineLaunch& l, hipStream_t s);
+hipError_t launch_line_ec_f64(int N, bool rk, const LineLaunch& l, hipStream_t s);
+hipError_t launch_line_kg_f32(int N, bool rk, const LineLaunch& l, hipStream_t s);
+hipError_t launch_line_ec_f32(int N, bool rk, const LineLaunch& l, hipStream_t s);
 // Stand-alone FP64 lifting, grad[3 q + d][e][node] (lift_kernels.hip).
 hipError_t launch_lift(int N, const DevMesh& m, const DevPhys& p, const DevBasis& b,
                        const double* U, double* grad, hipStream_t s);
