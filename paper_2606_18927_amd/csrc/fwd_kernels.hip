@@ -5,295 +5,254 @@
 //
 //   k_face_flux : U -> the normal viscous flux f_v,d (4 components) on the six
 //                 face planes of every element (BR1 lifting evaluated at the
-//                 face nodes only);
+//                 face nodes only); this file;
 //   k_rhs_line  : U, the neighbours' face viscous fluxes -> Ut, or the fused
 //                 low-storage RK update G <- A G + dt Ut, U' <- U + B G.
-//                 It recomputes its own element's lifted gradients from U.
+//                 It recomputes its own element's lifted gradients from U
+//                 (line_device.hpp).
 //
 // So the lifted gradients never travel through HBM: per DOF and stage the
 // method moves U in twice, G in and out, U' out and three face-flux values
 // (N = 7) out and in, instead of twelve gradient components out and in.
 //
-// This file holds the first kernel; the second is in line_device.hpp.
-//
-// Mixed precision (R = float): the LDS fields, gradients and viscous fluxes are
-// FP32; the primitive recovery and the lifting corrections stay FP64.
-// Temperature is stored relative to the element's first node, with the difference
-// taken in FP64.
-//
 // Workgroup ids are remapped so that each XCD (own L2) covers one contiguous
 // range of elements, keeping face neighbours in the same L2.
-#include "dg_device.hpp"
+#include "line_device.hpp"
 
 namespace dg {
 namespace {
 
-// Vector of two R values (one 64- or 128-bit LDS access).
-template <typename R>
-struct V2T;
-template <>
-struct V2T<double> {
-  using type = double2;
+struct FaceArgs {
+  const double* U;
+  void* ffv;  // R*
+  DevMesh mesh;
+  DevPhys ph;
+  DevBasis basis;
 };
-template <>
-struct V2T<float> {
-  using type = float2;
+typedef const __attribute__((address_space(4))) FaceArgs* FaceArgsPtr;
+
+__device__ inline const FaceArgs& again(FaceArgsPtr p) {
+  asm volatile("" : "+s"(p));
+  return *(const FaceArgs*)p;
+}
+
+// k_face_flux: f_v,d on the face planes, layout ffv[e][face][c][ab].
+//
+// One workgroup per element, of the line-lane shape.  A flux needs eight of the twelve
+// gradient components: the normal derivatives of u, v, w, T, and of each tangential
+// direction t those of u_t and of the normal velocity.
+//   nodes  all lanes: (u, v, w, T) into LDS; line lanes also recover the neighbours'
+//          states at the two ends of their line, the ghost values of the weak form
+//          (line_device.hpp), and put the ghost velocities into LDS;
+//   lines  a line lane forms the normal derivatives at its line's two ends; the other
+//          wave(s) the tangential ones along the 12 (N+1) lines of the face planes,
+//          two velocity components each;
+//   faces  a line lane, now lane of two face nodes, forms the two fluxes; its wave
+//          stores whole rows.
+// What bounds it (N = 7, 32^3 elements, FP64; 0.23 - 0.26 ms, with one lane per face
+// node that read three whole lines of four fields 0.31): HBM moves 0.81 GB (0.13 ms
+// at the rate of a triad), vector instructions issue 36 % of the time (51 M wave
+// instructions, before 92 M), LDS is busy 28 % (43 M cycles, before 79 M); the rest is
+// the latency of the two load - LDS - compute chains of the five workgroups (29 KB
+// LDS) of a CU.  The sums are settled before the barriers: sunk past them they need
+// 122 instead of 65 registers, and N = 5 runs 1.3x slower on half the waves.
+// Mixed precision stores FP32 and computes in FP64 (without packed instructions FP32
+// is no faster) with the FP32 entries of Q: the rounding of a row's entries is a
+// systematic error of a gradient (row sum times mean velocity), and the two
+// kernels' fluxes at a face have to share it, or momentum is lost there (5e-9 of the
+// kinetic energy of a channel in 500 steps).
+template <int N>
+struct FaceShape {
+  using L = Line<N>;
+  static constexpr int TASKS = 24 * L::NP;                            // tangential lines times two components
+  static constexpr int ROUNDS = (TASKS + 64 * L::FW - 1) / (64 * L::FW);
+  static constexpr int OUT = 4 * L::EB;                               // tangential derivatives, 4 per face node
+  // ghost velocities, 3 per face node; a single tangential wave reads all it needs
+  // before it writes: they share the place of its results
+  static constexpr int GHOST = L::FW == 1 ? OUT : OUT + 24 * L::NF;
+  static constexpr int COUNT = L::FW == 1 ? OUT + 24 * L::NF : GHOST + 18 * L::NF;
+  static constexpr int WAVES = N == 7 ? 5 : 8;                        // per SIMD, as LDS allows
 };
 
-// Line sums sum_m Q_im q_m, Q = diag(w) D, along direction d of (u, v, w, T) held as
-// LDS pairs q[0] = (u, v), q[1] = (w, T) at node (i, j, k); Q is read once per line
-// position.
-template <int N, typename R, int d, typename V2>
-__device__ inline void line_sums_pairs(const R* sQ, const V2 (*q)[Geo<N>::EB], int i, int j, int k,
-                                       R a[4]) {
-  using Gm = Geo<N>;
-  constexpr int NP = Gm::NP;
-  const int idx = d == 0 ? i : (d == 1 ? j : k);
-  a[0] = a[1] = a[2] = a[3] = R(0);
+template <int N>
+__device__ __forceinline__ void face_fields(const FaceArgs& A, double* sF, int tid, const double (&u)[Line<N>::ROUNDS][5]) {
+  using L = Line<N>;
 #pragma unroll
-  for (int m = 0; m < NP; ++m) {
-    const int lm = d == 0 ? Gm::lds(m, j, k) : (d == 1 ? Gm::lds(i, m, k) : Gm::lds(i, j, m));
-    const R Qm = sQ[idx * Gm::DS + m];
-    const V2 uv = q[0][lm], wT = q[1][lm];
-    a[0] += Qm * uv.x;
-    a[1] += Qm * uv.y;
-    a[2] += Qm * wT.x;
-    a[3] += Qm * wT.y;
+  for (int r = 0; r < L::ROUNDS; ++r) {
+    const unsigned n = tid + r * L::BS;
+    if (n < L::NN) {
+      const double* s = u[r];
+      const double ir = rcp_nr(s[0]);
+      const double vx = s[1] * ir, vy = s[2] * ir, vz = s[3] * ir;
+      const int l = L::at(n % L::NP, (n / L::NP) % L::NP, n / L::NF);
+      sF[l] = vx;
+      sF[L::EB + l] = vy;
+      sF[2 * L::EB + l] = vz;
+      sF[3 * L::EB + l] = A.ph.gm1 * (s[4] - 0.5 * (s[1] * vx + s[2] * vy + s[3] * vz)) * A.ph.inv_R * ir;
+    }
   }
 }
 
-// BR1 lifted gradients g[3 q + d] of (u, v, w, T) (LDS pairs) at node
-// (i, j, k), with the lifting corrections ssq of the six faces; sx, sy, sz include the
-// nodes' 1 / w.  The entries of Q are those of the line-lane kernel: the rounding
-// of a row's entries is a systematic error of a gradient (the row sum, times the mean
-// velocity), and in mixed precision the two kernels' fluxes at a face have to share it,
-// or momentum is lost there (5e-9 of the channel's kinetic energy in 500 steps).
-template <int N, typename R, typename V2>
-__device__ inline void lifted_gradients(const R* sQ, const V2 (*q)[Geo<N>::EB],
-                                        const R (*ssq)[4][Geo<N>::NF], int i, int j, int k, R sx,
-                                        R sy, R sz, R g[12]) {
-  constexpr int NP = N + 1;
-  R a[4];
-  line_sums_pairs<N, R, 0, V2>(sQ, q, i, j, k, a);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    if (i == 0) a[c] += ssq[0][c][j + NP * k];
-    if (i == N) a[c] += ssq[1][c][j + NP * k];
-    g[3 * c + 0] = sx * a[c];
-  }
-  line_sums_pairs<N, R, 1, V2>(sQ, q, i, j, k, a);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    if (j == 0) a[c] += ssq[2][c][i + NP * k];
-    if (j == N) a[c] += ssq[3][c][i + NP * k];
-    g[3 * c + 1] = sy * a[c];
-  }
-  line_sums_pairs<N, R, 2, V2>(sQ, q, i, j, k, a);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    if (k == 0) a[c] += ssq[4][c][i + NP * j];
-    if (k == N) a[c] += ssq[5][c][i + NP * j];
-    g[3 * c + 2] = sz * a[c];
-  }
-}
-
-// Per-element reference (p, e, T) of the mixed-precision sweeps: the values at
-// node 0 (state s0), or zero in FP64 and with the subtraction switched off.
-template <typename R>
-__device__ inline bool uses_ref(const DevPhys& ph) {
-  return sizeof(R) == sizeof(float) && ph.mixed_ref;
-}
-
-template <typename R>
-__device__ inline void element_ref(const double s0[5], const DevPhys& ph, double& p_ref,
-                                   double& e_ref, double& T_ref) {
-  if (!uses_ref<R>(ph)) {
-    p_ref = e_ref = T_ref = 0.0;
-    return;
-  }
-  const Prim P = primitives(s0, ph);
-  p_ref = P.p;
-  e_ref = P.e;
-  T_ref = P.T;
-}
-
-// --------------------------------------------------------------------------
-// k_face_flux: f_v,d on the face planes, layout ffv[e][face][c][ab]
-// --------------------------------------------------------------------------
 template <int N, typename R>
-__global__ __launch_bounds__(Cfg<N>::BS) __attribute__((amdgpu_waves_per_eu(Cfg<N>::FACE_WAVES))) void k_face_flux(
-    const double* __restrict__ U, R* __restrict__ ffv, DevMesh mesh, DevPhys ph, DevBasis basis) {
-  using Gm = Geo<N>;
-  constexpr int NP = Gm::NP, NF = Gm::NF, NN = Gm::NN, EB = Gm::EB;
-  constexpr int EPB = Cfg<N>::EPB, BS = Cfg<N>::BS;
-  constexpr int NFN = n_face_nodes<N>();
-  static_assert(EPB * NFN <= BS, "one lane per face node");
-  using V2 = typename V2T<R>::type;
-  __shared__ R sQ[NP * Gm::DS];
-  __shared__ double sW[NP];  // 1 / w_i
-  __shared__ V2 sq[EPB][2][EB];  // (u, v), (w, T - T_ref)
-  __shared__ R ssq[EPB][6][4][NF];
-  constexpr bool MIXED = sizeof(R) == 4;
-  // mixed precision: the FP64 (u, v, w, T) of every node, for the lifting terms
-  __shared__ double sqd[MIXED ? EPB : 1][4][MIXED ? NN : 1];
-
+__global__ __launch_bounds__(Line<N>::BS) __attribute__((amdgpu_waves_per_eu(FaceShape<N>::WAVES))) void k_face_flux(FaceArgs) {
+  using L = Line<N>;
+  using Fs = FaceShape<N>;
+  constexpr int NP = L::NP, NF = L::NF, EB = L::EB;
+  __shared__ double sF[Fs::COUNT];
+  const FaceArgsPtr args = (FaceArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const int tid = threadIdx.x;
-  const long long nE = mesh.nE;
-  const long long stride = nE * NN;
-  const long long e0 = static_cast<long long>(xcd_remap(blockIdx.x, gridDim.x)) * EPB;
-  int ex0 = 0, ey0 = 0, ez0 = 0;
-  elem_coords(e0 < nE ? e0 : 0, mesh, ex0, ey0, ez0);
+  const int e = xcd_remap(blockIdx.x, gridDim.x);
+  const FaceArgs& A = again(args);
+  const long long stride = A.mesh.nE * L::NN;
+  double u[L::ROUNDS][5];
+  fetch_nodes<N>(A.U, stride, e, tid, u);
 
-  // P1: node lanes stage (u, v, w, T - T_ref) in LDS (and, in mixed
-  // precision, an FP64 copy of (u, v, w, T)); face lanes fetch the
-  // neighbour state and form the BR1 lifting corrections in FP64 after the
-  // barrier, with the own values from LDS
-  const bool face_lane = tid < n_face_tasks<N>();
-  const bool face_ok = face_lane && (EPB == 1 ? e0 : e0 + FaceTask<N>(face_lane ? tid : 0).le) < nE;
-  // the own state is fetched first, so that it and the neighbour's face node
-  // are in flight together
-  const int nle = EPB == 1 ? 0 : tid / NN;
-  const int node = tid - nle * NN;
-  const long long ne = EPB == 1 ? e0 : e0 + nle;
-  const bool node_ok = (EPB == 1 ? tid < NN : nle < EPB) && ne < nE;
-  double s[5] = {1.0, 0.0, 0.0, 0.0, 1.0}, s0[5] = {1.0, 0.0, 0.0, 0.0, 1.0};
-  if (node_ok) {
-    load_state(U, stride, ne * NN + node, s);
-    if (uses_ref<R>(ph)) load_state(U, stride, ne * NN, s0);
-  }
-  double sn[5] = {1.0, 0.0, 0.0, 0.0, 1.0};
-  bool fwall = true;
-  if (face_ok) {
-    const FaceTask<N> ft(tid);
-    const long long te = EPB == 1 ? e0 : e0 + ft.le;
-    int ex = ex0, ey = ey0, ez = ez0;
-    if (EPB > 1) elem_coords(te, mesh, ex, ey, ez);
-    const long long nb = neighbour(mesh, ex, ey, ez, ft.d, ft.up);
-    fwall = nb < 0;
-    if (!fwall) load_state(U, stride, nb * NN + ft.nb_node(), sn);
-  }
-  if (node_ok) {
-    const int i = node % NP, j = (node / NP) % NP, k = node / NF;
-    const Prim P = primitives(s, ph);
-    double p_ref, e_ref, T_ref;
-    element_ref<R>(s0, ph, p_ref, e_ref, T_ref);
-    const int l = Gm::lds(i, j, k);
-    sq[nle][0][l] = V2{static_cast<R>(P.u), static_cast<R>(P.v)};
-    sq[nle][1][l] = V2{static_cast<R>(P.w), static_cast<R>(P.T - T_ref)};
-    if (MIXED) {
-      sqd[nle][0][node] = P.u;
-      sqd[nle][1][node] = P.v;
-      sqd[nle][2][node] = P.w;
-      sqd[nle][3][node] = P.T;
-    }
-  }
-  static_assert(NP * NP <= BS, "one lane per entry of Q");
-  if (tid < NP * NP) {
-    const int i = tid / NP, m = tid % NP;
-    const bool flip = i + m > N;  // Q_im = -Q_mi = -Q_(N-i)(N-m): the entries 0 <= i < m <= N - i are stored
-    const int a = flip ? (i < m ? N - m : N - i) : (i < m ? i : m), c = flip ? (i < m ? N - i : N - m) : (i < m ? m : i);
-    R q = i == m ? (i == 0 ? R(-0.5) : (i == N ? R(0.5) : R(0))) : R(0);
-    if (i != m) {
-      const int id = a * N - a * (a - 1) + c - a - 1;
+  if (__builtin_amdgcn_readfirstlane(tid) < 64 * L::LW) {
+    const Place pl(A.mesh, e);
+    const LineTask<N> t(tid);
+    const bool wm = pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL;
+    double sn[2][5];
+    bool wall[2];
 #pragma unroll
-      for (int t = 0; t < (NP * NP) / 4; ++t) {
-        const R b = sizeof(R) == 4 ? static_cast<R>(basis.Qf[t]) : static_cast<R>(basis.Q[t]);
-        q = id == t ? b : q;
-      }
-      if (i > m) q = -q;
+    for (int h = 0; h < 2; ++h) {
+      const int nb = pl.neighbour(t.d, h);
+      wall[h] = nb < 0;  // (there the own state)
+      const unsigned o = t.end_node((h != 0) == (nb >= 0) ? 0 : N);
+      const double* p = A.U + static_cast<long long>(nb >= 0 ? nb : e) * L::NN;
+      sn[h][0] = p[o];
+      sn[h][1] = (p + (1 + t.d) * stride)[o];
+      sn[h][2] = (p + (1 + t.d1) * stride)[o];
+      sn[h][3] = (p + (1 + t.d2) * stride)[o];
+      sn[h][4] = (p + 4 * stride)[o];
     }
-    sQ[i * Gm::DS + m] = q;
-    if (m == 0) {
-      double w = basis.inv_w[0];
+    face_fields<N>(A, sF, tid, u);
+    double gh[2][4];  // ghosts: velocity along and across the line, T
 #pragma unroll
-      for (int t = 1; t < NP; ++t) w = i == t ? basis.inv_w[t] : w;
-      sW[i] = w;
+    for (int h = 0; h < 2; ++h) {
+      const double* s = sn[h];
+      const double ir = rcp_nr(s[0]);
+      const double v0 = s[1] * ir, v1 = s[2] * ir, v2 = s[3] * ir;
+      const double T = A.ph.gm1 * (s[4] - 0.5 * (s[1] * v0 + s[2] * v1 + s[3] * v2)) * A.ph.inv_R * ir;
+      const double side = wall[h] && !wm ? -1.0 : 1.0;  // no-slip wall; the wall model's slips
+      gh[h][0] = wall[h] ? -v0 : v0;
+      gh[h][1] = side * v1;
+      gh[h][2] = side * v2;
+      gh[h][3] = wall[h] && !wm ? 2.0 * A.mesh.T_wall - T : T;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sF[Fs::GHOST + ((2 * t.d + h) * 3 + c) * NF + t.ab] = gh[h][c];
     }
-  }
-  __syncthreads();
-  {
-    if (face_ok) {
-      const FaceTask<N> ft(tid);
-      double qo[4];
-      if (MIXED) {
-        const int on = ft.own_node();
-#pragma unroll
-        for (int c = 0; c < 4; ++c) qo[c] = sqd[ft.le][c][on];
-      } else {
-        const int lo = Gm::lds(ft.oi, ft.oj, ft.ok);
-        const V2 uv = sq[ft.le][0][lo], wT = sq[ft.le][1][lo];
-        qo[0] = uv.x;
-        qo[1] = uv.y;
-        qo[2] = wT.x;
-        qo[3] = wT.y;
-      }
-      double qs[4];
-      wall_lifting_value(mesh, ft.d, qo, qs);
-      if (!fwall) {
-        const Prim Pn = primitives(sn, ph);
-        qs[0] = 0.5 * (qo[0] + Pn.u);
-        qs[1] = 0.5 * (qo[1] + Pn.v);
-        qs[2] = 0.5 * (qo[2] + Pn.w);
-        qs[3] = 0.5 * (qo[3] + Pn.T);
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) ssq[ft.le][ft.f][c][ft.ab] = static_cast<R>(ft.up ? qs[c] - qo[c] : qo[c] - qs[c]);
-    }
-    __syncthreads();
-  }
+    phase_end();
 
-  // P2: one lane per face node: lifted gradients and f_v,d of each face the
-  // node lies on
-  const int le = EPB == 1 ? 0 : tid / NFN;
-  const long long e = EPB == 1 ? e0 : e0 + le;
-  if ((EPB == 1 ? tid < NFN : le < EPB) && e < nE) {
-    int i, j, k;
-    face_node_of<N>(tid - le * NFN, i, j, k);
-    int ex = ex0, ey = ey0, ez = ez0;
-    if (EPB > 1) elem_coords(e, mesh, ex, ey, ez);
-    R g[12];
-    lifted_gradients<N, R, V2>(sQ, sq[le], ssq[le], i, j, k, static_cast<R>(mesh.s[0][ex] * sW[i]),
-                               static_cast<R>(mesh.s[1][ey] * sW[j]), static_cast<R>(mesh.s[2][ez] * sW[k]), g);
-    const int l = Gm::lds(i, j, k);
-    const V2 uv = sq[le][0][l], wT = sq[le][1][l];
-    const R u = uv.x, v = uv.y, w = wT.x;
-    R mu = static_cast<R>(ph.mu), kappa = static_cast<R>(ph.kappa);
-    if (ph.suth) {
-      // mu(T) at the node's temperature: in FP64 the LDS holds T itself, in
-      // mixed precision the FP64 copy holds it
-      const double T = MIXED ? sqd[le][3][i + NP * (j + NP * k)] : static_cast<double>(wT.y);
-      const R r = static_cast<R>(viscosity_ratio(ph, T));
-      mu *= r;
-      kappa *= r;
-    }
-    R* out = ffv + e * (6 * 4 * NF);
-    R f[4];
-    if (i == 0 || i == N) {
-      viscous_flux<0, R>(u, v, w, g, mu, kappa, f);
-      const int fi = i == 0 ? 0 : 1;
+    double own[2][4], g[2][4];  // values and normal derivatives at the line's ends
+    {
+      const DevBasis& b = again(args).basis;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) out[(fi * 4 + c) * NF + j + NP * k] = f[c];
-    }
-    if (j == 0 || j == N) {
-      viscous_flux<1, R>(u, v, w, g, mu, kappa, f);
-      const int fi = j == 0 ? 2 : 3;
+      for (int c = 0; c < 4; ++c) {
+        const int f = c == 0 ? t.d : (c == 1 ? t.d1 : (c == 2 ? t.d2 : 3));
+        double q[NP];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) out[(fi * 4 + c) * NF + i + NP * k] = f[c];
-    }
-    if (k == 0 || k == N) {
-      viscous_flux<2, R>(u, v, w, g, mu, kappa, f);
-      const int fi = k == 0 ? 4 : 5;
+        for (int m = 0; m < NP; ++m) q[m] = sF[f * EB + t.node(m)];
+        own[0][c] = q[0];
+        own[1][c] = q[N];
+        if (sizeof(R) == 4 && c == 3) {
+          // the other kernel's temperatures are relative too: no row sum times T
 #pragma unroll
-      for (int c = 0; c < 4; ++c) out[(fi * 4 + c) * NF + i + NP * j] = f[c];
+          for (int m = 0; m < NP; ++m) q[m] -= own[0][3];
+          gh[0][3] -= own[0][3];
+          gh[1][3] -= own[0][3];
+        }
+        g[0][c] = -0.5 * gh[0][c];
+        g[1][c] = 0.5 * gh[1][c];
+#pragma unroll
+        for (int m = 1; m < NP; ++m) g[0][c] += q_im<N, double>(b, 0, m) * q[m];
+#pragma unroll
+        for (int m = 0; m < N; ++m) g[1][c] -= q_im<N, double>(b, m, N) * q[m];
+        if (c & 1) settle(g);
+      }
     }
+    phase_end();
+
+    const FaceArgs& B = again(args);
+    const double sd = (t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz)) * B.basis.inv_w[0];
+    const double s1 = t.d1 == 0 ? pl.sx : (t.d1 == 1 ? pl.sy : pl.sz);
+    const double s2 = t.d2 == 0 ? pl.sx : (t.d2 == 1 ? pl.sy : pl.sz);
+    const int k1 = t.d == 1 ? 2 : 0;  // tangential results of direction d1, d2
+    R* out = static_cast<R*>(B.ffv) + static_cast<long long>(e) * (6 * 4 * NF);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double* o1 = &sF[Fs::OUT + ((2 * t.d + h) * 4 + k1) * NF + t.ab];
+      const double* o2 = &sF[Fs::OUT + ((2 * t.d + h) * 4 + (2 - k1)) * NF + t.ab];
+      double mu = B.ph.mu, kappa = B.ph.kappa;
+      if (B.ph.suth) {
+        const double r = viscosity_ratio(B.ph, own[h][3]);
+        mu *= r;
+        kappa *= r;
+      }
+      const double gn = sd * g[h][0];
+      const double dd = (2.0 / 3.0) * (gn + s1 * o1[0] + s2 * o2[0]);
+      const double t0 = mu * (gn + gn - dd);
+      const double t1 = mu * (sd * g[h][1] + s1 * o1[NF]);
+      const double t2 = mu * (sd * g[h][2] + s2 * o2[NF]);
+      R* f = out + (2 * t.d + h) * (4 * NF);
+      const unsigned ab = t.ab;
+      (f + t.d * NF)[ab] = static_cast<R>(t0);
+      (f + t.d1 * NF)[ab] = static_cast<R>(t1);
+      (f + t.d2 * NF)[ab] = static_cast<R>(t2);
+      (f + 3 * NF)[ab] = static_cast<R>(own[h][0] * t0 + own[h][1] * t1 + own[h][2] * t2 + kappa * sd * g[h][3]);
+    }
+  } else {
+    face_fields<N>(A, sF, tid, u);
+    phase_end();
+    // task: the line at position pos of face 2 d + h along its first or second
+    // direction t; the component u_t or u_d
+    struct Task {
+      int first, step, field, ghost, out, dout;
+      __device__ Task(int q) {
+        q = q < Fs::TASKS ? q : Fs::TASKS - 1;
+        const int d = q / (8 * NP), r = q - d * (8 * NP);
+        const int pos = r % NP, c = (r / NP) & 1, second = (r / (2 * NP)) & 1, h = r / (4 * NP);
+        const int t = second ? (d == 2 ? 1 : 2) : (d == 0 ? 1 : 0), o = 3 - d - t;
+        const int n = h ? N : 0;
+        const LineTask<N> line(t, d < o ? n + NP * pos : pos + NP * n);
+        first = line.first;
+        step = line.step;
+        field = c ? d : t;
+        const int turn = field - t;  // its place in the frame of the lines along t
+        ghost = Fs::GHOST + (2 * t * 3 + (turn < 0 ? turn + 3 : turn)) * NF + line.ab;
+        out = Fs::OUT + ((2 * d + h) * 4 + 2 * second + c) * NF + (second ? pos : NP * pos);
+        dout = second ? NP : 1;
+      }
+    };
+    const int lane = tid - 64 * L::LW;
+    double gl[Fs::ROUNDS], gr[Fs::ROUNDS];
+#pragma unroll
+    for (int r = 0; r < Fs::ROUNDS; ++r) {
+      const Task k(lane + 64 * L::FW * r);
+      gl[r] = sF[k.ghost];
+      gr[r] = sF[k.ghost + 3 * NF];
+    }
+    const DevBasis& b = again(args).basis;
+#pragma unroll
+    for (int r = 0; r < Fs::ROUNDS; ++r) {
+      const Task k(again(lane) + 64 * L::FW * r);
+      double q[NP], g[NP];
+#pragma unroll
+      for (int m = 0; m < NP; ++m) q[m] = sF[k.field * EB + (L::SWZ ? k.first ^ (m * k.step) : k.first + m * k.step)];
+      line_derivative<N, double, false>(b, q, gl[r], gr[r], g);
+#pragma unroll
+      for (int m = 0; m < NP; ++m) sF[k.out + m * k.dout] = b.inv_w[m] * g[m];
+    }
+    phase_end();
   }
 }
 
 template <int N, typename R>
 hipError_t face_flux_n(const DevMesh& m, const DevPhys& p, const DevBasis& b, const double* U,
                        void* ffv, hipStream_t s) {
-  hipLaunchKernelGGL((k_face_flux<N, R>), dim3(n_blocks<N>(m.nE)), dim3(Cfg<N>::BS), 0, s, U,
-                     static_cast<R*>(ffv), m, p, b);
+  FaceArgs a{U, ffv, m, p, b};
+  if (sizeof(R) == 4)
+    for (int i = 0; i < 16; ++i) a.basis.Q[i] = b.Qf[i];
+  hipLaunchKernelGGL((k_face_flux<N, R>), dim3(static_cast<unsigned>(m.nE)), dim3(Line<N>::BS), 0, s, a);
   return hipGetLastError();
 }
 
