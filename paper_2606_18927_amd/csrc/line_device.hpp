@@ -313,7 +313,7 @@ __host__ __device__ constexpr bool line_persists() {
 // Waves per SIMD the registers are bounded for: what LDS lets a CU hold.
 template <int N, typename R, bool EC>
 __host__ __device__ constexpr int line_waves() {
-  return sizeof(R) == 8 ? (N == 7 ? 2 : (N == 5 ? (EC ? 2 : 3) : (EC ? 3 : 4))) : (N == 7 || EC ? 3 : 4);
+  return sizeof(R) == 8 ? (N == 7 ? 2 : (N == 5 ? (EC ? 2 : 3) : (EC ? 2 : 4))) : (N == 7 || EC ? 3 : 4);
 }
 
 // A phase boundary: a workgroup barrier that no instruction is scheduled across
@@ -421,12 +421,31 @@ __device__ inline void roe_line(const double (&Lp)[5], double EL, const double (
   D[4] = t1 * (H - u * a) + t2 * (0.5 * q2) + t5 * (H + u * a) + ts * (v * dv + w * dw);
 }
 
+// F = atanh f / f and G = 1 / F for u = f^2 below 1e-2 (dropped terms below 1e-17).
+__device__ inline void ln_series(double u, double& F, double& G) {
+  F = 1.0 + u * (1.0 / 3.0 + u * (1.0 / 5.0 + u * (1.0 / 7.0 + u * (1.0 / 9.0 + u * (1.0 / 11.0 + u * (1.0 / 13.0 + u * (1.0 / 15.0)))))));
+  G = rcp_nr(F);
+}
+
 // Chandrashekar's flux of two states (rho, u along the line, v, w) with
-// beta = rho / (2 p) and |u|^2 = q2, pressure relative to pl in the momentum.
+// beta = rho / (2 p) and |u|^2 = q2, pressure relative to pl in the momentum.  LONG: the
+// logarithmic means by their long series, else chosen (ec_means).
+template <bool LONG = false>
 __device__ inline void ec_pair(const double (&a)[4], double ba, double qa, const double (&b)[4], double bb, double qb,
                                double gm1, double pl, double (&f)[5]) {
   double rho_ln, inv_beta_ln, p_hat;
-  ec_means(a[0], b[0], ba, bb, rho_ln, inv_beta_ln, p_hat);
+  if constexpr (LONG) {
+    const double sr = a[0] + b[0], sb = ba + bb, x = rcp_nr(sr * sb);
+    const double ir = sb * x, ib = sr * x, fr = (a[0] - b[0]) * ir, fb = (ba - bb) * ib;
+    double F, G, unused;
+    ln_series(fr * fr, unused, G);
+    ln_series(fb * fb, F, unused);
+    rho_ln = 0.5 * sr * G;
+    inv_beta_ln = 2.0 * ib * F;
+    p_hat = 0.5 * sr * ib;
+  } else {
+    ec_means(a[0], b[0], ba, bb, rho_ln, inv_beta_ln, p_hat);
+  }
   const double u = 0.5 * (a[1] + b[1]), v = 0.5 * (a[2] + b[2]), w = 0.5 * (a[3] + b[3]);
   f[0] = rho_ln * u;
   f[1] = f[0] * u + (p_hat - pl);
@@ -601,16 +620,18 @@ __device__ __forceinline__ void face_values(const LineArgs& A, const R* sF, cons
 }
 
 // The pair sums acc[v][i] = sum_{m != i} Q_im f#_v(i, m) of a line with the
-// entropy-conserving pair for states with large jumps, row by row and not
-// unrolled: the logarithmic means choose between series and atanh pair by pair.
-template <int N, typename R>
+// entropy-conserving pair for states with larger jumps.  LONG: the logarithmic means by
+// their long series; else they choose between series and atanh pair by pair.  Not
+// unrolled (a second unrolled version spills registers into the usual one): the sums
+// of row m are selected by factors 0 and 1.
+template <int N, typename R, bool LONG>
 __device__ inline void ec_rows(const LineArgs& A, const R* sF, const double* head, const LineTask<N>& t, double pl,
                                R (&acc)[5][N + 1]) {
   using L = Line<N>;
   constexpr int NP = N + 1, EB = L::EB, NFLD = sizeof(R) == 4 ? 7 : 6;
   const float br = static_cast<float>(head[NP + 2]), ibr = static_cast<float>(1.0 / head[NP + 2]);
 #pragma unroll 1
-  for (int i = 0; i < NP; ++i) {
+  for (int i = 0; i < N; ++i) {
     R a[NFLD], s[5] = {0, 0, 0, 0, 0};
     const auto load = [&](int m, R* x) {
       const int l = t.node(m);
@@ -623,9 +644,9 @@ __device__ inline void ec_rows(const LineArgs& A, const R* sF, const double* hea
       if constexpr (NFLD == 7) x[6] = sF[6 * EB + l];
     };
     load(i, a);
+    const double w = 1.0 / head[i];  // Q = w D
 #pragma unroll 1
-    for (int m = 0; m < NP; ++m) {
-      if (m == i) continue;
+    for (int m = i + 1; m < NP; ++m) {
       R b[NFLD], f[5];
       load(m, b);
       if constexpr (NFLD == 7) {
@@ -633,17 +654,27 @@ __device__ inline void ec_rows(const LineArgs& A, const R* sF, const double* hea
       } else {
         const double x[4] = {a[0] + a[0], a[1] + a[1], a[2] + a[2], a[3] + a[3]};
         const double y[4] = {b[0] + b[0], b[1] + b[1], b[2] + b[2], b[3] + b[3]};
-        ec_pair(x, a[4], 4.0 * a[5], y, b[4], 4.0 * b[5], A.ph.gm1, pl, f);
+        ec_pair<LONG>(x, a[4], 4.0 * a[5], y, b[4], 4.0 * b[5], A.ph.gm1, pl, f);
       }
-      const R c = static_cast<R>(A.basis.D[i * NP + m]);
+      const R c = static_cast<R>(w * A.basis.D[i * NP + m]);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) s[v] += c * f[v];
+      for (int v = 0; v < 5; ++v) {
+        f[v] *= c;
+        s[v] += f[v];
+      }
+#pragma unroll
+      for (int r = 1; r < NP; ++r) {
+        const R sel = r == m ? R(-1) : R(0);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) acc[v][r] += sel * f[v];
+      }
     }
-    const R w = static_cast<R>(1.0 / head[i]);  // Q = w D
 #pragma unroll
-    for (int r = 0; r < NP; ++r)
+    for (int r = 0; r < N; ++r) {
+      const R sel = r == i ? R(1) : R(0);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) acc[v][r] = r == i ? w * s[v] : acc[v][r];
+      for (int v = 0; v < 5; ++v) acc[v][r] += sel * s[v];
+    }
   }
 }
 
@@ -795,8 +826,11 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
           lo[1] = q[4][m] < lo[1] ? q[4][m] : lo[1];
           hi[1] = q[4][m] > hi[1] ? q[4][m] : hi[1];
         }
-        const R lim = MIXED ? R(0.1) : R(0.01);  // sqrt of the series' f^2 bound
-        const bool large = hi[0] - lo[0] >= lim * (hi[0] + lo[0]) || hi[1] - lo[1] >= lim * (two_ref + (hi[1] + lo[1]));
+        // (sqrt of the bounds on f^2: the short series 1e-4, the long one, also that of
+        // mixed precision, 1e-2)
+        const R dr = hi[0] - lo[0], sr = hi[0] + lo[0], db = hi[1] - lo[1], sb = two_ref + (hi[1] + lo[1]);
+        const bool mid = dr >= R(0.01) * sr || db >= R(0.01) * sb;
+        const bool large = dr >= R(0.1) * sr || db >= R(0.1) * sb;
         // (momentum relative to the pressure of the line's first node, as above)
         const R pl0 = MIXED ? R(0) : static_cast<R>(q[0][0] * rcp_nr(q[4][0]));
         const R k2 = static_cast<R>((MIXED ? 0.5 : 1.0) / A.ph.gm1);
@@ -828,8 +862,11 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
           }
         };
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(large) != 0, 0)) {
-          ec_rows<N, R>(A, sF, head, t, static_cast<double>(pl0), acc);
+          ec_rows<N, R, false>(A, sF, head, t, static_cast<double>(pl0), acc);
+        } else if (!MIXED && __builtin_amdgcn_ballot_w64(mid) != 0) {
+          ec_rows<N, R, true>(A, sF, head, t, static_cast<double>(pl0), acc);
         } else {
+          settle(q);  // (nothing of the versions is shared, and held, before the branch)
 #pragma unroll
           for (int i = 0; i < N; ++i) {
 #pragma unroll
