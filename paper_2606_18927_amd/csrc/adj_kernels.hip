@@ -30,7 +30,7 @@
 // entropy correction's branch of the Roe flux, take the derivative of the
 // branch that is active (ties to the lower side L), as the CPU oracle's
 // reverse mode does.
-#include "dg_device.hpp"
+#include "line_device.hpp"
 
 namespace dg {
 namespace {
@@ -53,21 +53,6 @@ __device__ inline void kg_vjp(const double a[6], const double b[6], const double
   abar[1 + d] += 0.5 * (rho * S + p * mu[4]);
   abar[4] += 0.5 * (mu[1 + d] + ud * mu[4]);
   abar[5] += 0.5 * mass * mu[4];
-}
-
-// abar += (d f_d(a) / d a)^T mu for the Euler flux
-// f = (rho u_d, rho u u_d + p e_d, (rho e + p) u_d).
-template <int d>
-__device__ inline void euler_vjp(const double a[6], const double mu[5], double abar[6]) {
-  const double rho = a[0], ud = a[1 + d], p = a[4], e = a[5];
-  const double Sk = a[1] * mu[1] + a[2] * mu[2] + a[3] * mu[3];
-  abar[0] += ud * (mu[0] + Sk + e * mu[4]);
-  abar[1] += rho * ud * mu[1];
-  abar[2] += rho * ud * mu[2];
-  abar[3] += rho * ud * mu[3];
-  abar[1 + d] += rho * (mu[0] + Sk) + (rho * e + p) * mu[4];
-  abar[4] += mu[1 + d] + ud * mu[4];
-  abar[5] += rho * ud * mu[4];
 }
 
 // Ubar += (dP/dU)^T Pbar + (dT/dU)^T Tbar, P = (rho, u, v, w, p, e), T = p/(rho R).
@@ -336,80 +321,6 @@ __device__ inline void roe_vjp(const double so[5], const double sn[5], bool own_
   Pb[5] += Eb * so[0];
 }
 
-// Cotangents of one face node of the own element (o) in k_vjp_a: the state
-// cotangent Ud (the primitive map already applied), the cotangent Fvb of the
-// own normal viscous flux f_v,d, and om, the cotangent of the u . tau_d term
-// that a wall removes from the viscous flux.
-template <int d, bool EC>
-__device__ inline void face_vjp(const double so[5], const double lo[5], const double sn[5],
-                                const double ln[5], bool wall, bool up, double s_o, double s_n,
-                                const DevPhys& ph, double inv_w, double Ud[5], double Fvb[4],
-                                double& om) {
-  double Po[6];
-  to_prim(so, ph, Po);
-  const double sc_o = up ? inv_w : -inv_w;
-  double psi[5], phi[5], Pb[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int v = 0; v < 5; ++v) psi[v] = -sc_o * s_o * lo[v];
-#pragma unroll
-  for (int v = 0; v < 5; ++v) Ud[v] = 0.0;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) Fvb[c] = 0.0;
-  om = 0.0;
-  if (wall) {
-    // F*_c = (0, p_o e_d, 0); F*_v = f_v,o - (0, 0, 0, 0, u . tau_d)
-    Pb[4] += psi[1 + d];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) Fvb[c] -= psi[1 + c];
-    om += psi[4];
-  } else {
-    double Pn[6];
-    to_prim(sn, ph, Pn);
-    const double sc_n = -sc_o;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) phi[v] = psi[v] - sc_n * s_n * ln[v];
-    if constexpr (EC) {
-      // F*_c = f#_EC(U_L, U_R) - (1/2) Roe(U_L, U_R), the own element is L when up
-      const double Ae[6] = {Po[0], Po[1], Po[2], Po[3], Po[4], 0.5 * Po[0] / Po[4]};
-      const double Be[6] = {Pn[0], Pn[1], Pn[2], Pn[3], Pn[4], 0.5 * Pn[0] / Pn[4]};
-      double Pbe[6] = {0, 0, 0, 0, 0, 0};
-      ec_vjp<d>(Ae, Be, phi, ph.gm1, Pbe);
-      fold_beta(Ae, Pbe, Pb);
-      if (!ph.central) roe_vjp<d>(so, sn, up, phi, ph, Pb);
-    } else {
-      kg_vjp<d>(Po, Pn, phi, Pb);
-      if (!ph.central) {
-        const double co = fabs(Po[1 + d]) + sqrt(ph.gamma * Po[4] / Po[0]);
-        const double cn = fabs(Pn[1 + d]) + sqrt(ph.gamma * Pn[4] / Pn[0]);
-        // the own element is the lower side L of the face when the face is its upper one
-        const bool own_L = up;
-        const double lam = own_L ? (co >= cn ? co : cn) : (cn >= co ? cn : co);
-        const bool own_active = own_L ? (co >= cn) : (co > cn);
-        // F*_c contains -lam/2 (U_R - U_L)
-        const double dU = own_L ? 0.5 * lam : -0.5 * lam;
-        double lb = 0.0;
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          Ud[v] += dU * phi[v];
-          const double jump = own_L ? sn[v] - so[v] : so[v] - sn[v];
-          lb -= 0.5 * phi[v] * jump;
-        }
-        if (own_active) speed_vjp<d>(Po, lb, ph, Pb);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) Fvb[c] -= 0.5 * phi[1 + c];
-  }
-  // the own physical flux -(f_c - f_v)(o) of the own equation
-  double mpsi[5];
-#pragma unroll
-  for (int v = 0; v < 5; ++v) mpsi[v] = -psi[v];
-  euler_vjp<d>(Po, mpsi, Pb);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) Fvb[c] += psi[1 + c];
-  prim_vjp(so, Pb, 0.0, ph, Ud);
-}
-
 // Scale s_d of the neighbour across face (d, up) of element (ex, ey, ez).
 __device__ inline double nb_scale(const DevMesh& m, int ex, int ey, int ez, int d, bool up) {
   const int c = d == 0 ? ex : (d == 1 ? ey : ez);
@@ -422,237 +333,562 @@ __device__ inline double nb_scale(const DevMesh& m, int ex, int ey, int ez, int 
 // --------------------------------------------------------------------------
 // k_vjp_a
 // --------------------------------------------------------------------------
-// The line loops of the volume cotangents stay rolled and the kernel is
-// bounded for four waves per SIMD: unrolled, each iteration's LDS operands
-// are hoisted and the kernel needs all 256 registers (two waves per SIMD,
-// 15 % slower at degree 5).
+struct VjpArgs {
+  const double* U;
+  const double* lam;
+  double* gbar;
+  double* ubar;
+  DevMesh mesh;
+  DevPhys ph;
+  DevBasis basis;
+};
+typedef const __attribute__((address_space(4))) VjpArgs* VjpArgsPtr;
+
+__device__ inline const VjpArgs& again(VjpArgsPtr p) {
+  asm volatile("" : "+s"(p));
+  return *(const VjpArgs*)p;
+}
+
+// One workgroup per element: LW waves of line lanes (lam's derivatives along the line,
+// the pairs) and as many of face lanes (the faces at the line's ends, the gradients of
+// u, v, w, T); a node phase takes one node per lane.  LDS fields (of EB values): halves of rho, u, v, w, p, e
+// (entropy-conserving pair: beta in place of p), T, lam (5); raw gradients GR + 3 q + d;
+// viscous flux cotangents FV + 3 c + d.  At the end the lines' sums (6 per direction) take
+// the place of the latter two, the faces' primitive cotangents END that of T and lam.
+template <int N>
+struct VjpShape {
+  using L = Line<N>;
+  static constexpr int LW = L::LW, BS = N == 7 ? 512 : 128 * LW;
+  static constexpr int T = 6, LAM = 7, GR = 12, FV = 24, SUM = 12;
+  static constexpr int END = 6 * L::EB >= 12 * L::LINES ? T * L::EB : 36 * L::EB;
+  static constexpr int HEAD = 8;  // 1 / w_i
+  static constexpr size_t BYTES = 8 * (HEAD + 36 * L::EB + (END == 36 * L::EB ? 12 * L::LINES : 0));
+  static constexpr int BLOCK = N == 7 ? 4 : L::NP;  // nodes of a line held in registers
+};
+
+// dF/df of F = atanh f / f for u = f^2 below 1e-2 (dropped terms below 1e-16).
+__device__ inline double ln_series_slope(double f, double u) {
+  return 2.0 * f * (1.0 / 3.0 + u * (2.0 / 5.0 + u * (3.0 / 7.0 + u * (4.0 / 9.0 + u * (5.0 / 11.0 + u * (6.0 / 13.0 + u * (7.0 / 15.0 + u * (8.0 / 17.0))))))));
+}
+
+// The node of the pair sums: what a line lane reads of node m, x = (rho, u, v, w) / 2 in
+// the line frame, then (p, e) / 2 or (beta, |u|^2 / 4), and lam c / w_m (c = -s_d, or -2 s_d).
 template <int N, bool EC>
-__global__ __launch_bounds__(Cfg<N>::BS) __attribute__((amdgpu_waves_per_eu(4))) void k_vjp_a(const double* __restrict__ U,
-                                                       const double* __restrict__ lam,
-                                                       double* __restrict__ gbar,
-                                                       double* __restrict__ ubar, DevMesh mesh,
-                                                       DevPhys ph, DevBasis basis) {
-  using Gm = Geo<N>;
-  constexpr int NP = Gm::NP, NF = Gm::NF, NN = Gm::NN, EB = Gm::EB, DS = Gm::DS;
-  constexpr int EPB = Cfg<N>::EPB, BS = Cfg<N>::BS;
-  __shared__ double sD[NP * DS];
-  __shared__ double sP[EPB][6][EB];
-  __shared__ double sL[EPB][5][EB];
-  __shared__ double sFU[EPB][6][5][NF];
-  __shared__ double sFV[EPB][6][5][NF];
-  __shared__ double sT[EPB][EB];          // T, for the forward lifting
-  __shared__ double ssq[EPB][6][4][NF];   // BR1 lifting corrections of the faces
+__device__ __forceinline__ void vjp_node(const double* sF, const double* inv_w, const LineTask<N>& t, int m, double c,
+                                         double (&x)[11]) {
+  using S = VjpShape<N>;
+  constexpr int EB = Line<N>::EB;
+  const int l = t.node(m);
+  x[0] = sF[l];
+  x[1] = sF[(1 + t.d) * EB + l];
+  x[2] = sF[(1 + t.d1) * EB + l];
+  x[3] = sF[(1 + t.d2) * EB + l];
+  x[4] = sF[4 * EB + l];
+  x[5] = EC ? x[1] * x[1] + x[2] * x[2] + x[3] * x[3] : sF[5 * EB + l];
+  const double f = c * inv_w[m];
+  x[6] = f * sF[S::LAM * EB + l];
+  x[7] = f * sF[(S::LAM + 1 + t.d) * EB + l];
+  x[8] = f * sF[(S::LAM + 1 + t.d1) * EB + l];
+  x[9] = f * sF[(S::LAM + 1 + t.d2) * EB + l];
+  x[10] = f * sF[(S::LAM + 4) * EB + l];
+}
 
-  const int tid = threadIdx.x;
-  const long long nE = mesh.nE;
-  const long long stride = nE * NN;
-  const long long e0 = static_cast<long long>(xcd_remap(blockIdx.x, gridDim.x)) * EPB;
-  for (int t = tid; t < NP * NP; t += BS) sD[(t / NP) * DS + t % NP] = basis.D[t];
-  int ex0 = 0, ey0 = 0, ez0 = 0;
-  elem_coords(e0 < nE ? e0 : 0, mesh, ex0, ey0, ez0);
+// One Kennedy-Gruber pair, cotangent mu = Q_im (lam_i / w_i - lam_m / w_m) (-2 s_d)
+// on f#(i, m) (half of it here, for the means).  f# depends on sums only, so both nodes
+// take the same increments; with S = mu_0 + u . mu_m + e mu_4 and m = rho u_d
+//   (u_d S, m mu_m + e_d (rho S + p mu_4), mu_d + u_d mu_4, m mu_4).
+__device__ __forceinline__ void kg_pair_vjp(const double (&a)[11], const double (&b)[11], double q, double (&ya)[6],
+                                            double (&yb)[6]) {
+  const double rho = a[0] + b[0], u = a[1] + b[1], v = a[2] + b[2], w = a[3] + b[3], p = a[4] + b[4], e = a[5] + b[5];
+  const double m0 = q * (a[6] - b[6]), m1 = q * (a[7] - b[7]), m2 = q * (a[8] - b[8]), m3 = q * (a[9] - b[9]),
+               m4 = q * (a[10] - b[10]);
+  const double S = m0 + u * m1 + v * m2 + w * m3 + e * m4;
+  const double m = rho * u;
+  const double du = m * m1 + rho * S + p * m4, dp = m1 + u * m4;
+  ya[0] += u * S;
+  yb[0] += u * S;
+  ya[1] += du;
+  yb[1] += du;
+  ya[2] += m * m2;
+  yb[2] += m * m2;
+  ya[3] += m * m3;
+  yb[3] += m * m3;
+  ya[4] += dp;
+  yb[4] += dp;
+  ya[5] += m * m4;
+  yb[5] += m * m4;
+}
 
-  const int le = EPB == 1 ? 0 : tid / NN;
-  const int node = tid - le * NN;
-  const long long e = EPB == 1 ? e0 : e0 + le;
-  const bool active = (EPB == 1 ? tid < NN : le < EPB) && e < nE;
-  const int i = node % NP, j = (node / NP) % NP, k = node / NF;
-  const int l = Gm::lds(i, j, k);
-
-  // P1: node lanes stage primitives and lam; face lanes form the face cotangents
-  double own[6] = {0, 0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
-  int ex = ex0, ey = ey0, ez = ez0;
-  if (active) {
-    if (EPB > 1) elem_coords(e, mesh, ex, ey, ez);
-    double s[5];
-    load_state(U, stride, e * NN + node, s);
-    to_prim(s, ph, own);
-    if (EC) own[5] = 0.5 * own[0] / own[4];  // beta in place of e
-    load_state(lam, stride, e * NN + node, lo);
-#pragma unroll
-    for (int q = 0; q < 6; ++q) sP[le][q][l] = own[q];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) sL[le][v][l] = lo[v];
-    sT[le][l] = own[4] * ph.inv_R / own[0];
+// One entropy-conserving pair (ec_vjp for both nodes at once): y[4] is the cotangent of
+// beta.  MEANS: the logarithmic means' factors by the short series (f^2 below 1e-4), the
+// long one (1e-2), or chosen pair by pair.
+template <int MEANS>
+__device__ __forceinline__ void ec_pair_vjp(const double (&a)[11], const double (&b)[11], double q, double kap,
+                                            double (&ya)[6], double (&yb)[6]) {
+  const double sr = a[0] + b[0], sb = a[4] + b[4];  // {{rho}}, 2 {{beta}}
+  const double x = rcp_nr(sr * sb);
+  const double ir = sb * x, ib = sr * x;
+  const double fr = (a[0] - b[0]) * ir, fb = (a[4] - b[4]) * ib;
+  const double ur = fr * fr, ub = fb * fb;
+  double G, dG, F, dF;
+  if constexpr (MEANS == 0) {
+    G = 1.0 - ur * (1.0 / 3.0 + ur * (4.0 / 45.0 + ur * (44.0 / 945.0)));
+    dG = -2.0 * fr * (1.0 / 3.0 + ur * (8.0 / 45.0 + ur * (132.0 / 945.0)));
+    F = 1.0 + ub * (1.0 / 3.0 + ub * (0.2 + ub * (1.0 / 7.0)));
+    dF = 2.0 * fb * (1.0 / 3.0 + ub * (0.4 + ub * (3.0 / 7.0)));
+  } else if constexpr (MEANS == 1) {
+    double unused;
+    ln_series(ur, unused, G);
+    dG = -ln_series_slope(fr, ur) * (G * G);
+    ln_series(ub, F, unused);
+    dF = ln_series_slope(fb, ub);
+  } else {
+    double unused0, unused1;
+    ln_mean_factors(fr, G, dG, unused0, unused1, true);
+    ln_mean_factors(fb, unused0, unused1, F, dF, false);
   }
-  if (tid < n_face_tasks<N>()) {
-    const FaceTask<N> ft(tid);
-    const long long te = EPB == 1 ? e0 : e0 + ft.le;
-    if (te < nE) {
-      int fx = ex0, fy = ey0, fz = ez0;
-      if (EPB > 1) elem_coords(te, mesh, fx, fy, fz);
-      const long long nb = neighbour(mesh, fx, fy, fz, ft.d, ft.up);
-      const bool wall = nb < 0;
-      const long long oidx = te * NN + ft.own_node();
-      double so[5], fl[5], sn[5] = {1, 0, 0, 0, 1}, ln[5] = {0, 0, 0, 0, 0};
-      load_state(U, stride, oidx, so);
-      load_state(lam, stride, oidx, fl);
-      double s_n = 0.0;
-      if (!wall) {
-        const long long nidx = nb * NN + ft.nb_node();
-        load_state(U, stride, nidx, sn);
-        load_state(lam, stride, nidx, ln);
-        s_n = nb_scale(mesh, fx, fy, fz, ft.d, ft.up);
+  const double m0 = q * (a[6] - b[6]), m1 = q * (a[7] - b[7]), m2 = q * (a[8] - b[8]), m3 = q * (a[9] - b[9]),
+               m4 = q * (a[10] - b[10]);
+  const double u = a[1] + b[1], v = a[2] + b[2], w = a[3] + b[3];
+  const double rho_ln = sr * G, p_hat = sr * ib, F1 = rho_ln * u;
+  const double A = m0 + m1 * u + m2 * v + m3 * w +
+                   m4 * (2.0 * kap * ib * F - (a[5] + b[5]) + (u * u + v * v + w * w));
+  const double Bp = m1 + m4 * u, hb = 0.5 * ib * Bp;
+  // d rho_ln / d rho_a = G / 2 + rho_b G' / (2 {{rho}}), and of b with G' odd
+  const double Au = A * u, Ag = 0.5 * Au * G + hb, At = Au * dG * ir;
+  ya[0] += Ag + b[0] * At;
+  yb[0] += Ag - a[0] * At;
+  // d (1 / beta_ln) / d beta_a = ib^2 (-2 F + 4 beta_b ib F')
+  const double k5 = F1 * m4 * kap * ib * ib;
+  const double c5 = -2.0 * k5 * F - p_hat * ib * Bp, t5 = 4.0 * k5 * ib * dF;
+  ya[4] += c5 + b[4] * t5;
+  yb[4] += c5 - a[4] * t5;
+  const double f4 = F1 * m4;
+  const double s1 = 0.5 * (F1 * m1 + m4 * p_hat + A * rho_ln) + f4 * u, s2 = 0.5 * F1 * m2 + f4 * v,
+               s3 = 0.5 * F1 * m3 + f4 * w;
+  ya[1] += s1 - f4 * a[1];
+  yb[1] += s1 - f4 * b[1];
+  ya[2] += s2 - f4 * a[2];
+  yb[2] += s2 - f4 * b[2];
+  ya[3] += s3 - f4 * a[3];
+  yb[3] += s3 - f4 * b[3];
+}
+
+// All pairs of a line.  A line of eight nodes with its cotangents and sums exceeds the
+// registers: blocks of four, the second block's nodes one by one against the first.
+template <int N, bool EC>
+__device__ __forceinline__ void line_pairs(const DevBasis& b, const double* sF, const LineTask<N>& t, double c, double kap,
+                                           double (&y)[N + 1][6]) {
+  constexpr int NP = N + 1, H = VjpShape<N>::BLOCK;
+  double x[H][11];
+  const auto pair = [&](const double (&p)[11], const double (&q)[11], int i, int m) {
+    if constexpr (EC)
+      ec_pair_vjp<0>(p, q, q_im<N, double>(b, i, m), kap, y[i], y[m]);
+    else
+      kg_pair_vjp(p, q, q_im<N, double>(b, i, m), y[i], y[m]);
+  };
+#pragma unroll
+  for (int b0 = 0; b0 < NP; b0 += H) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) vjp_node<N, EC>(sF, b.inv_w, t, b0 + i, c, x[i]);
+    if (EC) settle(x);  // (nothing of the versions is shared, and held, before the branch)
+#pragma unroll
+    for (int i = 0; i < H; ++i)
+#pragma unroll
+      for (int m = i + 1; m < H; ++m) {
+        pair(x[i], x[m], b0 + i, b0 + m);
+        if (EC || m % 2) __builtin_amdgcn_sched_barrier(0);
       }
-      const double s_o = mesh.s[ft.d][ft.d == 0 ? fx : (ft.d == 1 ? fy : fz)];
-      if (ph.viscous) {
-        // forward lifting correction (q* - q_own) (+-1/w_end) of this face node
-        const Prim Po = primitives(so, ph);
-        const double qo[4] = {Po.u, Po.v, Po.w, Po.T};
-        double qs[4];
-        wall_lifting_value(mesh, ft.d, qo, qs);
-        if (!wall) {
-          const Prim Pn = primitives(sn, ph);
-          qs[0] = 0.5 * (qo[0] + Pn.u);
-          qs[1] = 0.5 * (qo[1] + Pn.v);
-          qs[2] = 0.5 * (qo[2] + Pn.w);
-          qs[3] = 0.5 * (qo[3] + Pn.T);
+    if (b0 == 0)
+#pragma unroll
+      for (int m = H; m < NP; ++m) {
+        double z[11];
+        vjp_node<N, EC>(sF, b.inv_w, t, m, c, z);
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+          pair(x[i], z, i, m);
+          if (EC || i % 2) __builtin_amdgcn_sched_barrier(0);
         }
-        const double sc = ft.up ? basis.inv_w_end : -basis.inv_w_end;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) ssq[ft.le][ft.f][c][ft.ab] = (qs[c] - qo[c]) * sc;
       }
-      double Ud[5], Fvb[4], om;
-      if (ft.d == 0)
-        face_vjp<0, EC>(so, fl, sn, ln, wall, ft.up, s_o, s_n, ph, basis.inv_w_end, Ud, Fvb, om);
-      else if (ft.d == 1)
-        face_vjp<1, EC>(so, fl, sn, ln, wall, ft.up, s_o, s_n, ph, basis.inv_w_end, Ud, Fvb, om);
-      else
-        face_vjp<2, EC>(so, fl, sn, ln, wall, ft.up, s_o, s_n, ph, basis.inv_w_end, Ud, Fvb, om);
+  }
+}
+
+// The same with larger jumps (MEANS 1 or 2), not unrolled (further unrolled versions
+// spill registers into the usual one): the sums of row m are selected by factors 0 and 1.
+template <int N, int MEANS>
+__device__ inline void line_rows_ec(const DevBasis& b, const double* sF, const double* sW, const LineTask<N>& t, double c,
+                                    double kap, double (&y)[N + 1][6]) {
+  constexpr int NP = N + 1;
+#pragma unroll 1
+  for (int i = 0; i < N; ++i) {
+    double x[11], z[6] = {0, 0, 0, 0, 0, 0};
+    vjp_node<N, true>(sF, sW, t, i, c, x);
+    const double w = 1.0 / sW[i];  // Q = w D
+#pragma unroll 1
+    for (int m = i + 1; m < NP; ++m) {
+      double q[11], f[6] = {0, 0, 0, 0, 0, 0};
+      vjp_node<N, true>(sF, sW, t, m, c, q);
+      ec_pair_vjp<MEANS>(x, q, w * b.D[i * NP + m], kap, z, f);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) sFU[ft.le][ft.f][v][ft.ab] = Ud[v];
+      for (int r = 1; r < NP; ++r) {
+        const double sel = r == m ? 1.0 : 0.0;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) sFV[ft.le][ft.f][c][ft.ab] = Fvb[c];
-      sFV[ft.le][ft.f][4][ft.ab] = om;
+        for (int v = 0; v < 5; ++v) y[r][v] += sel * f[v];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const double sel = r == i ? 1.0 : 0.0;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) y[r][v] += sel * z[v];
     }
   }
-  __syncthreads();
-  if (!active) return;
+}
 
-  // P2: node lanes
-  const bool visc = ph.viscous != 0;
-  // viscosity and conductivity at this node's temperature (Sutherland's law,
-  // or constant: r = 1)
-  const double Tn = sT[le][l];
-  const double rT = viscosity_ratio(ph, Tn);
-  const double mu = ph.mu * rT, kappa = ph.kappa * rT;
-  // forward BR1 gradients g[3 q + d] of q = (u, v, w, T) at this node
-  double g[12];
+// Cotangents of the own primitives Pb = (rho, u, v, w, p, e), line frame, through one
+// face's convective flux F*: P own primitives, lo own lam, sn and ln of the neighbour,
+// so_iw and sn_iw the two elements' s_d / w_end.  The own side is L of an upper face.
+// (In the weak form the own physical flux cancels with the diagonal of the volume sum.)
+template <bool EC>
+__device__ __forceinline__ void face_vjp(const DevPhys& ph, const double (&P)[6], const double (&lo)[5],
+                                         const double (&sn)[5], const double (&ln)[5], bool wall, bool up, double so_iw,
+                                         double sn_iw, double (&Pb)[6]) {
 #pragma unroll
-  for (int c = 0; c < 12; ++c) g[c] = 0.0;
-  if (visc) {
-    const double sx = mesh.s[0][ex], sy = mesh.s[1][ey], sz = mesh.s[2][ez];
+  for (int q = 0; q < 6; ++q) Pb[q] = 0.0;
+  const double sg = up ? -1.0 : 1.0;
+  if (wall) {  // F*_c = (0, p_o e_d, 0)
+    Pb[4] = sg * so_iw * lo[1];
+    return;
+  }
+  double phi[5];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const double* q = c < 3 ? sP[le][1 + c] : sT[le];
-      double ax = 0.0, ay = 0.0, az = 0.0;
+  for (int v = 0; v < 5; ++v) phi[v] = sg * (so_iw * lo[v] - sn_iw * ln[v]);
+  double Pn[6];
+  to_prim(sn, ph, Pn);
+  const double so[5] = {P[0], P[0] * P[1], P[0] * P[2], P[0] * P[3], P[0] * P[5]};
+  if constexpr (EC) {
+    // F*_c = f#_EC(U_L, U_R) - (1/2) Roe(U_L, U_R)
+    const double Ae[6] = {P[0], P[1], P[2], P[3], P[4], 0.5 * P[0] / P[4]};
+    const double Be[6] = {Pn[0], Pn[1], Pn[2], Pn[3], Pn[4], 0.5 * Pn[0] / Pn[4]};
+    double Pbe[6] = {0, 0, 0, 0, 0, 0};
+    ec_vjp<0>(Ae, Be, phi, ph.gm1, Pbe);
+    fold_beta(Ae, Pbe, Pb);
+    if (!ph.central) roe_vjp<0>(so, sn, up, phi, ph, Pb);
+  } else {
+    kg_vjp<0>(P, Pn, phi, Pb);
+    if (!ph.central) {
+      const double co = fabs(P[1]) + sqrt(ph.gamma * P[4] / P[0]);
+      const double cn = fabs(Pn[1]) + sqrt(ph.gamma * Pn[4] / Pn[0]);
+      const double lam = up ? (co >= cn ? co : cn) : (cn >= co ? cn : co);
+      const bool own_active = up ? (co >= cn) : (co > cn);
+      // F*_c contains -lam/2 (U_R - U_L)
+      const double dU = up ? 0.5 * lam : -0.5 * lam;
+      double lb = 0.0, Ud[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        Ud[v] = dU * phi[v];
+        lb -= 0.5 * phi[v] * (up ? sn[v] - so[v] : so[v] - sn[v]);
+      }
+      Pb[0] += Ud[0] + P[1] * Ud[1] + P[2] * Ud[2] + P[3] * Ud[3] + P[5] * Ud[4];
+      Pb[1] += P[0] * Ud[1];
+      Pb[2] += P[0] * Ud[2];
+      Pb[3] += P[0] * Ud[3];
+      Pb[5] += P[0] * Ud[4];
+      if (own_active) speed_vjp<0>(P, lb, ph, Pb);
+    }
+  }
+}
+
+// ROLE 0: line lanes, 1: face lanes, 2: neither (the node phases only).
+template <int N, bool EC, int ROLE>
+__device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const head, const int e, const int tid) {
+  using L = Line<N>;
+  using S = VjpShape<N>;
+  constexpr int NP = L::NP, NF = L::NF, NN = L::NN, EB = L::EB, LINES = L::LINES;
+  double* const sW = head;
+  double* const sF = head + S::HEAD;
+  double y[NP][6];     // line lanes: cotangents of the line's nodes
+  double pe[2][6];     // face lanes: those through the faces at its ends
+  const Place pl(again(args).mesh, e);
+  const bool visc = again(args).ph.viscous != 0;
+  {
+    const VjpArgs& A = again(args);
+    const long long stride = A.mesh.nE * NN;
+    const unsigned n = tid < NN ? tid : 0;
+    double u[5], l[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) u[v] = (A.U + v * stride + static_cast<long long>(e) * NN)[n];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) l[v] = (A.lam + v * stride + static_cast<long long>(e) * NN)[n];
+    if (tid < NP) {
+      double w = A.basis.inv_w[0];
+#pragma unroll
+      for (int i = 1; i < NP; ++i) w = tid == i ? A.basis.inv_w[i] : w;
+      sW[tid] = w;
+    }
+    double sn[2][5], ln[2][5], s_n[2];  // the neighbours' at the line's ends
+    if constexpr (ROLE < 2) {
+      const LineTask<N> t(ROLE == 0 ? tid : tid - 64 * S::LW);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (ROLE == 1) fetch_end<N>(A.U, stride, pl, e, t, h, sn[h]);
+        fetch_end<N>(A.lam, stride, pl, e, t, h, ln[h]);
+        s_n[h] = nb_scale(A.mesh, pl.ex, pl.ey, pl.ez, t.d, h != 0);
+      }
+    }
+    if (tid < NN) {
+      double P[6];
+      to_prim(u, A.ph, P);
+      const int p = L::at(n % NP, (n / NP) % NP, n / NF);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sF[q * EB + p] = 0.5 * P[q];
+      if (EC) {
+        sF[4 * EB + p] = 0.5 * P[0] / P[4];
+      } else {
+        sF[4 * EB + p] = 0.5 * P[4];
+        sF[5 * EB + p] = 0.5 * P[5];
+      }
+      sF[S::T * EB + p] = P[4] * A.ph.inv_R / P[0];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sF[(S::LAM + v) * EB + p] = l[v];
+    }
+    phase_end();
+
+    // ---- pairs on the line waves; faces and derivatives on the face waves ----
+    if constexpr (ROLE == 1) {
+      const VjpArgs& B = again(args);
+      const LineTask<N> t(again(tid) - 64 * S::LW);
+      const double iw = B.basis.inv_w[0];
+      const double s = t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz);
+      double gq[2][4];  // ghosts: u, v, w (halves), T
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int p = t.node(h ? N : 0);
+        const bool wall = pl.neighbour(t.d, h) < 0;
+        const double siw = s * iw, niw = iw * s_n[h];
+        const double r = 2.0 * sF[p], T = sF[S::T * EB + p];
+        double P[6] = {r, 2.0 * sF[(1 + t.d) * EB + p], 2.0 * sF[(1 + t.d1) * EB + p], 2.0 * sF[(1 + t.d2) * EB + p], 0, 0};
+        if (EC) {
+          P[4] = 0.5 * r / sF[4 * EB + p];
+          P[5] = P[4] / (B.ph.gm1 * r) + 0.5 * (P[1] * P[1] + P[2] * P[2] + P[3] * P[3]);
+        } else {
+          P[4] = 2.0 * sF[4 * EB + p];
+          P[5] = 2.0 * sF[5 * EB + p];
+        }
+        const double lo[5] = {sF[S::LAM * EB + p], sF[(S::LAM + 1 + t.d) * EB + p], sF[(S::LAM + 1 + t.d1) * EB + p],
+                              sF[(S::LAM + 1 + t.d2) * EB + p], sF[(S::LAM + 4) * EB + p]};
+        face_vjp<EC>(B.ph, P, lo, sn[h], ln[h], wall, h != 0, siw, niw, pe[h]);
+        const double ir = rcp_nr(sn[h][0]);
+        const double v0 = sn[h][1] * ir, v1 = sn[h][2] * ir, v2 = sn[h][3] * ir;
+        const double Tn = B.ph.gm1 * (sn[h][4] - 0.5 * (sn[h][1] * v0 + sn[h][2] * v1 + sn[h][3] * v2)) * B.ph.inv_R * ir;
+        gq[h][0] = wall ? -0.5 * P[1] : 0.5 * v0;
+        gq[h][1] = wall ? -0.5 * P[2] : 0.5 * v1;
+        gq[h][2] = wall ? -0.5 * P[3] : 0.5 * v2;
+        gq[h][3] = wall ? 2.0 * B.mesh.T_wall - T : Tn;
+      }
+      settle(pe);
+      settle(gq);
+      if (visc) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int k = v == 0 ? t.d : (v == 1 ? t.d1 : (v == 2 ? t.d2 : 3));
+          double q[NP], g[NP];
+#pragma unroll
+          for (int m = 0; m < NP; ++m) q[m] = sF[(v == 3 ? S::T : 1 + k) * EB + t.node(m)];
+          line_derivative<N, double, false>(B.basis, q, gq[0][v], gq[1][v], g);
+#pragma unroll
+          for (int m = 0; m < NP; ++m) sF[(S::GR + 3 * k + t.d) * EB + t.node(m)] = g[m];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if constexpr (ROLE == 0) {
+      if (visc) {
+        // lam of momentum and energy -> the flux cotangents -w s dlam/dx (a wall's flux
+        // takes the own stresses and heat flux: ghost -lam)
+        const VjpArgs& B = again(args);
+        const LineTask<N> t(again(tid));
+        const double iw = B.basis.inv_w[0], s = t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz);
+        const bool wall[2] = {pl.neighbour(t.d, 0) < 0, pl.neighbour(t.d, 1) < 0};
+        const double gs[2] = {iw * (wall[0] ? -s : s_n[0]), iw * (wall[1] ? -s : s_n[1])};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int k = v == 0 ? t.d : (v == 1 ? t.d1 : (v == 2 ? t.d2 : 3));
+          double q[NP], g[NP];
+#pragma unroll
+          for (int m = 0; m < NP; ++m) q[m] = sF[(S::LAM + 1 + k) * EB + t.node(m)];
+          const double g0 = gs[0] * (wall[0] ? q[0] : ln[0][1 + v]), g1 = gs[1] * (wall[1] ? q[N] : ln[1][1 + v]);
+#pragma unroll
+          for (int m = 0; m < NP; ++m) q[m] *= -s * B.basis.inv_w[m];
+          line_derivative<N, double, false>(B.basis, q, -g0, -g1, g);
+#pragma unroll
+          for (int m = 0; m < NP; ++m) sF[(S::FV + 3 * k + t.d) * EB + t.node(m)] = g[m];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  }
+  if constexpr (ROLE == 0) {
+    const VjpArgs& A = again(args);
+    const LineTask<N> t(again(tid));
+    const double s = t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz);
+#pragma unroll
+    for (int m = 0; m < NP; ++m)
+#pragma unroll
+      for (int v = 0; v < 6; ++v) y[m][v] = 0.0;
+    if constexpr (EC) {
+      // f of the largest pair is that of the line's extremes: small for rho and beta
+      // on all lines of the wave, all means take their series
+      double lo[2], hi[2];
 #pragma unroll
       for (int m = 0; m < NP; ++m) {
-        ax += sD[i * DS + m] * q[Gm::lds(m, j, k)];
-        ay += sD[j * DS + m] * q[Gm::lds(i, m, k)];
-        az += sD[k * DS + m] * q[Gm::lds(i, j, m)];
+        const double r = sF[t.node(m)], be = sF[4 * EB + t.node(m)];
+        lo[0] = m == 0 || r < lo[0] ? r : lo[0];
+        hi[0] = m == 0 || r > hi[0] ? r : hi[0];
+        lo[1] = m == 0 || be < lo[1] ? be : lo[1];
+        hi[1] = m == 0 || be > hi[1] ? be : hi[1];
       }
-      if (i == 0) ax += ssq[le][0][c][j + NP * k];
-      if (i == N) ax += ssq[le][1][c][j + NP * k];
-      if (j == 0) ay += ssq[le][2][c][i + NP * k];
-      if (j == N) ay += ssq[le][3][c][i + NP * k];
-      if (k == 0) az += ssq[le][4][c][i + NP * j];
-      if (k == N) az += ssq[le][5][c][i + NP * j];
-      g[3 * c + 0] = sx * ax;
-      g[3 * c + 1] = sy * ay;
-      g[3 * c + 2] = sz * az;
+      const double dr = hi[0] - lo[0], sr = hi[0] + lo[0], db = hi[1] - lo[1], sb = hi[1] + lo[1];
+      const bool mid = dr >= 0.01 * sr || db >= 0.01 * sb, large = dr >= 0.1 * sr || db >= 0.1 * sb;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(large) != 0, 0))
+        line_rows_ec<N, 2>(A.basis, sF, sW, t, -2.0 * s, 0.5 / A.ph.gm1, y);
+      else if (__builtin_amdgcn_ballot_w64(mid) != 0)
+        line_rows_ec<N, 1>(A.basis, sF, sW, t, -2.0 * s, 0.5 / A.ph.gm1, y);
+      else
+        line_pairs<N, true>(A.basis, sF, t, -2.0 * s, 0.5 / A.ph.gm1, y);
+    } else {
+      line_pairs<N, false>(A.basis, sF, t, -s, 0.0, y);
     }
+    settle(y);
   }
-  // stress tau_ab (a, b in 0..2), symmetric
-  const double dv = (2.0 / 3.0) * (g[0] + g[4] + g[8]);
-  double tau[9];
+  phase_end();
+
+  // ---- node phase: transposed viscous flux ----------------------------------
+  double Pu[3] = {0, 0, 0}, Tb = 0.0;
+  const int tn = again(tid);
+  const unsigned n = tn < NN ? tn : 0;
+  const int i = n % NP, j = (n / NP) % NP, k = n / NF, l = L::at(i, j, k);
+  if (visc && tn < NN) {
+    const VjpArgs& A = again(args);
+    const double c[3] = {2.0 * (pl.sx * sW[i]), 2.0 * (pl.sy * sW[j]), 2.0 * (pl.sz * sW[k])};
+    const double T = sF[S::T * EB + l], rT = viscosity_ratio(A.ph, T);
+    const double mu = A.ph.mu * rT, kappa = A.ph.kappa * rT;
+    double g[9];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+    for (int q = 0; q < 9; ++q) g[q] = c[q % 3] * sF[(S::GR + q) * EB + l];
+    const double l4 = 0.5 * sF[(S::LAM + 4) * EB + l];
+    double tb[9], gT[3], eb[3];
 #pragma unroll
-    for (int b = 0; b < 3; ++b) tau[3 * a + b] = mu * (g[3 * a + b] + g[3 * b + a] - (a == b ? dv : 0.0));
-
-  double Pb[6] = {0, 0, 0, 0, 0, 0};
-  double tb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  double gT[3] = {0, 0, 0};
-  double Ub[5] = {0, 0, 0, 0, 0};
-
-#define DG_ADJ_DIRECTION(D)                                                                    \
-  {                                                                                            \
-    const int idx = D == 0 ? i : (D == 1 ? j : k);                                             \
-    const int ab = D == 0 ? j + NP * k : (D == 1 ? i + NP * k : i + NP * j);                   \
-    const double sd = mesh.s[D][D == 0 ? ex : (D == 1 ? ey : ez)];                              \
-    double Fv[4] = {0, 0, 0, 0};                                                               \
-    _Pragma("unroll 1") for (int m = 0; m < NP; ++m) {                                         \
-      const int lm = D == 0 ? Gm::lds(m, j, k) : (D == 1 ? Gm::lds(i, m, k) : Gm::lds(i, j, m)); \
-      const double Dim = sD[idx * DS + m], Dmi = sD[m * DS + idx];                              \
-      double b[6], lmv[5], mu5[5];                                                             \
-      _Pragma("unroll") for (int q = 0; q < 6; ++q) b[q] = sP[le][q][lm];                      \
-      _Pragma("unroll") for (int v = 0; v < 5; ++v) lmv[v] = sL[le][v][lm];                    \
-      _Pragma("unroll") for (int v = 0; v < 5; ++v) mu5[v] = -2.0 * sd * (Dim * lo[v] + Dmi * lmv[v]); \
-      if constexpr (EC)                                                                        \
-        ec_vjp<D>(own, b, mu5, ph.gm1, Pb);                                                    \
-      else                                                                                     \
-        kg_vjp<D>(own, b, mu5, Pb);                                                            \
-      _Pragma("unroll") for (int c = 0; c < 4; ++c) Fv[c] += sd * Dmi * lmv[1 + c];             \
-    }                                                                                          \
-    double omd = 0.0;                                                                          \
-    if (idx == 0) {                                                                            \
-      _Pragma("unroll") for (int c = 0; c < 4; ++c) Fv[c] += sFV[le][2 * D][c][ab];            \
-      omd += sFV[le][2 * D][4][ab];                                                            \
-      _Pragma("unroll") for (int v = 0; v < 5; ++v) Ub[v] += sFU[le][2 * D][v][ab];            \
-    }                                                                                          \
-    if (idx == N) {                                                                            \
-      _Pragma("unroll") for (int c = 0; c < 4; ++c) Fv[c] += sFV[le][2 * D + 1][c][ab];        \
-      omd += sFV[le][2 * D + 1][4][ab];                                                        \
-      _Pragma("unroll") for (int v = 0; v < 5; ++v) Ub[v] += sFU[le][2 * D + 1][v][ab];        \
-    }                                                                                          \
-    if (visc) {                                                                                \
-      const double eb = Fv[3] + omd;                                                           \
-      _Pragma("unroll") for (int a = 0; a < 3; ++a) {                                          \
-        tb[3 * a + D] += Fv[a] + eb * own[1 + a];                                              \
-        Pb[1 + a] += eb * tau[3 * a + D];                                                      \
-      }                                                                                        \
-      gT[D] += kappa * Fv[3];                                                                  \
-    }                                                                                          \
-  }
-  DG_ADJ_DIRECTION(0)
-  DG_ADJ_DIRECTION(1)
-  DG_ADJ_DIRECTION(2)
-#undef DG_ADJ_DIRECTION
-
-  const long long idx = e * NN + node;
-  if (visc) {
-    const double tr = tb[0] + tb[4] + tb[8];
+    for (int d = 0; d < 3; ++d) {
+      const int x = d == 0 ? i : (d == 1 ? j : k);
+      gT[d] = sF[(S::FV + 9 + d) * EB + l];
+      // a wall's energy flux is without the stresses' work
+      const double om = (x == 0 && pl.nb[2 * d] < 0 ? c[d] * l4 : 0.0) - (x == N && pl.nb[2 * d + 1] < 0 ? c[d] * l4 : 0.0);
+      eb[d] = gT[d] + om;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) tb[3 * q + d] = sF[(S::FV + 3 * q + d) * EB + l] + eb[d] * (2.0 * sF[(1 + q) * EB + l]);
+    }
+    const double dv = (2.0 / 3.0) * (g[0] + g[4] + g[8]), tr = (2.0 / 3.0) * mu * (tb[0] + tb[4] + tb[8]);
+    const long long stride = A.mesh.nE * NN;
+    double* out = A.gbar + static_cast<long long>(e) * NN;
+    double st = 0.0;
 #pragma unroll
     for (int x = 0; x < 3; ++x)
 #pragma unroll
-      for (int y = 0; y < 3; ++y)
-        store_once(&gbar[(3 * x + y) * stride + idx],
-                   mu * (tb[3 * x + y] + tb[3 * y + x]) - (x == y ? (2.0 / 3.0) * mu * tr : 0.0));
+      for (int y2 = 0; y2 < 3; ++y2) {
+        const double gb = mu * (tb[3 * x + y2] + tb[3 * y2 + x]) - (x == y2 ? tr : 0.0);
+        store_once(&(out + (3 * x + y2) * stride)[n], gb);
+        st += gb * g[3 * x + y2];
+        Pu[x] += eb[y2] * (mu * (g[3 * x + y2] + g[3 * y2 + x] - (x == y2 ? dv : 0.0)));
+      }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) store_once(&gbar[(9 + d) * stride + idx], gT[d]);
+    for (int d = 0; d < 3; ++d) {
+      store_once(&(out + (9 + d) * stride)[n], kappa * gT[d]);
+      st += kappa * gT[d] * (0.5 * c[d] * sF[(S::GR + 9 + d) * EB + l]);
+    }
+    // Sutherland's law: tau and q scale with r(T), d ln r / dT = 3 / (2 T) - 1 / (T + S)
+    if (A.ph.suth) Tb = (1.5 / T - 1.0 / (T + A.ph.suth_S)) * st;
   }
-  // Sutherland's law: tau and q scale with r(T), so T gets
-  // (d ln r / dT) (tbar : tau + sum_d Fv_d,E q_d), d ln r / dT = 3 / (2 T) - 1 / (T + S)
-  double Tb = 0.0;
-  if (visc && ph.suth) {
-    double st = 0.0;
+  phase_end();
+
+  // ---- sums of the lines and faces, transposed primitive map ----------------
+  if constexpr (ROLE == 0) {
+    const LineTask<N> t(again(tid));
+    double* o = sF + (S::SUM + 6 * t.d) * EB;
 #pragma unroll
-    for (int c = 0; c < 9; ++c) st += tb[c] * tau[c];
+    for (int m = 0; m < NP; ++m) {
+      const int p = t.node(m);
+      o[p] = y[m][0];
+      o[(1 + t.d) * EB + p] = y[m][1];
+      o[(1 + t.d1) * EB + p] = y[m][2];
+      o[(1 + t.d2) * EB + p] = y[m][3];
+      o[4 * EB + p] = y[m][4];
+      if (!EC) o[5 * EB + p] = y[m][5];
+    }
+  } else if constexpr (ROLE == 1) {
+    const LineTask<N> t(again(tid) - 64 * S::LW);
+    double* o = sF + S::END + t.d * NF + t.ab;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) st += gT[d] * g[9 + d];
-    Tb = (1.5 / Tn - 1.0 / (Tn + ph.suth_S)) * st;
+    for (int h = 0; h < 2; ++h) {
+      o[(6 * h) * LINES] = pe[h][0];
+      o[(6 * h + 1 + t.d) * LINES] = pe[h][1];
+      o[(6 * h + 1 + t.d1) * LINES] = pe[h][2];
+      o[(6 * h + 1 + t.d2) * LINES] = pe[h][3];
+      o[(6 * h + 4) * LINES] = pe[h][4];
+      o[(6 * h + 5) * LINES] = pe[h][5];
+    }
   }
-  if (EC) {
-    // slot 5 holds the cotangent of beta = rho / (2 p)
-    const double Pbe[6] = {0, 0, 0, 0, 0, Pb[5]};
-    Pb[5] = 0.0;
-    fold_beta(own, Pbe, Pb);
-  }
-  double s[5];
-  load_state(U, stride, idx, s);
-  prim_vjp(s, Pb, Tb, ph, Ub);
+  phase_end();
+  if (tn < NN) {
+    const VjpArgs& A = again(args);
+    double Pb[6] = {0, Pu[0], Pu[1], Pu[2], 0, 0};
 #pragma unroll
-  for (int v = 0; v < 5; ++v) store_once(&ubar[v * stride + idx], Ub[v]);
+    for (int q = 0; q < (EC ? 5 : 6); ++q)
+#pragma unroll
+      for (int d = 0; d < 3; ++d) Pb[q] += sF[(S::SUM + 6 * d + q) * EB + l];
+    double P[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) P[q] = EC && q > 3 ? 0.0 : 2.0 * sF[q * EB + l];
+    if (EC) {
+      const double beta = sF[4 * EB + l];
+      P[4] = 0.5 * P[0] / beta;
+      P[5] = P[4] / (A.ph.gm1 * P[0]) + 0.5 * (P[1] * P[1] + P[2] * P[2] + P[3] * P[3]);
+      const double Ae[6] = {P[0], 0, 0, 0, P[4], beta}, Pbe[6] = {0, 0, 0, 0, 0, Pb[4]};
+      Pb[4] = 0.0;
+      fold_beta(Ae, Pbe, Pb);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int x = d == 0 ? i : (d == 1 ? j : k);
+      if (x == 0 || x == N) {
+        const int ab = d == 0 ? j + NP * k : (d == 1 ? i + NP * k : i + NP * j);
+        const double* o = sF + S::END + (x == N ? 6 : 0) * LINES + d * NF + ab;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) Pb[q] += o[q * LINES];
+      }
+    }
+    const double s[5] = {P[0], P[0] * P[1], P[0] * P[2], P[0] * P[3], P[0] * P[5]};
+    double Ub[5] = {0, 0, 0, 0, 0};
+    prim_vjp(s, Pb, Tb, A.ph, Ub);
+    const long long stride = A.mesh.nE * NN;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) store_once(&(A.ubar + v * stride + static_cast<long long>(e) * NN)[n], Ub[v]);
+  }
+}
+
+template <int N, bool EC>
+__global__ __launch_bounds__(VjpShape<N>::BS) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp_a(VjpArgs) {
+  extern __shared__ double lds[];
+  const VjpArgsPtr args = (VjpArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid) / 64;
+  const int e = xcd_remap(blockIdx.x, gridDim.x);
+  constexpr int LW = VjpShape<N>::LW;
+  if (wave < LW)
+    vjp_phases<N, EC, 0>(args, lds, e, tid);
+  else if (2 * LW * 64 == VjpShape<N>::BS || wave < 2 * LW)
+    vjp_phases<N, EC, 1>(args, lds, e, tid);
+  else
+    vjp_phases<N, EC, 2>(args, lds, e, tid);
 }
 
 // --------------------------------------------------------------------------
@@ -781,12 +1017,12 @@ template <int N>
 hipError_t vjp_n(const DevMesh& m, const DevPhys& p, const DevBasis& b, const double* U,
                  const double* lam, double* gbar, double* ubar, double* out,
                  bool acc, double scale, double* cot, double cot_a, double cot_b, hipStream_t s) {
+  const VjpArgs a{U, lam, gbar, ubar, m, p, b};
+  const dim3 grid(static_cast<unsigned>(m.nE)), block(VjpShape<N>::BS);
   if (p.ec)
-    hipLaunchKernelGGL((k_vjp_a<N, true>), dim3(n_blocks<N>(m.nE)), dim3(Cfg<N>::BS), 0, s, U,
-                       lam, gbar, ubar, m, p, b);
+    hipLaunchKernelGGL((k_vjp_a<N, true>), grid, block, VjpShape<N>::BYTES, s, a);
   else
-    hipLaunchKernelGGL((k_vjp_a<N, false>), dim3(n_blocks<N>(m.nE)), dim3(Cfg<N>::BS), 0, s, U,
-                       lam, gbar, ubar, m, p, b);
+    hipLaunchKernelGGL((k_vjp_a<N, false>), grid, block, VjpShape<N>::BYTES, s, a);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (acc)
