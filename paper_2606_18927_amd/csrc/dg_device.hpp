@@ -251,6 +251,17 @@ __device__ inline double rcp_nr(double x) {
   return fma(r, e, r);
 }
 
+// sqrt(x) for x > 0 of moderate size: the hardware estimate of 1 / sqrt(x) and
+// one coupled and one residual Newton step.
+__device__ inline double sqrt_nr(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  return fma(fma(-g, g, x), h, g);
+}
+
 // Means of the entropy-conserving flux for one pair: rho_ln and 1 / beta_ln
 // (logarithmic means) and p^ = {{rho}} / (2 {{beta}}).  The logarithmic mean of
 // positive a, b is (a - b) / (ln a - ln b) = (a + b) / (2 F), F = atanh(f) / f,
@@ -279,7 +290,7 @@ __device__ inline void ec_means(double ra, double rb, double ba, double bb, doub
 __device__ inline double hh_abs(double lam, double lam_L, double lam_R) {
   double delta = fmax(lam - lam_L, lam_R - lam);
   delta = delta > 0.0 ? delta : 0.0;
-  return fabs(lam) < delta ? (lam * lam + delta * delta) / (2.0 * delta) : fabs(lam);
+  return fabs(lam) < delta ? (lam * lam + delta * delta) * (0.5 * rcp_nr(delta)) : fabs(lam);
 }
 
 // Viscous flux along d: g[3 q + b] = d q / d x_b for q in (u, v, w, T);

@@ -170,17 +170,6 @@ __device__ inline void line_derivative(const DevBasis& b, const R (&q)[N + 1], R
     }
 }
 
-// sqrt(x) for x > 0 of moderate size: the hardware estimate of 1 / sqrt(x) and
-// one coupled and one residual Newton step.
-__device__ inline double sqrt_nr(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-  const double e = fma(-h, g, 0.5);
-  g = fma(g, e, g);
-  h = fma(h, e, h);
-  return fma(fma(-g, g, x), h, g);
-}
-
 // The line of a line lane: direction d, position ab in the face
 // plane, and the LDS entries of its nodes.
 template <int N>
@@ -214,7 +203,8 @@ struct LineTask {
 struct Place {
   int ex, ey, ez, nb[6];
   double sx, sy, sz;
-  __device__ Place(const DevMesh& m, int e) {
+  // (scales: none on curved elements)
+  __device__ Place(const DevMesh& m, int e, bool scales = true) {
     elem_coords(e, m, ex, ey, ez);
     ex = __builtin_amdgcn_readfirstlane(ex);
     ey = __builtin_amdgcn_readfirstlane(ey);
@@ -228,9 +218,9 @@ struct Place {
     nb[5] = ez < m.n[2] - 1 ? e + sxy : (m.bc[2] == DG_BC_PERIODIC ? e - sxy * (m.n[2] - 1) : -1);
     // (scalar loads: the tables are constant while the kernel runs)
     typedef const __attribute__((address_space(4))) double* Table;
-    sx = ((Table)(uintptr_t)m.s[0])[ex];
-    sy = ((Table)(uintptr_t)m.s[1])[ey];
-    sz = ((Table)(uintptr_t)m.s[2])[ez];
+    sx = scales ? ((Table)(uintptr_t)m.s[0])[ex] : 0.0;
+    sy = scales ? ((Table)(uintptr_t)m.s[1])[ey] : 0.0;
+    sz = scales ? ((Table)(uintptr_t)m.s[2])[ez] : 0.0;
   }
   __device__ int neighbour(int d, int h) const {
     return h ? pick3(nb[1], nb[3], nb[5], d) : pick3(nb[0], nb[2], nb[4], d);
@@ -316,6 +306,14 @@ __host__ __device__ constexpr int line_waves() {
   return sizeof(R) == 8 ? (N == 7 ? 2 : (N == 5 ? (EC ? 2 : 3) : (EC ? 2 : 4))) : (N == 7 || EC ? 3 : 4);
 }
 
+// Faces of a line that its face lane takes.  The Roe flux is as long as a line's
+// pairs are together, so with it the line lanes take the upper ones themselves where
+// the face waves would be the last (N = 5 has as many face waves as line waves).
+template <int N, bool EC>
+__host__ __device__ constexpr int line_faces() {
+  return EC && N != 5 ? 1 : 2;
+}
+
 // A phase boundary: a workgroup barrier that no instruction is scheduled across
 // (the phases' values would else overlap and spill).
 __device__ __forceinline__ void phase_end() {
@@ -395,7 +393,7 @@ __device__ __forceinline__ void primitives_to_lds(const LineArgs& A, double* con
 // rho~ (0, 0, [[v]], [[w]], v~ [[v]] + w~ [[w]]).
 __device__ inline void roe_line(const double (&Lp)[5], double EL, const double (&Rp)[5], double ER, double gamma,
                                 double (&D)[5]) {
-  const double sl = sqrt(Lp[0]), sr = sqrt(Rp[0]);
+  const double sl = sqrt_nr(Lp[0]), sr = sqrt_nr(Rp[0]);
   const double isum = rcp_nr(sl + sr);
   const double wl = sl * isum, wr = sr * isum;
   const double iL = rcp_nr(Lp[0]), iR = rcp_nr(Rp[0]);
@@ -403,13 +401,13 @@ __device__ inline void roe_line(const double (&Lp)[5], double EL, const double (
   const double H = wl * (EL + Lp[4]) * iL + wr * (ER + Rp[4]) * iR;
   const double q2 = u * u + v * v + w * w;
   const double a2 = (gamma - 1.0) * (H - 0.5 * q2);
-  const double a = sqrt(a2), ia2 = rcp_nr(a2);
+  const double a = sqrt_nr(a2), ia2 = rcp_nr(a2);
   const double rho = sl * sr;
   const double dp = Rp[4] - Lp[4], du = Rp[1] - Lp[1], dv = Rp[2] - Lp[2], dw = Rp[3] - Lp[3];
   const double al1 = 0.5 * (dp - rho * a * du) * ia2;
   const double al5 = 0.5 * (dp + rho * a * du) * ia2;
   const double al2 = (Rp[0] - Lp[0]) - dp * ia2;
-  const double cl = sqrt(gamma * Lp[4] * iL), cr = sqrt(gamma * Rp[4] * iR);
+  const double cl = sqrt_nr(gamma * Lp[4] * iL), cr = sqrt_nr(gamma * Rp[4] * iR);
   const double l1 = hh_abs(u - a, Lp[1] - cl, Rp[1] - cr);
   const double l5 = hh_abs(u + a, Lp[1] + cl, Rp[1] + cr);
   const double l2 = fabs(u);
@@ -695,6 +693,8 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
   double sn[FL][2][5];     // face lanes, Kennedy-Gruber pair: the neighbours' states
   R eh[FL][NP];            // face lanes: the diffusive part of the lines' energy sums
   R acc[5][NP];            // line lanes: the other sums of the line's nodes
+  constexpr int HF = line_faces<N, EC>();
+  double su[5];            // line lanes with a face: the upper neighbour's state
   {
     const LineArgs& A = again(args);
     const long long stride = A.mesh.nE * NN;
@@ -706,6 +706,7 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       for (int v = 0; v < 5; ++v) s0[v] = *(Row)(uintptr_t)(A.U + v * stride + static_cast<long long>(e) * NN);
     }
     if constexpr (FACE && !EC) fetch_faces<N>(A.U, stride, Place(A.mesh, e), e, wtid - 64 * L::LW, sn);
+    if constexpr (!FACE && HF == 1) fetch_end<N>(A.U, stride, Place(A.mesh, e), e, LineTask<N>(wtid), 1, su);
     if (tid < NP) {
       double w = A.basis.inv_w[0];
 #pragma unroll
@@ -719,32 +720,40 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
     const Place pl(again(args).mesh, e);
     phase_end();
 
-    // ---- line phase: flux differencing; faces on the other wave(s) ---------
+    // ---- line phase: flux differencing; faces (on the other wave(s)) ---------
+    const auto face = [&](const LineTask<N>& t, int h, const double (&s)[5]) {
+      R gv[3], gT, fs[5];
+      face_values<N, R, EC>(again(args), sF, t, h, pl.neighbour(t.d, h) < 0, s, gv, gT, fs);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) sF[Fd::end_at(t.d, 8 * h + k, t.ab)] = gv[k];
+#pragma unroll
+      for (int k = 0; k < 5; ++k) sF[Fd::end_at(t.d, 8 * h + 3 + k, t.ab)] = fs[k];
+      sF[Fd::GT + h * L::LINES + t.d * NF + t.ab] = gT;
+    };
     if constexpr (FACE) {
       const LineArgs& A = again(args);
       const int lane = again(wtid) - 64 * L::LW;
-      const auto face = [&](const LineTask<N>& t, int h, const double (&s)[5]) {
-        R gv[3], gT, fs[5];
-        face_values<N, R, EC>(A, sF, t, h, pl.neighbour(t.d, h) < 0, s, gv, gT, fs);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) sF[Fd::end_at(t.d, 8 * h + k, t.ab)] = gv[k];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) sF[Fd::end_at(t.d, 8 * h + 3 + k, t.ab)] = fs[k];
-        sF[Fd::GT + h * L::LINES + t.d * NF + t.ab] = gT;
-      };
       if constexpr (EC) {
-        // one face after the other (the Roe flux is long), the next one's state in
+        // one line after the other (the Roe flux is long), the next one's states in
         // flight meanwhile
         const long long stride = A.mesh.nE * NN;
-        double cur[5], nxt[5];
-        fetch_end<N>(A.U, stride, pl, e, face_line<N>(lane, 0), 0, cur);
-#pragma unroll 1
-        for (int f = 0; f < 2 * FL; ++f) {
-          const int g = f + 1 < 2 * FL ? f + 1 : f;
-          fetch_end<N>(A.U, stride, pl, e, face_line<N>(lane, g >> 1), g & 1, nxt);
-          face(face_line<N>(lane, f >> 1), f & 1, cur);
+        double cur[HF][5], nxt[HF][5];
 #pragma unroll
-          for (int v = 0; v < 5; ++v) cur[v] = nxt[v];
+        for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, face_line<N>(lane, 0), h, cur[h]);
+#pragma unroll 1
+        for (int q = 0; q < FL; ++q) {
+          const LineTask<N> t = face_line<N>(lane, q), tn = face_line<N>(lane, q + 1 < FL ? q + 1 : q);
+#pragma unroll
+          for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, tn, h, nxt[h]);
+#pragma unroll
+          for (int h = 0; h < HF; ++h) {
+            face(t, h, cur[h]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int h = 0; h < HF; ++h)
+#pragma unroll
+            for (int v = 0; v < 5; ++v) cur[h][v] = nxt[h][v];
         }
       } else {
 #pragma unroll
@@ -753,6 +762,10 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
           for (int h = 0; h < 2; ++h) face(face_line<N>(lane, q), h, sn[q][h]);
       }
     } else {
+      if constexpr (HF == 1) {
+        face(LineTask<N>(again(wtid)), 1, su);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       const LineArgs& A = again(args);
       const LineTask<N> t(again(wtid));
       constexpr int NQ = EC && MIXED ? 7 : 6;
@@ -1184,6 +1197,11 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       // for together with all stores issued before it
       settle(g1);
       if (RK) settle(u1);
+      if constexpr (!FACE && HF == 1) {
+        const LineArgs& A = again(args);
+        const int en = e + step_e < end_e ? e + step_e : e;
+        fetch_end<N>(A.U, A.mesh.nE * NN, Place(A.mesh, en), en, LineTask<N>(again(wtid)), 1, su);
+      }
       phase_end();
       const double s0[5] = {1, 0, 0, 0, 1};
       primitives_to_lds<N, R, VISC, EC>(again(args), head, sF, again(tid), un, s0);
