@@ -17,8 +17,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdgsem.so")
-SOURCES = ["api.cpp", "lgl.cpp", "fwd_kernels.hip", "line_kg_f64.hip", "line_ec_f64.hip", "line_kg_f32.hip", "line_ec_f32.hip", "lift_kernels.hip", "aux_kernels.hip",
-           "adj_kernels.hip", "wall_kernels.hip", "curv_kernels.hip", "noalloc.hip"]
+SOURCES = ["api.cpp", "lgl.cpp", "fwd_kernels.hip", "line_kg_f64.hip", "line_ec_f64.hip", "line_kg_f32.hip",
+           "line_ec_f32.hip", "lift_kernels.hip", "aux_kernels.hip", "adj_kernels.hip", "wall_kernels.hip",
+           "curv_kernels.hip", "curv_kg_f64.hip", "curv_ec_f64.hip", "curv_kg_f32.hip", "curv_ec_f32.hip",
+           "noalloc.hip"]
 
 ARCH = os.environ.get("DGSEM_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

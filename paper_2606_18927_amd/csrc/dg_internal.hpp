@@ -89,6 +89,11 @@ hipError_t launch_line_kg_f64(int N, bool rk, const LineLaunch& l, hipStream_t s
 hipError_t launch_line_ec_f64(int N, bool rk, const LineLaunch& l, hipStream_t s);
 hipError_t launch_line_kg_f32(int N, bool rk, const LineLaunch& l, hipStream_t s);
 hipError_t launch_line_ec_f32(int N, bool rk, const LineLaunch& l, hipStream_t s);
+// the same on curvilinear elements (curv_line.hpp)
+hipError_t launch_curv_kg_f64(int N, bool rk, const LineLaunch& l, hipStream_t s);
+hipError_t launch_curv_ec_f64(int N, bool rk, const LineLaunch& l, hipStream_t s);
+hipError_t launch_curv_kg_f32(int N, bool rk, const LineLaunch& l, hipStream_t s);
+hipError_t launch_curv_ec_f32(int N, bool rk, const LineLaunch& l, hipStream_t s);
 // Stand-alone FP64 lifting, grad[3 q + d][e][node] (lift_kernels.hip).
 hipError_t launch_lift(int N, const DevMesh& m, const DevPhys& p, const DevBasis& b,
                        const double* U, double* grad, hipStream_t s);

@@ -108,3 +108,34 @@ def test_rhs_vjp(N, n, bc, opts, flux, spread):
     e = rel_l2(got, rhs_vjp(U, lam, mesh, g, **kw).numpy())
     say("vjp", e)
     assert np.all(e < 1e-11)
+
+
+@pytest.mark.parametrize("N,n,opts", [
+    (3, (1, 1, 1), {}),
+    (3, (3, 1, 2), {"suth": True}),
+    (5, (1, 3, 2), {}),
+    (7, (2, 1, 3), {"suth": True}),
+    (7, (1, 2, 1), {"viscous": False, "central": True}),
+])
+@pytest.mark.parametrize("flux,precision,spread", [
+    ("kg_llf", "fp64", 0.2), ("ec_roe", "fp64", 0.2), ("ec_roe", "fp64", 0.02), ("ec_roe", "fp64", 0.002),
+    ("kg_llf", "mixed", 0.2), ("ec_roe", "mixed", 0.2), ("ec_roe", "mixed", 0.02)])
+def test_curved_rhs(N, n, opts, flux, precision, spread):
+    """The right-hand side on warped elements, same criteria."""
+    from oracle import curvilinear as cv
+    from paper_2606_18927_amd import workloads
+    need_gpu()
+    say("curved case", N, n, opts, flux, precision, spread)
+    X = workloads.warped_nodes(dgsem.lgl(N)[0], n, amp=0.05)
+    mesh = cv.CurvMesh(N, torch.as_tensor(X))
+    suth = (1.0, 0.4) if opts.get("suth") else None
+    g = Gas(gamma=1.4, R=1.0, mu=0.02, Pr=0.72, sutherland=suth is not None, T_ref=1.0, S=0.4)
+    U = random_state(mesh, g.gamma, g.R, np.random.default_rng(60 + N), p_amp=spread, rho_amp=spread)
+    kw = {"viscous": opts.get("viscous", True), "central_only": opts.get("central", False), "flux": flux}
+    S = dgsem.Solver(dgsem.MeshSpec(N, None, (P, P, P), 1.0, nodes=X), g.gamma, g.R, g.mu, g.Pr, precision=precision,
+                     sutherland=suth, **kw)
+    got = S.eval_rhs(to_dev(U.numpy())).cpu().numpy()
+    S.sync()
+    e = rel_l2(got, cv.rhs(U, mesh, g, **kw).numpy())
+    say("curved rhs", e)
+    assert np.all(e < BOUND[precision])
