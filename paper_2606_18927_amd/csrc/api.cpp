@@ -256,32 +256,39 @@ dg_status forward_stages(dg_ctx* c, const double* in, double dt, Out stage_out) 
 }
 
 // Reverse sweep of one RK step over its five stage inputs stage_in(s):
-// cot_s = A_{s+1} cot_{s+1} + B_s lamU;  lamU += dt (dL/dU(U_s))^T cot_s.
+// cot_s = A_{s+1} cot_{s+1} + B_s lamU;  lamU += dt (dL/dU(U_s))^T cot_s.  lamU is lam_n
+// itself (a copy of 5 n_dof values less), unless lam_n lies in the stage states (from
+// `first` on, five of them), which are read until the end.
 template <typename In>
-dg_status reverse_stages(dg_ctx* c, In stage_in, double dt, const double* lam_np1, double* lam_n) {
+dg_status reverse_stages(dg_ctx* c, In stage_in, const double* first, double dt, const double* lam_np1, double* lam_n) {
   const dg::DevMesh m = dev_mesh(c);
   const dg::DevPhys p = dev_phys(c);
   const dg::DevBasis b = dev_basis(c);
   const size_t bytes = static_cast<size_t>(5 * c->n_dof) * sizeof(double);
   dg_status st = DG_OK;
-  if ((st = hip_check(c, hipMemcpyAsync(c->lamU, lam_np1, bytes, hipMemcpyDeviceToDevice, c->stream),
-                      "lam copy")) != DG_OK)
+  const long long n5 = 5 * c->n_dof;
+  const bool overlap = lam_n < first + 5 * n5 && first < lam_n + n5;
+  const bool partly = lam_n != lam_np1 && lam_n < lam_np1 + n5 && lam_np1 < lam_n + n5;
+  double* const lamU = overlap || partly ? c->lamU : lam_n;
+  if (lamU != lam_np1 &&
+      (st = hip_check(c, hipMemcpyAsync(lamU, lam_np1, bytes, hipMemcpyDeviceToDevice, c->stream), "lam copy")) != DG_OK)
     return st;
   // cot_4 = B_4 lamU (A_5 = 0; a = 0 does not read the old lamG); each later
   // cot_{s-1} = A_s cot_s + B_{s-1} lamU is formed by the VJP kernel of stage s
   // right after it updates lamU
-  if ((st = hip_check(c, dg::launch_axpby(c->lamG, c->lamU, 0.0, kRkB[4], 5 * c->n_dof, c->stream),
+  if ((st = hip_check(c, dg::launch_axpby(c->lamG, lamU, 0.0, kRkB[4], 5 * c->n_dof, c->stream),
                       "axpby kernel")) != DG_OK)
     return st;
   for (int s = 4; s >= 0; --s) {
     if ((st = hip_check(c, dg::launch_rhs_vjp(c->N, m, p, b, stage_in(s), c->lamG, c->gbar,
-                                              c->ubar, c->lamU, true, dt, c->stream,
+                                              c->ubar, lamU, true, dt, c->stream,
                                               s > 0 ? c->lamG : nullptr, kRkA[s],
                                               s > 0 ? kRkB[s - 1] : 0.0),
                         "vjp kernels")) != DG_OK)
       return st;
   }
-  return hip_check(c, hipMemcpyAsync(lam_n, c->lamU, bytes, hipMemcpyDeviceToDevice, c->stream),
+  if (lamU == lam_n) return DG_OK;
+  return hip_check(c, hipMemcpyAsync(lam_n, lamU, bytes, hipMemcpyDeviceToDevice, c->stream),
                    "lam copy");
 }
 
@@ -491,11 +498,8 @@ dg_status dg_set_state(dg_ctx* c, const double* U) {
   if (!U) return fail(c, DG_EINVAL, "null state");
   c->cur = 0;
   const size_t bytes = 5 * c->n_dof * sizeof(double);
-  if ((st = hip_check(c, hipMemcpyAsync(c->U[0], U, bytes, hipMemcpyDeviceToDevice, c->stream),
-                      "set_state copy")) != DG_OK)
-    return st;
-  // cleared by a kernel: a caller may capture this call into a graph
-  return hip_check(c, dg::launch_axpby(c->G, nullptr, 0.0, 0.0, 5 * c->n_dof, c->stream), "clear G");
+  // (the RK register needs no clearing: a step's first stage does not read it)
+  return hip_check(c, hipMemcpyAsync(c->U[0], U, bytes, hipMemcpyDeviceToDevice, c->stream), "set_state copy");
 }
 
 dg_status dg_get_state(const dg_ctx* cc, double* U) {
@@ -579,7 +583,7 @@ dg_status dg_rk_step_vjp(dg_ctx* c, const double* U_n, double /*t*/, double dt, 
   if ((st = forward_stages(c, stage_state(0), dt,
                            [&](int s) { return s < 4 ? stage_state(s + 1) : c->tmp; })) != DG_OK)
     return st;
-  return reverse_stages(c, [&](int s) -> const double* { return stage_state(s); }, dt, lam_np1, lam_n);
+  return reverse_stages(c, [&](int s) -> const double* { return stage_state(s); }, c->stages, dt, lam_np1, lam_n);
 }
 
 dg_status dg_rk_record_stages(dg_ctx* c, const double* U0, double /*t*/, double dt, int nsteps,
@@ -613,7 +617,7 @@ dg_status dg_rk_step_vjp_stages(dg_ctx* c, const double* stages, double /*t*/, d
   if (st != DG_OK) return st;
   if (!stages || !lam_np1 || !lam_n || !std::isfinite(dt)) return fail(c, DG_EINVAL, "bad arguments");
   const size_t n5 = static_cast<size_t>(5 * c->n_dof);
-  return reverse_stages(c, [&](int s) { return stages + static_cast<size_t>(s) * n5; }, dt, lam_np1, lam_n);
+  return reverse_stages(c, [&](int s) { return stages + static_cast<size_t>(s) * n5; }, stages, dt, lam_np1, lam_n);
 }
 
 dg_status dg_wall_faces(const dg_ctx* c, long long* n) {

@@ -139,3 +139,28 @@ def test_curved_rhs(N, n, opts, flux, precision, spread):
     e = rel_l2(got, cv.rhs(U, mesh, g, **kw).numpy())
     say("curved rhs", e)
     assert np.all(e < BOUND[precision])
+
+
+def test_reverse_step_in_place():
+    """The reverse step may write its cotangent over the one it reads or over the
+    stage states: the same result as into a buffer of its own."""
+    need_gpu()
+    N, n = 3, (2, 3, 2)
+    rng = np.random.default_rng(5)
+    faces = tuple(random_faces(n[d], 0.0, 1.0 + d, rng) for d in range(3))
+    mesh = Mesh(N, faces, bc=(P, P, P))
+    g = Gas(gamma=1.4, R=1.0, mu=0.01, Pr=0.72)
+    U = to_dev(random_state(mesh, g.gamma, g.R, rng).numpy()).reshape(-1)
+    S = dgsem.Solver(dgsem.MeshSpec(N, faces, (P, P, P)), g.gamma, g.R, g.mu, g.Pr, with_adjoint=True)
+    lam = to_dev(rng.standard_normal(U.numel()))
+    stages = S.rk_record_stages(U, 1e-3, 1)
+    want = S.rk_step_vjp_stages(stages[0], 1e-3, lam, out=torch.empty_like(lam)).clone()
+    same = lam.clone()
+    S.rk_step_vjp_stages(stages[0], 1e-3, same, out=same)
+    for s in (0, 2, 4):
+        st = stages.clone()
+        S.rk_step_vjp_stages(st[0], 1e-3, lam, out=st[0][s])
+        S.sync()
+        assert torch.equal(st[0][s], want)
+    S.sync()
+    assert torch.equal(same, want)
