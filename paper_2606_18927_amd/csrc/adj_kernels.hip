@@ -349,9 +349,9 @@ __device__ inline const VjpArgs& again(VjpArgsPtr p) {
   return *(const VjpArgs*)p;
 }
 
-// One workgroup per element: LW waves of line lanes (lam's derivatives along the line,
-// the pairs) and as many of face lanes (the faces at the line's ends, the gradients of
-// u, v, w, T); a node phase takes one node per lane.  LDS fields (of EB values): halves of rho, u, v, w, p, e
+// One workgroup per element: LW waves of line lanes (the pairs of a line) and as many
+// of face lanes (the faces at the line's ends and all its derivatives); a node
+// phase takes one node per lane.  LDS fields (of EB values): halves of rho, u, v, w, p, e
 // (entropy-conserving pair: beta in place of p), T, lam (5); raw gradients GR + 3 q + d;
 // viscous flux cotangents FV + 3 c + d.  At the end the lines' sums (6 per direction) take
 // the place of the latter two, the faces' primitive cotangents END that of T and lam.
@@ -627,11 +627,11 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
       sW[tid] = w;
     }
     double sn[2][5], ln[2][5], s_n[2];  // the neighbours' at the line's ends
-    if constexpr (ROLE < 2) {
-      const LineTask<N> t(ROLE == 0 ? tid : tid - 64 * S::LW);
+    if constexpr (ROLE == 1) {
+      const LineTask<N> t(tid - 64 * S::LW);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        if (ROLE == 1) fetch_end<N>(A.U, stride, pl, e, t, h, sn[h]);
+        fetch_end<N>(A.U, stride, pl, e, t, h, sn[h]);
         fetch_end<N>(A.lam, stride, pl, e, t, h, ln[h]);
         s_n[h] = nb_scale(A.mesh, pl.ex, pl.ey, pl.ez, t.d, h != 0);
       }
@@ -660,7 +660,7 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
       const LineTask<N> t(again(tid) - 64 * S::LW);
       const double iw = B.basis.inv_w[0];
       const double s = t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz);
-      double gq[2][4];  // ghosts: u, v, w (halves), T
+      double gl[2][4], gq[2][4];  // ghosts: lam (momentum, energy) s / w; u, v, w (halves), T
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int p = t.node(h ? N : 0);
@@ -681,48 +681,32 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
         const double ir = rcp_nr(sn[h][0]);
         const double v0 = sn[h][1] * ir, v1 = sn[h][2] * ir, v2 = sn[h][3] * ir;
         const double Tn = B.ph.gm1 * (sn[h][4] - 0.5 * (sn[h][1] * v0 + sn[h][2] * v1 + sn[h][3] * v2)) * B.ph.inv_R * ir;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) gl[h][c] = wall ? siw * lo[1 + c] : -niw * ln[h][1 + c];
         gq[h][0] = wall ? -0.5 * P[1] : 0.5 * v0;
         gq[h][1] = wall ? -0.5 * P[2] : 0.5 * v1;
         gq[h][2] = wall ? -0.5 * P[3] : 0.5 * v2;
         gq[h][3] = wall ? 2.0 * B.mesh.T_wall - T : Tn;
       }
       settle(pe);
+      settle(gl);
       settle(gq);
       if (visc) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int k = v == 0 ? t.d : (v == 1 ? t.d1 : (v == 2 ? t.d2 : 3));
-          double q[NP], g[NP];
-#pragma unroll
-          for (int m = 0; m < NP; ++m) q[m] = sF[(v == 3 ? S::T : 1 + k) * EB + t.node(m)];
-          line_derivative<N, double, false>(B.basis, q, gq[0][v], gq[1][v], g);
-#pragma unroll
-          for (int m = 0; m < NP; ++m) sF[(S::GR + 3 * k + t.d) * EB + t.node(m)] = g[m];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    if constexpr (ROLE == 0) {
-      if (visc) {
         // lam of momentum and energy -> the flux cotangents -w s dlam/dx (a wall's flux
-        // takes the own stresses and heat flux: ghost -lam)
-        const VjpArgs& B = again(args);
-        const LineTask<N> t(again(tid));
-        const double iw = B.basis.inv_w[0], s = t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz);
-        const bool wall[2] = {pl.neighbour(t.d, 0) < 0, pl.neighbour(t.d, 1) < 0};
-        const double gs[2] = {iw * (wall[0] ? -s : s_n[0]), iw * (wall[1] ? -s : s_n[1])};
+        // takes the own stresses and heat flux: ghost -lam); u, v, w, T -> gradients
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int k = v == 0 ? t.d : (v == 1 ? t.d1 : (v == 2 ? t.d2 : 3));
+        for (int c = 0; c < 8; ++c) {
+          const int v = c & 3, k = v == 0 ? t.d : (v == 1 ? t.d1 : (v == 2 ? t.d2 : 3));
+          const int src = c < 4 ? S::LAM + 1 + k : (v == 3 ? S::T : 1 + k);
           double q[NP], g[NP];
 #pragma unroll
-          for (int m = 0; m < NP; ++m) q[m] = sF[(S::LAM + 1 + k) * EB + t.node(m)];
-          const double g0 = gs[0] * (wall[0] ? q[0] : ln[0][1 + v]), g1 = gs[1] * (wall[1] ? q[N] : ln[1][1 + v]);
+          for (int m = 0; m < NP; ++m) q[m] = sF[src * EB + t.node(m)];
+          if (c < 4)
 #pragma unroll
-          for (int m = 0; m < NP; ++m) q[m] *= -s * B.basis.inv_w[m];
-          line_derivative<N, double, false>(B.basis, q, -g0, -g1, g);
+            for (int m = 0; m < NP; ++m) q[m] *= -s * B.basis.inv_w[m];
+          line_derivative<N, double, false>(B.basis, q, c < 4 ? gl[0][v] : gq[0][v], c < 4 ? gl[1][v] : gq[1][v], g);
 #pragma unroll
-          for (int m = 0; m < NP; ++m) sF[(S::FV + 3 * k + t.d) * EB + t.node(m)] = g[m];
+          for (int m = 0; m < NP; ++m) sF[((c < 4 ? S::FV : S::GR) + 3 * k + t.d) * EB + t.node(m)] = g[m];
           __builtin_amdgcn_sched_barrier(0);
         }
       }
