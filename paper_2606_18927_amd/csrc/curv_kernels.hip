@@ -10,8 +10,8 @@
 // J = det(dX/dxi).  k_metrics computes them once per mesh into
 //   geo[c][e][node], c = 3 i + n: J a^i_n; c = 9: 1 / J; then the same ten
 //   fields in FP32 (read by the mixed-precision sweeps).
-// Operator per stage (one workgroup per element, one lane per node; face
-// lanes = one lane per face node):
+// Operator per stage (line_device.hpp has the split of the work and the weak form of
+// the surface terms; k_rhs_curv is in curv_line.hpp):
 //   k_face_flux_curv  BR1 gradients at the face nodes (chain rule with the
 //                     node's metrics: J grad q = sum_i J a^i (D_i q + lifting
 //                     term)) and the contravariant normal viscous flux
@@ -24,6 +24,7 @@
 //                     the face, shared by both sides), Ut = -(1/J)(...),
 //                     fused RK update.
 #include "curv_flux.hpp"
+#include "line_device.hpp"
 
 namespace dg {
 namespace {
@@ -133,118 +134,216 @@ __global__ __launch_bounds__(CurvCfg<N>::BS) void k_metrics(const double* __rest
   }
 }
 
-// Physical gradients of q = (u, v, w, T) at node (i, j, k): reference
-// derivatives plus the lifting terms of the faces the node lies on, then
-// grad q = (1/J) sum_r J a^r gxi_r.  sq[c] are LDS fields of q; corr[f][c][ab]
-// the lifting terms (q* - q)(+-1/w) of face f.
-template <int N, typename R>
-__device__ inline void curv_gradients(const R* const sq[4], const double (*sD)[N + 2],
-                                      const R (*corr)[4][(N + 1) * (N + 1)], int i, int j, int k,
-                                      const R Ja[9], R invJ, R g[12]) {
-  constexpr int NP = N + 1;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    R gx[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) gx[r] = dline<N, R>(sq[c], sD, r, i, j, k);
-    if (i == 0) gx[0] += corr[0][c][j + NP * k];
-    if (i == N) gx[0] += corr[1][c][j + NP * k];
-    if (j == 0) gx[1] += corr[2][c][i + NP * k];
-    if (j == N) gx[1] += corr[3][c][i + NP * k];
-    if (k == 0) gx[2] += corr[4][c][i + NP * j];
-    if (k == N) gx[2] += corr[5][c][i + NP * j];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) g[3 * c + d] = invJ * (Ja[d] * gx[0] + Ja[3 + d] * gx[1] + Ja[6 + d] * gx[2]);
-  }
-}
-
 // ---------------------------------------------------------- face viscous flux
-// (R = float in mixed precision: the fluxes are formed in FP64 and stored in FP32)
+// One workgroup per element, of the line-lane shape.  All twelve reference derivatives
+// enter a face node's gradient:
+//   nodes  all lanes: (u, v, w, T) into LDS; line lanes also the neighbours' states at the
+//          two ends of their line, the ghost values of the weak form, and the metric
+//          terms of their two face nodes (boundary-node copy);
+//   lines  a line lane: the normal derivatives at its line's two ends, and one line of a
+//          face plane for one of u, v, w, T; the other wave(s): the remaining such lines;
+//   faces  a line lane, now lane of two face nodes: physical gradients, the two
+//          contravariant fluxes; its wave stores whole rows.
+// What bounds it: @@
+// Mixed precision stores FP32 and computes in FP64 with the FP32 entries of Q, as the
+// axis-aligned kernel does and for its reason.
+template <int N>
+struct CurvFaceShape {
+  using L = Line<N>;
+  static constexpr int TASKS = 48 * L::NP;                            // tangential lines times four fields
+  static constexpr int MINE = 64 * L::LW;                             // of them on the line lanes
+  static constexpr int ROUNDS = (TASKS - MINE + 64 * L::FW - 1) / (64 * L::FW);
+  // tangential derivatives, eight per face node; before them, ghost values, four per face node
+  static constexpr int OUT = 4 * L::EB, COUNT = OUT + 48 * L::NF;
+  static constexpr int WAVES = 4;                                    // per SIMD
+};
+
 template <int N, typename R>
-__global__ __launch_bounds__(CurvCfg<N>::BS) void k_face_flux_curv(const double* __restrict__ U,
-                                                                  R* __restrict__ ffv, DevMesh mesh,
-                                                                  DevPhys ph, DevBasis basis) {
-  using C = CurvCfg<N>;
-  constexpr int NP = C::NP, NF = C::NF, NN = C::NN;
-  __shared__ double sD[NP][N + 2];
-  __shared__ double sq[4][NN];
-  __shared__ double corr[6][4][NF];
+__global__ __launch_bounds__(Line<N>::BS) __attribute__((amdgpu_waves_per_eu(CurvFaceShape<N>::WAVES))) void k_face_flux_curv(
+    LineArgs) {
+  using L = Line<N>;
+  using Fs = CurvFaceShape<N>;
+  constexpr int NP = L::NP, NF = L::NF, EB = L::EB;
+  __shared__ double sF[Fs::COUNT];
+  const LineArgsPtr args = (LineArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const int tid = threadIdx.x;
-  const long long nE = mesh.nE;
-  const long long stride = nE * NN;
-  const long long e = xcd_remap(blockIdx.x, gridDim.x);
-  int ex, ey, ez;
-  elem_coords(e, mesh, ex, ey, ez);
-  if (tid < NP * NP) sD[tid / NP][tid % NP] = basis.D[tid];
-  constexpr int NFN = n_face_nodes<N>();
-  static_assert(NFN <= CurvCfg<N>::BS, "one lane per boundary node");
-  double Ja[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, invJ = 0.0;
-  if (tid < NFN) {
-    const long long fs = nE * NFN, of = e * NFN + tid;
-#pragma unroll
-    for (int c = 0; c < 9; ++c) Ja[c] = mesh.geoF[c * fs + of];
-    invJ = mesh.geoF[9 * fs + of];
-  }
-  if (tid < NN) {
-    double s[5];
-    load_state(U, stride, e * NN + tid, s);
-    const Prim P = primitives(s, ph);
-    sq[0][tid] = P.u;
-    sq[1][tid] = P.v;
-    sq[2][tid] = P.w;
-    sq[3][tid] = P.T;
-  }
-  // face lanes fetch the neighbour's face node now and take their own values
-  // from LDS after the barrier
-  double sn[5] = {1.0, 0.0, 0.0, 0.0, 1.0};
-  long long nb = -1;  // -1: the face is a wall
-  if (tid < 6 * NF) {
-    const FaceTask<N> ft(tid);
-    nb = neighbour(mesh, ex, ey, ez, ft.d, ft.up);
-    if (nb >= 0) load_state(U, stride, nb * NN + ft.nb_node(), sn);
-  }
-  __syncthreads();
-  if (tid < 6 * NF) {
-    const FaceTask<N> ft(tid);
-    const int lo = ft.own_node();
-    const double qo[4] = {sq[0][lo], sq[1][lo], sq[2][lo], sq[3][lo]};
-    double qs[4] = {0.0, 0.0, 0.0, mesh.T_wall};  // isothermal no-slip wall
-    if (nb >= 0) {
-      const Prim Pn = primitives(sn, ph);
-      qs[0] = 0.5 * (qo[0] + Pn.u);
-      qs[1] = 0.5 * (qo[1] + Pn.v);
-      qs[2] = 0.5 * (qo[2] + Pn.w);
-      qs[3] = 0.5 * (qo[3] + Pn.T);
+  const int e = xcd_remap(blockIdx.x, gridDim.x);
+  // task q: the line at position pos of face 2 d + h along its first or second
+  // direction t, field c
+  struct Task {
+    int first, step, field, ghost, out, dout;
+    __device__ Task(int q) {
+      q = q < Fs::TASKS ? q : Fs::TASKS - 1;
+      const int d = q / (16 * NP), r = q - d * (16 * NP);
+      const int pos = r % NP, c = (r / NP) & 3, second = (r / (4 * NP)) & 1, h = r / (8 * NP);
+      const int t = second ? (d == 2 ? 1 : 2) : (d == 0 ? 1 : 0), o = 3 - d - t;
+      const int n = h ? N : 0;
+      const LineTask<N> line(t, d < o ? n + NP * pos : pos + NP * n);
+      first = line.first;
+      step = line.step;
+      field = c;
+      ghost = Fs::OUT + (2 * t * 4 + c) * NF + line.ab;
+      out = Fs::OUT + ((2 * d + h) * 8 + 4 * second + c) * NF + (second ? pos : NP * pos);
+      dout = second ? NP : 1;
     }
-    const double sc = ft.up ? basis.inv_w_end : -basis.inv_w_end;
+  };
+  const auto along = [&](const DevBasis& b, const Task& k, double gl, double gr) {
+    double q[NP], g[NP];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) corr[ft.f][c][ft.ab] = (qs[c] - qo[c]) * sc;
+    for (int m = 0; m < NP; ++m) q[m] = sF[k.field * EB + (L::SWZ ? k.first ^ (m * k.step) : k.first + m * k.step)];
+    if (sizeof(R) == 4) {  // (no row sum times T, as in the other kernel; the same for u, v, w)
+      const double r = k.field == 3 ? q[0] : 0.0;
+#pragma unroll
+      for (int m = 0; m < NP; ++m) q[m] -= r;
+      gl -= r;
+      gr -= r;
+    }
+    line_derivative<N, double, false>(b, q, gl, gr, g);
+#pragma unroll
+    for (int m = 0; m < NP; ++m) sF[k.out + m * k.dout] = b.inv_w[m] * g[m];
+  };
+
+  double u[L::ROUNDS][5];
+  {
+    const LineArgs& A = again(args);
+    fetch_nodes<N>(A.U, A.mesh.nE * L::NN, e, tid, u);
   }
-  __syncthreads();
-  // one lane per boundary node (face node number t = tid), with that node's
-  // metric terms from the boundary-node copy (fetched before the barriers)
-  if (tid >= NFN) return;
-  int i, j, k;
-  face_node_of<N>(tid, i, j, k);
-  const int n = i + NP * (j + NP * k);
-  const double* const q[4] = {sq[0], sq[1], sq[2], sq[3]};
-  double g[12];
-  curv_gradients<N, double>(q, sD, corr, i, j, k, Ja, invJ, g);
-  const double r = viscosity_ratio(ph, sq[3][n]);
-  double tau[6], qT[3];
-  stress64<double>(g, ph.mu * r, ph.kappa * r, tau, qT);
-  const double u = sq[0][n], v = sq[1][n], w = sq[2][n];
-  R* out = ffv + e * (6 * 4 * NF);
-  double f[4];
+  const auto fields = [&](const LineArgs& A) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const int idx = d == 0 ? i : (d == 1 ? j : k);
-    if (idx != 0 && idx != N) continue;
-    const int ab = d == 0 ? j + NP * k : (d == 1 ? i + NP * k : i + NP * j);
-    const int fi = 2 * d + (idx == N ? 1 : 0);
-    contra_viscous<double>(u, v, w, tau, qT, Ja[3 * d], Ja[3 * d + 1], Ja[3 * d + 2], f);
+    for (int r = 0; r < L::ROUNDS; ++r) {
+      const unsigned n = tid + r * L::BS;
+      if (n < L::NN) {
+        const double* s = u[r];
+        const double ir = rcp_nr(s[0]);
+        const double vx = s[1] * ir, vy = s[2] * ir, vz = s[3] * ir;
+        const int l = L::at(n % NP, (n / NP) % NP, n / NF);
+        sF[l] = vx;
+        sF[EB + l] = vy;
+        sF[2 * EB + l] = vz;
+        sF[3 * EB + l] = A.ph.gm1 * (s[4] - 0.5 * (s[1] * vx + s[2] * vy + s[3] * vz)) * A.ph.inv_R * ir;
+      }
+    }
+  };
+
+  if (__builtin_amdgcn_readfirstlane(tid) < 64 * L::LW) {
+    const LineArgs& A = again(args);
+    const Place pl(A.mesh, e, false);
+    const LineTask<N> t(tid);
+    const long long stride = A.mesh.nE * L::NN;
+    const int ta = t.d == 0 ? 1 : 0, tb = t.d == 2 ? 1 : 2;  // the face's first and second direction
+    double sn[2][5], J[2][3][3], invJ[2];  // metric rows of d, ta, tb
+    bool wall[2];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) out[(fi * 4 + c) * NF + ab] = static_cast<R>(f[c]);
+    for (int h = 0; h < 2; ++h) {
+      const int nb = pl.neighbour(t.d, h);
+      wall[h] = nb < 0;  // (there the own state)
+      const unsigned o = t.end_node((h != 0) == (nb >= 0) ? 0 : N);
+      const double* p = A.U + static_cast<long long>(nb >= 0 ? nb : e) * L::NN;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sn[h][v] = (p + v * stride)[o];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      constexpr int NB = n_face_nodes<N>();
+      const unsigned o = t.end_node(h ? N : 0), fs = static_cast<unsigned>(face_node_index<N>(o % NP, (o / NP) % NP, o / NF));
+      const double* g = A.mesh.geoF + static_cast<long long>(e) * NB;
+      const long long rows = A.mesh.nE * NB;
+#pragma unroll
+      for (int x = 0; x < 3; ++x) {
+        J[h][0][x] = (g + (3 * t.d + x) * rows)[fs];
+        J[h][1][x] = (g + (3 * ta + x) * rows)[fs];
+        J[h][2][x] = (g + (3 * tb + x) * rows)[fs];
+      }
+      invJ[h] = (g + 9 * rows)[fs];
+    }
+    fields(A);
+    double gh[2][4];  // ghosts: u, v, w, T
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double* s = sn[h];
+      const double ir = rcp_nr(s[0]);
+      const double v0 = s[1] * ir, v1 = s[2] * ir, v2 = s[3] * ir;
+      const double T = A.ph.gm1 * (s[4] - 0.5 * (s[1] * v0 + s[2] * v1 + s[3] * v2)) * A.ph.inv_R * ir;
+      const double side = wall[h] ? -1.0 : 1.0;  // isothermal no-slip wall
+      gh[h][0] = side * v0;
+      gh[h][1] = side * v1;
+      gh[h][2] = side * v2;
+      gh[h][3] = wall[h] ? 2.0 * A.mesh.T_wall - T : T;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sF[Fs::OUT + ((2 * t.d + h) * 4 + c) * NF + t.ab] = gh[h][c];
+    }
+    phase_end();
+    double gl, gr;
+    {
+      const Task k(again(tid));
+      gl = sF[k.ghost];
+      gr = sF[k.ghost + 4 * NF];
+    }
+    phase_end();
+
+    double own[2][4], g[2][4];  // values and normal derivatives at the line's ends
+    const DevBasis& b = again(args).basis;
+    along(b, Task(again(tid)), gl, gr);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      double q[NP];
+#pragma unroll
+      for (int m = 0; m < NP; ++m) q[m] = sF[c * EB + t.node(m)];
+      own[0][c] = q[0];
+      own[1][c] = q[N];
+      if (sizeof(R) == 4 && c == 3) {
+#pragma unroll
+        for (int m = 0; m < NP; ++m) q[m] -= own[0][3];
+        gh[0][3] -= own[0][3];
+        gh[1][3] -= own[0][3];
+      }
+      g[0][c] = -0.5 * gh[0][c];
+      g[1][c] = 0.5 * gh[1][c];
+#pragma unroll
+      for (int m = 1; m < NP; ++m) g[0][c] += q_im<N, double>(b, 0, m) * q[m];
+#pragma unroll
+      for (int m = 0; m < N; ++m) g[1][c] -= q_im<N, double>(b, m, N) * q[m];
+      if (c & 1) settle(g);
+    }
+    phase_end();
+
+    const LineArgs& B = again(args);
+    const double iw = B.basis.inv_w[0];
+    R* out = static_cast<R*>(const_cast<void*>(B.ffv)) + static_cast<long long>(e) * (6 * 4 * NF);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double* o = &sF[Fs::OUT + (2 * t.d + h) * 8 * NF + t.ab];
+      double gp[12];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const double gn = invJ[h] * iw * g[h][c], ga = invJ[h] * o[c * NF], gb = invJ[h] * o[(4 + c) * NF];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) gp[3 * c + x] = J[h][0][x] * gn + J[h][1][x] * ga + J[h][2][x] * gb;
+      }
+      const double r = viscosity_ratio(B.ph, own[h][3]);
+      double tau[6], qT[3], f[4];
+      stress64<double>(gp, B.ph.mu * r, B.ph.kappa * r, tau, qT);
+      contra_viscous<double>(own[h][0], own[h][1], own[h][2], tau, qT, J[h][0][0], J[h][0][1], J[h][0][2], f);
+      R* dst = out + (2 * t.d + h) * (4 * NF);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) (dst + c * NF)[static_cast<unsigned>(t.ab)] = static_cast<R>(f[c]);
+    }
+  } else {
+    fields(again(args));
+    phase_end();
+    const int lane = tid - 64 * L::LW;
+    double gl[Fs::ROUNDS], gr[Fs::ROUNDS];
+#pragma unroll
+    for (int r = 0; r < Fs::ROUNDS; ++r) {
+      const Task k(Fs::MINE + lane + 64 * L::FW * r);
+      gl[r] = sF[k.ghost];
+      gr[r] = sF[k.ghost + 4 * NF];
+    }
+    phase_end();
+    const DevBasis& b = again(args).basis;
+#pragma unroll
+    for (int r = 0; r < Fs::ROUNDS; ++r) along(b, Task(Fs::MINE + again(lane) + 64 * L::FW * r), gl[r], gr[r]);
+    phase_end();
   }
 }
 
@@ -259,8 +358,10 @@ hipError_t metrics_n(const double* X, double* geo, double* geoF, bool with_f32, 
 template <int N, typename R>
 hipError_t face_flux_curv_n(const DevMesh& m, const DevPhys& p, const DevBasis& b, const double* U,
                             void* ffv, hipStream_t s) {
-  hipLaunchKernelGGL((k_face_flux_curv<N, R>), dim3(static_cast<unsigned>(m.nE)), dim3(CurvCfg<N>::BS), 0, s,
-                     U, static_cast<R*>(ffv), m, p, b);
+  LineArgs a{U, ffv, nullptr, nullptr, nullptr, m, p, b, Stage{}};
+  if (sizeof(R) == 4)
+    for (int i = 0; i < 16; ++i) a.basis.Q[i] = b.Qf[i];
+  hipLaunchKernelGGL((k_face_flux_curv<N, R>), dim3(static_cast<unsigned>(m.nE)), dim3(Line<N>::BS), 0, s, a);
   return hipGetLastError();
 }
 
