@@ -394,11 +394,10 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
   {
     const LineArgs& A = again(args);
     const long long stride = A.mesh.nE * NN;
-    double u[ROUNDS][5], sn[EC ? 1 : FL][2][8];
+    double u[ROUNDS][5], sn[EC ? 1 : FL][2][8];  // (entropy-conserving pair: the first line's)
     R M[NP][3];
     fetch_nodes<N>(A.U, stride, e, tid, u);
     if constexpr (FACE) {
-      if (!EC)
 #pragma unroll
         for (int q = 0; q < (EC ? 1 : FL); ++q)
 #pragma unroll
@@ -491,12 +490,15 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
         const long long st = B.mesh.nE * NN;
         double cur[HF][8], nxt[HF][8], fs[HF][5];
 #pragma unroll
-        for (int h = 0; h < HF; ++h) fetch_face<N, R>(B, st, pl, e, face_line<N>(lane, 0), h, cur[h]);
+        for (int h = 0; h < HF; ++h)
+#pragma unroll
+          for (int v = 0; v < 8; ++v) cur[h][v] = sn[0][h][v];
 #pragma unroll 1
         for (int q = 0; q < FL; ++q) {
           const LineTask<N> t = face_line<N>(lane, q), tn = face_line<N>(lane, q + 1 < FL ? q + 1 : q);
+          if (FL > 1)
 #pragma unroll
-          for (int h = 0; h < HF; ++h) fetch_face<N, R>(B, st, pl, e, tn, h, nxt[h]);
+            for (int h = 0; h < HF; ++h) fetch_face<N, R>(B, st, pl, e, tn, h, nxt[h]);
 #pragma unroll
           for (int h = 0; h < HF; ++h) {
             face(t, h, cur[h], fs[h]);
@@ -509,10 +511,11 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
               for (int h = 0; h < HF; ++h)
 #pragma unroll
                 for (int v = 0; v < 5; ++v) fe[r][h][v] = r == q ? fs[h][v] : fe[r][h][v];
+          if (FL > 1)
 #pragma unroll
-          for (int h = 0; h < HF; ++h)
+            for (int h = 0; h < HF; ++h)
 #pragma unroll
-            for (int v = 0; v < 8; ++v) cur[h][v] = nxt[h][v];
+              for (int v = 0; v < 8; ++v) cur[h][v] = nxt[h][v];
         }
       } else {
 #pragma unroll

@@ -694,7 +694,15 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
   R eh[FL][NP];            // face lanes: the diffusive part of the lines' energy sums
   R acc[5][NP];            // line lanes: the other sums of the line's nodes
   constexpr int HF = line_faces<N, EC>();
-  double su[5];            // line lanes with a face: the upper neighbour's state
+  double su[EC ? 2 : 1][5];  // entropy-conserving pair: neighbours' states, a line lane's upper, a face lane's first line's
+  const auto fetch_su = [&](const LineArgs& A, int e) {
+    if constexpr (FACE && EC)
+#pragma unroll
+      for (int h = 0; h < HF; ++h)
+        fetch_end<N>(A.U, A.mesh.nE * NN, Place(A.mesh, e), e, face_line<N>(again(wtid) - 64 * L::LW, 0), h, su[h]);
+    if constexpr (!FACE && HF == 1)
+      fetch_end<N>(A.U, A.mesh.nE * NN, Place(A.mesh, e), e, LineTask<N>(again(wtid)), 1, su[0]);
+  };
   {
     const LineArgs& A = again(args);
     const long long stride = A.mesh.nE * NN;
@@ -706,7 +714,7 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       for (int v = 0; v < 5; ++v) s0[v] = *(Row)(uintptr_t)(A.U + v * stride + static_cast<long long>(e) * NN);
     }
     if constexpr (FACE && !EC) fetch_faces<N>(A.U, stride, Place(A.mesh, e), e, wtid - 64 * L::LW, sn);
-    if constexpr (!FACE && HF == 1) fetch_end<N>(A.U, stride, Place(A.mesh, e), e, LineTask<N>(wtid), 1, su);
+    fetch_su(A, e);
     if (tid < NP) {
       double w = A.basis.inv_w[0];
 #pragma unroll
@@ -739,21 +747,25 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
         const long long stride = A.mesh.nE * NN;
         double cur[HF][5], nxt[HF][5];
 #pragma unroll
-        for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, face_line<N>(lane, 0), h, cur[h]);
+        for (int h = 0; h < HF; ++h)
+#pragma unroll
+          for (int v = 0; v < 5; ++v) cur[h][v] = su[h][v];
 #pragma unroll 1
         for (int q = 0; q < FL; ++q) {
           const LineTask<N> t = face_line<N>(lane, q), tn = face_line<N>(lane, q + 1 < FL ? q + 1 : q);
+          if (FL > 1)
 #pragma unroll
-          for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, tn, h, nxt[h]);
+            for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, tn, h, nxt[h]);
 #pragma unroll
           for (int h = 0; h < HF; ++h) {
             face(t, h, cur[h]);
             __builtin_amdgcn_sched_barrier(0);
           }
+          if (FL > 1)
 #pragma unroll
-          for (int h = 0; h < HF; ++h)
+            for (int h = 0; h < HF; ++h)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) cur[h][v] = nxt[h][v];
+              for (int v = 0; v < 5; ++v) cur[h][v] = nxt[h][v];
         }
       } else {
 #pragma unroll
@@ -763,7 +775,7 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       }
     } else {
       if constexpr (HF == 1) {
-        face(LineTask<N>(again(wtid)), 1, su);
+        face(LineTask<N>(again(wtid)), 1, su[0]);
         __builtin_amdgcn_sched_barrier(0);
       }
       const LineArgs& A = again(args);
@@ -1197,11 +1209,7 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       // for together with all stores issued before it
       settle(g1);
       if (RK) settle(u1);
-      if constexpr (!FACE && HF == 1) {
-        const LineArgs& A = again(args);
-        const int en = e + step_e < end_e ? e + step_e : e;
-        fetch_end<N>(A.U, A.mesh.nE * NN, Place(A.mesh, en), en, LineTask<N>(again(wtid)), 1, su);
-      }
+      if constexpr (EC) fetch_su(again(args), e + step_e < end_e ? e + step_e : e);
       phase_end();
       const double s0[5] = {1, 0, 0, 0, 1};
       primitives_to_lds<N, R, VISC, EC>(again(args), head, sF, again(tid), un, s0);
