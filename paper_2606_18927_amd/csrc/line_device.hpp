@@ -292,14 +292,6 @@ __device__ __forceinline__ void settle(R (&x)[A][B]) {
     for (int b = 0; b < B; ++b) asm volatile("" : "+v"(x[a][b]));
 }
 
-// Workgroups that loop over elements, as many as run at once: at N = 7 in FP64 a
-// CU holds two, and fetching the next element early hides what two cannot hide from
-// each other.  Elsewhere more workgroups fit, and one element each is as fast.
-template <int N, typename R>
-__host__ __device__ constexpr bool line_persists() {
-  return N == 7 && sizeof(R) == 8;
-}
-
 // Waves per SIMD the registers are bounded for: what LDS lets a CU hold.
 template <int N, typename R, bool EC>
 __host__ __device__ constexpr int line_waves() {
@@ -680,13 +672,13 @@ __device__ inline void ec_rows(const LineArgs& A, const R* sF, const double* hea
 // run the same node phases and meet at the same barriers.  tid: the lane's number
 // in the node phases; wtid: its line (>= 64 LW: face lane).
 template <int N, typename R, bool RK, bool VISC, bool EC, bool FACE>
-__device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* const head, int e, const int step_e,
-                                               const int end_e, const int tid, const int wtid) {
+__device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* const head, const int e, const int tid,
+                                               const int wtid) {
   using L = Line<N>;
   using Fd = Fields<N, R, EC>;
   constexpr int NP = L::NP, NF = L::NF, NN = L::NN, EB = L::EB, BS = L::BS, ROUNDS = L::ROUNDS, FL = L::FL;
   constexpr int GS = Fd::GS;
-  constexpr bool MIXED = Fd::MIXED, PERSIST = line_persists<N, R>();
+  constexpr bool MIXED = Fd::MIXED;
   double* const sW = head;
   R* const sF = reinterpret_cast<R*>(head + Fd::HEAD);
   double u[ROUNDS][5];
@@ -724,96 +716,173 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
     primitives_to_lds<N, R, VISC, EC>(again(args), head, sF, again(tid), u, s0);
   }
 
-  do {
-    const Place pl(again(args).mesh, e);
-    phase_end();
+  const Place pl(again(args).mesh, e);
+  phase_end();
 
-    // ---- line phase: flux differencing; faces (on the other wave(s)) ---------
-    const auto face = [&](const LineTask<N>& t, int h, const double (&s)[5]) {
-      R gv[3], gT, fs[5];
-      face_values<N, R, EC>(again(args), sF, t, h, pl.neighbour(t.d, h) < 0, s, gv, gT, fs);
+  // ---- line phase: flux differencing; faces (on the other wave(s)) ---------
+  const auto face = [&](const LineTask<N>& t, int h, const double (&s)[5]) {
+    R gv[3], gT, fs[5];
+    face_values<N, R, EC>(again(args), sF, t, h, pl.neighbour(t.d, h) < 0, s, gv, gT, fs);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) sF[Fd::end_at(t.d, 8 * h + k, t.ab)] = gv[k];
+    for (int k = 0; k < 3; ++k) sF[Fd::end_at(t.d, 8 * h + k, t.ab)] = gv[k];
 #pragma unroll
-      for (int k = 0; k < 5; ++k) sF[Fd::end_at(t.d, 8 * h + 3 + k, t.ab)] = fs[k];
-      sF[Fd::GT + h * L::LINES + t.d * NF + t.ab] = gT;
-    };
-    if constexpr (FACE) {
-      const LineArgs& A = again(args);
-      const int lane = again(wtid) - 64 * L::LW;
-      if constexpr (EC) {
-        // one line after the other (the Roe flux is long), the next one's states in
-        // flight meanwhile
-        const long long stride = A.mesh.nE * NN;
-        double cur[HF][5], nxt[HF][5];
+    for (int k = 0; k < 5; ++k) sF[Fd::end_at(t.d, 8 * h + 3 + k, t.ab)] = fs[k];
+    sF[Fd::GT + h * L::LINES + t.d * NF + t.ab] = gT;
+  };
+  if constexpr (FACE) {
+    const LineArgs& A = again(args);
+    const int lane = again(wtid) - 64 * L::LW;
+    if constexpr (EC) {
+      // one line after the other (the Roe flux is long), the next one's states in
+      // flight meanwhile
+      const long long stride = A.mesh.nE * NN;
+      double cur[HF][5], nxt[HF][5];
 #pragma unroll
-        for (int h = 0; h < HF; ++h)
+      for (int h = 0; h < HF; ++h)
 #pragma unroll
-          for (int v = 0; v < 5; ++v) cur[h][v] = su[h][v];
+        for (int v = 0; v < 5; ++v) cur[h][v] = su[h][v];
 #pragma unroll 1
-        for (int q = 0; q < FL; ++q) {
-          const LineTask<N> t = face_line<N>(lane, q), tn = face_line<N>(lane, q + 1 < FL ? q + 1 : q);
-          if (FL > 1)
+      for (int q = 0; q < FL; ++q) {
+        const LineTask<N> t = face_line<N>(lane, q), tn = face_line<N>(lane, q + 1 < FL ? q + 1 : q);
+        if (FL > 1)
 #pragma unroll
-            for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, tn, h, nxt[h]);
+          for (int h = 0; h < HF; ++h) fetch_end<N>(A.U, stride, pl, e, tn, h, nxt[h]);
 #pragma unroll
-          for (int h = 0; h < HF; ++h) {
-            face(t, h, cur[h]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          if (FL > 1)
-#pragma unroll
-            for (int h = 0; h < HF; ++h)
-#pragma unroll
-              for (int v = 0; v < 5; ++v) cur[h][v] = nxt[h][v];
+        for (int h = 0; h < HF; ++h) {
+          face(t, h, cur[h]);
+          __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
+        if (FL > 1)
 #pragma unroll
-        for (int q = 0; q < FL; ++q)
+          for (int h = 0; h < HF; ++h)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) face(face_line<N>(lane, q), h, sn[q][h]);
+            for (int v = 0; v < 5; ++v) cur[h][v] = nxt[h][v];
       }
     } else {
-      if constexpr (HF == 1) {
-        face(LineTask<N>(again(wtid)), 1, su[0]);
+#pragma unroll
+      for (int q = 0; q < FL; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) face(face_line<N>(lane, q), h, sn[q][h]);
+    }
+  } else {
+    if constexpr (HF == 1) {
+      face(LineTask<N>(again(wtid)), 1, su[0]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const LineArgs& A = again(args);
+    const LineTask<N> t(again(wtid));
+    constexpr int NQ = EC && MIXED ? 7 : 6;
+    R q[NQ][NP];  // the fields 0..5 (6), velocities in the line frame
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+      const int l = t.node(m);
+      q[0][m] = sF[l];
+      q[1][m] = sF[(1 + t.d) * EB + l];
+      q[2][m] = sF[(1 + t.d1) * EB + l];
+      q[3][m] = sF[(1 + t.d2) * EB + l];
+      q[4][m] = sF[4 * EB + l];
+      q[5][m] = sF[5 * EB + l];
+      if constexpr (NQ == 7) q[NQ - 1][m] = sF[6 * EB + l];
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+#pragma unroll
+      for (int m = 0; m < NP; ++m) acc[v][m] = R(0);
+    if constexpr (!EC) {
+      // Kennedy-Gruber pairs of half values: with the sums (means) rho, u, v, w,
+      // p, e, f = (m, m u + p, m v, m w, u (rho e + p + p0)), m = rho u; in FP64 p
+      // is relative to the line's first node (p0): the multiple of the row sum
+      // of Q it leaves out of the momentum vanishes, and so do its rounding errors
+      const R ph0 = MIXED ? R(0) : q[4][0], p0 = ph0 + ph0;
+      if (!MIXED)
+#pragma unroll
+        for (int m = 0; m < NP; ++m) q[4][m] -= ph0;
+      const auto pair = [&](int i, int m, R (&f)[5]) {
+        const R rho = q[0][i] + q[0][m], un = q[1][i] + q[1][m], pm = q[4][i] + q[4][m];
+        f[0] = rho * un;
+        f[1] = f[0] * un + pm;
+        f[2] = f[0] * (q[2][i] + q[2][m]);
+        f[3] = f[0] * (q[3][i] + q[3][m]);
+        f[4] = un * (rho * (q[5][i] + q[5][m]) + (MIXED ? pm : pm + p0));
+      };
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+#pragma unroll
+        for (int m = i + 1; m <= N; ++m) {
+          R f[5];
+          pair(i, m, f);
+          const R c = q_im<N, R>(A.basis, i, m);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) {
+            acc[v][i] += c * f[v];
+            acc[v][m] -= c * f[v];
+          }
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
-      const LineArgs& A = again(args);
-      const LineTask<N> t(again(wtid));
-      constexpr int NQ = EC && MIXED ? 7 : 6;
-      R q[NQ][NP];  // the fields 0..5 (6), velocities in the line frame
+      if (MIXED) {  // strong form at the ends: their own flux
+        R f[5];
+        pair(0, 0, f);
 #pragma unroll
-      for (int m = 0; m < NP; ++m) {
-        const int l = t.node(m);
-        q[0][m] = sF[l];
-        q[1][m] = sF[(1 + t.d) * EB + l];
-        q[2][m] = sF[(1 + t.d1) * EB + l];
-        q[3][m] = sF[(1 + t.d2) * EB + l];
-        q[4][m] = sF[4 * EB + l];
-        q[5][m] = sF[5 * EB + l];
-        if constexpr (NQ == 7) q[NQ - 1][m] = sF[6 * EB + l];
+        for (int v = 0; v < 5; ++v) acc[v][0] -= R(0.5) * f[v];
+        pair(N, N, f);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) acc[v][N] += R(0.5) * f[v];
       }
+    } else {
+      // entropy-conserving pairs.  f of the largest pair is that of the line's
+      // extremes: where it is small for rho and beta on every line of the wave,
+      // all logarithmic means take their series (the usual case)
+      const R two_ref = MIXED ? static_cast<R>(2.0 * sW[NP + 2]) : R(0);
+      R lo[2] = {q[0][0], q[4][0]}, hi[2] = {q[0][0], q[4][0]};
 #pragma unroll
-      for (int v = 0; v < 5; ++v)
+      for (int m = 1; m < NP; ++m) {
+        lo[0] = q[0][m] < lo[0] ? q[0][m] : lo[0];
+        hi[0] = q[0][m] > hi[0] ? q[0][m] : hi[0];
+        lo[1] = q[4][m] < lo[1] ? q[4][m] : lo[1];
+        hi[1] = q[4][m] > hi[1] ? q[4][m] : hi[1];
+      }
+      // (sqrt of the bounds on f^2: the short series 1e-4, the long one, also that of
+      // mixed precision, 1e-2)
+      const R dr = hi[0] - lo[0], sr = hi[0] + lo[0], db = hi[1] - lo[1], sb = two_ref + (hi[1] + lo[1]);
+      const bool mid = dr >= R(0.01) * sr || db >= R(0.01) * sb;
+      const bool large = dr >= R(0.1) * sr || db >= R(0.1) * sb;
+      // (momentum relative to the pressure of the line's first node, as above)
+      const R pl0 = MIXED ? R(0) : static_cast<R>(q[0][0] * rcp_nr(q[4][0]));
+      const R k2 = static_cast<R>((MIXED ? 0.5 : 1.0) / A.ph.gm1);
+      const R br = R(0.5) * two_ref, ibr = MIXED ? static_cast<R>(1.0 / sW[NP + 2]) : R(0);
+      const auto pair = [&](int i, int m, R (&f)[5]) {
+        if constexpr (MIXED) {
+          R a[7], b[7];
 #pragma unroll
-        for (int m = 0; m < NP; ++m) acc[v][m] = R(0);
-      if constexpr (!EC) {
-        // Kennedy-Gruber pairs of half values: with the sums (means) rho, u, v, w,
-        // p, e, f = (m, m u + p, m v, m w, u (rho e + p + p0)), m = rho u; in FP64 p
-        // is relative to the line's first node (p0): the multiple of the row sum
-        // of Q it leaves out of the momentum vanishes, and so do its rounding errors
-        const R ph0 = MIXED ? R(0) : q[4][0], p0 = ph0 + ph0;
-        if (!MIXED)
-#pragma unroll
-          for (int m = 0; m < NP; ++m) q[4][m] -= ph0;
-        const auto pair = [&](int i, int m, R (&f)[5]) {
-          const R rho = q[0][i] + q[0][m], un = q[1][i] + q[1][m], pm = q[4][i] + q[4][m];
-          f[0] = rho * un;
-          f[1] = f[0] * un + pm;
-          f[2] = f[0] * (q[2][i] + q[2][m]);
-          f[3] = f[0] * (q[3][i] + q[3][m]);
-          f[4] = un * (rho * (q[5][i] + q[5][m]) + (MIXED ? pm : pm + p0));
-        };
+          for (int c = 0; c < 7; ++c) {
+            a[c] = q[c][i];
+            b[c] = q[c][m];
+          }
+          ec_pair_ref<true>(a, b, k2, br, ibr, f);
+        } else {
+          const double sr = q[0][i] + q[0][m], sb = q[4][i] + q[4][m];  // {{rho}}, 2 {{beta}}
+          const double x = rcp_nr(sr * sb);
+          const double ir = sb * x, ib = sr * x;
+          const double fr = (q[0][i] - q[0][m]) * ir, fb = (q[4][i] - q[4][m]) * ib;
+          const double ur = fr * fr, ub = fb * fb;
+          const double G = 1.0 - ur * (1.0 / 3.0 + ur * (4.0 / 45.0 + ur * (44.0 / 945.0)));
+          const double F = 1.0 + ub * (1.0 / 3.0 + ub * (0.2 + ub * (1.0 / 7.0)));
+          const double p_hat = sr * ib;
+          const double un = q[1][i] + q[1][m], v = q[2][i] + q[2][m], w = q[3][i] + q[3][m];
+          f[0] = sr * G * un;
+          f[1] = f[0] * un + (p_hat - pl0);
+          f[2] = f[0] * v;
+          f[3] = f[0] * w;
+          f[4] = f[0] * (k2 * ib * F - (q[5][i] + q[5][m]) + (un * un + v * v + w * w)) + p_hat * un;
+        }
+      };
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(large) != 0, 0)) {
+        ec_rows<N, R, false>(A, sF, head, t, static_cast<double>(pl0), acc);
+      } else if (!MIXED && __builtin_amdgcn_ballot_w64(mid) != 0) {
+        ec_rows<N, R, true>(A, sF, head, t, static_cast<double>(pl0), acc);
+      } else {
+        settle(q);  // (nothing of the versions is shared, and held, before the branch)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
 #pragma unroll
@@ -826,457 +895,327 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
               acc[v][i] += c * f[v];
               acc[v][m] -= c * f[v];
             }
+            if (m % 2) __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (MIXED) {  // strong form at the ends: their own flux
-          R f[5];
-          pair(0, 0, f);
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v][0] -= R(0.5) * f[v];
-          pair(N, N, f);
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v][N] += R(0.5) * f[v];
-        }
-      } else {
-        // entropy-conserving pairs.  f of the largest pair is that of the line's
-        // extremes: where it is small for rho and beta on every line of the wave,
-        // all logarithmic means take their series (the usual case)
-        const R two_ref = MIXED ? static_cast<R>(2.0 * sW[NP + 2]) : R(0);
-        R lo[2] = {q[0][0], q[4][0]}, hi[2] = {q[0][0], q[4][0]};
-#pragma unroll
-        for (int m = 1; m < NP; ++m) {
-          lo[0] = q[0][m] < lo[0] ? q[0][m] : lo[0];
-          hi[0] = q[0][m] > hi[0] ? q[0][m] : hi[0];
-          lo[1] = q[4][m] < lo[1] ? q[4][m] : lo[1];
-          hi[1] = q[4][m] > hi[1] ? q[4][m] : hi[1];
-        }
-        // (sqrt of the bounds on f^2: the short series 1e-4, the long one, also that of
-        // mixed precision, 1e-2)
-        const R dr = hi[0] - lo[0], sr = hi[0] + lo[0], db = hi[1] - lo[1], sb = two_ref + (hi[1] + lo[1]);
-        const bool mid = dr >= R(0.01) * sr || db >= R(0.01) * sb;
-        const bool large = dr >= R(0.1) * sr || db >= R(0.1) * sb;
-        // (momentum relative to the pressure of the line's first node, as above)
-        const R pl0 = MIXED ? R(0) : static_cast<R>(q[0][0] * rcp_nr(q[4][0]));
-        const R k2 = static_cast<R>((MIXED ? 0.5 : 1.0) / A.ph.gm1);
-        const R br = R(0.5) * two_ref, ibr = MIXED ? static_cast<R>(1.0 / sW[NP + 2]) : R(0);
-        const auto pair = [&](int i, int m, R (&f)[5]) {
-          if constexpr (MIXED) {
-            R a[7], b[7];
-#pragma unroll
-            for (int c = 0; c < 7; ++c) {
-              a[c] = q[c][i];
-              b[c] = q[c][m];
-            }
-            ec_pair_ref<true>(a, b, k2, br, ibr, f);
-          } else {
-            const double sr = q[0][i] + q[0][m], sb = q[4][i] + q[4][m];  // {{rho}}, 2 {{beta}}
-            const double x = rcp_nr(sr * sb);
-            const double ir = sb * x, ib = sr * x;
-            const double fr = (q[0][i] - q[0][m]) * ir, fb = (q[4][i] - q[4][m]) * ib;
-            const double ur = fr * fr, ub = fb * fb;
-            const double G = 1.0 - ur * (1.0 / 3.0 + ur * (4.0 / 45.0 + ur * (44.0 / 945.0)));
-            const double F = 1.0 + ub * (1.0 / 3.0 + ub * (0.2 + ub * (1.0 / 7.0)));
-            const double p_hat = sr * ib;
-            const double un = q[1][i] + q[1][m], v = q[2][i] + q[2][m], w = q[3][i] + q[3][m];
-            f[0] = sr * G * un;
-            f[1] = f[0] * un + (p_hat - pl0);
-            f[2] = f[0] * v;
-            f[3] = f[0] * w;
-            f[4] = f[0] * (k2 * ib * F - (q[5][i] + q[5][m]) + (un * un + v * v + w * w)) + p_hat * un;
-          }
-        };
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(large) != 0, 0)) {
-          ec_rows<N, R, false>(A, sF, head, t, static_cast<double>(pl0), acc);
-        } else if (!MIXED && __builtin_amdgcn_ballot_w64(mid) != 0) {
-          ec_rows<N, R, true>(A, sF, head, t, static_cast<double>(pl0), acc);
-        } else {
-          settle(q);  // (nothing of the versions is shared, and held, before the branch)
-#pragma unroll
-          for (int i = 0; i < N; ++i) {
-#pragma unroll
-            for (int m = i + 1; m <= N; ++m) {
-              R f[5];
-              pair(i, m, f);
-              const R c = q_im<N, R>(A.basis, i, m);
-#pragma unroll
-              for (int v = 0; v < 5; ++v) {
-                acc[v][i] += c * f[v];
-                acc[v][m] -= c * f[v];
-              }
-              if (m % 2) __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-        }
-        if (MIXED) {
-          R f[5];
-          pair(0, 0, f);
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v][0] -= R(0.5) * f[v];
-          pair(N, N, f);
-#pragma unroll
-          for (int v = 0; v < 5; ++v) acc[v][N] += R(0.5) * f[v];
         }
       }
-      settle(acc);
+      if (MIXED) {
+        R f[5];
+        pair(0, 0, f);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) acc[v][0] -= R(0.5) * f[v];
+        pair(N, N, f);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) acc[v][N] += R(0.5) * f[v];
+      }
     }
-    phase_end();
+    settle(acc);
+  }
+  phase_end();
 
-    // ---- line phase: gradients ------------------------------------------------
-    R fn[FACE ? FL : 2][3];  // face lanes: (line, end); line lanes: (end, component)
-    R dun[NP], fm[2];        // mixed precision: sum D u / 2 and the faces' mass parts
-    if constexpr (!FACE) {
-      const LineArgs& A = again(args);
-      const LineTask<N> t(again(wtid));
-      const int nb[2] = {pl.neighbour(t.d, 0), pl.neighbour(t.d, 1)};
-      R gh[2][3];
+  // ---- line phase: gradients ------------------------------------------------
+  R fn[FACE ? FL : 2][3];  // face lanes: (line, end); line lanes: (end, component)
+  R dun[NP], fm[2];        // mixed precision: sum D u / 2 and the faces' mass parts
+  if constexpr (!FACE) {
+    const LineArgs& A = again(args);
+    const LineTask<N> t(again(wtid));
+    const int nb[2] = {pl.neighbour(t.d, 0), pl.neighbour(t.d, 1)};
+    R gh[2][3];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) gh[h][c] = sF[Fd::end_at(t.d, 8 * h + c, t.ab)];
-        fm[h] = sF[Fd::end_at(t.d, 8 * h + 3, t.ab)];
-        if (!MIXED) acc[0][h ? N : 0] += fm[h];
+      for (int c = 0; c < 3; ++c) gh[h][c] = sF[Fd::end_at(t.d, 8 * h + c, t.ab)];
+      fm[h] = sF[Fd::end_at(t.d, 8 * h + 3, t.ab)];
+      if (!MIXED) acc[0][h ? N : 0] += fm[h];
 #pragma unroll
-        for (int v = 1; v < 5; ++v) acc[v][h ? N : 0] += sF[Fd::end_at(t.d, 8 * h + 3 + v, t.ab)];
-      }
-      if (VISC) {
-        // the neighbours' normal viscous flux at the ends, in flight over the next phases
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const R* src = static_cast<const R*>(A.ffv) + static_cast<long long>(nb[h] >= 0 ? nb[h] : e) * (6 * 4 * NF) +
-                         (2 * t.d + 1 - h) * (4 * NF);
-          const unsigned ab = t.ab;
-          fn[h][0] = load_once(&(src + t.d * NF)[ab]);
-          fn[h][1] = load_once(&(src + t.d1 * NF)[ab]);
-          fn[h][2] = load_once(&(src + t.d2 * NF)[ab]);
-        }
-        // (tangential components at a wall-model wall: the modelled stress)
-        if (A.mesh.tauw != nullptr && pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            if (nb[h] < 0) {
-              const double* tw = A.mesh.tauw + wall_face_index(A.mesh, pl.ex, pl.ey, pl.ez, t.d, h != 0) * 3 * NF + t.ab;
-              fn[h][1] = static_cast<R>(tw[t.d1 * NF]);
-              fn[h][2] = static_cast<R>(tw[t.d2 * NF]);
-            }
-      }
-      if (VISC || MIXED) {
-        int ad[NP];
-#pragma unroll
-        for (int m = 0; m < NP; ++m) ad[m] = t.node(m);
-#pragma unroll
-        for (int c = 0; c < (VISC ? 3 : 1); ++c) {
-          const int qc = c == 0 ? t.d : (c == 1 ? t.d1 : t.d2);
-          R q[NP], g[NP];
-#pragma unroll
-          for (int m = 0; m < NP; ++m) q[m] = sF[(1 + qc) * EB + ad[m]];
-          if (MIXED) {
-            line_derivative<N, R, true>(A.basis, q, R(0), R(0), g);
-            if (c == 0)
-#pragma unroll
-              for (int m = 0; m < NP; ++m) dun[m] = g[m];
-            g[0] -= R(0.5) * gh[0][c];
-            g[N] += R(0.5) * gh[1][c];
-          } else {
-            line_derivative<N, R, false>(A.basis, q, gh[0][c], gh[1][c], g);
-          }
-          if (VISC)
-#pragma unroll
-            for (int m = 0; m < NP; ++m) sF[(GS + 3 * qc + t.d) * EB + ad[m]] = g[m];
-        }
-      }
-      settle(acc);
-    } else if (VISC) {
-      // heat flux: it needs the temperature's derivative along the line only
-      // (half value; a wall's ghost is 2 q* - q: the own heat flux at an isothermal
-      // wall, none at an adiabatic one)
-      const LineArgs& A = again(args);
-      const int lane = again(wtid) - 64 * L::LW;
-#pragma unroll
-      for (int q = 0; q < FL; ++q) {
-        const LineTask<N> t = face_line<N>(lane, q);
-        const int nb[2] = {pl.neighbour(t.d, 0), pl.neighbour(t.d, 1)};
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          fn[q][h] = load_once(&(static_cast<const R*>(A.ffv) + static_cast<long long>(nb[h] >= 0 ? nb[h] : e) * (6 * 4 * NF) +
-                                 ((2 * t.d + 1 - h) * 4 + 3) * NF)[static_cast<unsigned>(t.ab)]);
-        R T[NP], g[NP];
-#pragma unroll
-        for (int m = 0; m < NP; ++m) T[m] = sF[Fd::TS * EB + t.node(m)];
-        const int gt = Fd::GT + t.d * NF + t.ab;
-        line_derivative<N, R, MIXED>(A.basis, T, sF[gt], sF[gt + L::LINES], g);
-        const double sk = 0.5 * A.ph.kappa * (t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz));
-#pragma unroll
-        for (int m = 0; m < NP; ++m) g[m] *= static_cast<R>(sk * A.basis.inv_w[m]);
-        if (A.ph.suth)
-#pragma unroll
-          for (int m = 0; m < NP; ++m) g[m] *= sF[Fd::MU + t.node(m)];
-        const R qw = pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL ? R(-1) : R(1);
-        line_derivative<N, R, false>(A.basis, g, (nb[0] < 0 ? qw : R(0)) * g[0], (nb[1] < 0 ? qw : R(0)) * g[N], eh[q]);
-      }
-      settle(eh);
-      if constexpr (PERSIST && !EC) {
-        const LineArgs& B = again(args);
-        const int en = e + step_e < end_e ? e + step_e : e;
-        fetch_faces<N>(B.U, B.mesh.nE * NN, Place(B.mesh, en), en, again(wtid) - 64 * L::LW, sn);
-      }
+      for (int v = 1; v < 5; ++v) acc[v][h ? N : 0] += sF[Fd::end_at(t.d, 8 * h + 3 + v, t.ab)];
     }
     if (VISC) {
-      phase_end();
-
-      // ---- node phase: velocity gradients -> half viscous fluxes (in place) ---
-      {
-        const LineArgs& A = again(args);
-        const int ts = again(tid);
+      // the neighbours' normal viscous flux at the ends, in flight over the next phases
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-          const unsigned n = ts + r * BS;
-          if (n < NN) {
-            const int i = n % NP, j = (n / NP) % NP, k = n / NF;
-            const int l = L::at(i, j, k);
-            const R c0 = static_cast<R>(pl.sx * sW[i]), c1 = static_cast<R>(pl.sy * sW[j]), c2 = static_cast<R>(pl.sz * sW[k]);
-            R mu = static_cast<R>(A.ph.mu);  // half fluxes: the gradients are those of half velocities
-            if (A.ph.suth) mu *= sF[Fd::MU + l];
-            R gr[9];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              gr[3 * c] = c0 * sF[(GS + 3 * c) * EB + l];
-              gr[3 * c + 1] = c1 * sF[(GS + 1 + 3 * c) * EB + l];
-              gr[3 * c + 2] = c2 * sF[(GS + 2 + 3 * c) * EB + l];
-            }
-            const R dd = R(2.0 / 3.0) * (gr[0] + gr[4] + gr[8]);
-            const R t00 = mu * (gr[0] + gr[0] - dd), t11 = mu * (gr[4] + gr[4] - dd), t22 = mu * (gr[8] + gr[8] - dd);
-            const R t01 = mu * (gr[1] + gr[3]), t02 = mu * (gr[2] + gr[6]), t12 = mu * (gr[5] + gr[7]);
-            const R uu = R(2) * sF[EB + l], vv = R(2) * sF[2 * EB + l], ww = R(2) * sF[3 * EB + l];
-            sF[GS * EB + l] = t00;
-            sF[(GS + 1) * EB + l] = t11;
-            sF[(GS + 2) * EB + l] = t22;
-            sF[(GS + 3) * EB + l] = t01;
-            sF[(GS + 4) * EB + l] = t02;
-            sF[(GS + 5) * EB + l] = t12;
-            sF[(GS + 6) * EB + l] = uu * t00 + vv * t01 + ww * t02;
-            sF[(GS + 7) * EB + l] = uu * t01 + vv * t11 + ww * t12;
-            sF[(GS + 8) * EB + l] = uu * t02 + vv * t12 + ww * t22;
-          }
-        }
+      for (int h = 0; h < 2; ++h) {
+        const R* src = static_cast<const R*>(A.ffv) + static_cast<long long>(nb[h] >= 0 ? nb[h] : e) * (6 * 4 * NF) +
+                       (2 * t.d + 1 - h) * (4 * NF);
+        const unsigned ab = t.ab;
+        fn[h][0] = load_once(&(src + t.d * NF)[ab]);
+        fn[h][1] = load_once(&(src + t.d1 * NF)[ab]);
+        fn[h][2] = load_once(&(src + t.d2 * NF)[ab]);
       }
-      phase_end();
-    }
-
-    // G of this element is in flight over the rest
-    __builtin_amdgcn_sched_barrier(0);
-    const int tl = again(tid);
-    double gA[ROUNDS][5];
-    if (RK) {
-      const LineArgs& A = again(args);
-      const long long stride = A.mesh.nE * NN;
-      // (the first stage has no G: it reads U's rows again, mostly from cache)
-      const double* G = A.st.read_G ? A.out : A.U;
+      // (tangential components at a wall-model wall: the modelled stress)
+      if (A.mesh.tauw != nullptr && pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL)
 #pragma unroll
-      for (int r = 0; r < ROUNDS; ++r)
-#pragma unroll
-        for (int v = 0; v < 5; ++v)
-          gA[r][v] = load_once(&(G + v * stride + static_cast<long long>(e) * NN)[node_of<N>(tl, r)]);
+        for (int h = 0; h < 2; ++h)
+          if (nb[h] < 0) {
+            const double* tw = A.mesh.tauw + wall_face_index(A.mesh, pl.ex, pl.ey, pl.ez, t.d, h != 0) * 3 * NF + t.ab;
+            fn[h][1] = static_cast<R>(tw[t.d1 * NF]);
+            fn[h][2] = static_cast<R>(tw[t.d2 * NF]);
+          }
     }
-
-    // ---- line phase: divergence of the viscous flux --------------------------
-    if constexpr (VISC && !FACE) {
-      const LineArgs& A = again(args);
-      const LineTask<N> t(again(wtid));
-      const int nb[2] = {pl.neighbour(t.d, 0), pl.neighbour(t.d, 1)};
-      const bool wm = pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL;
+    if (VISC || MIXED) {
       int ad[NP];
 #pragma unroll
       for (int m = 0; m < NP; ++m) ad[m] = t.node(m);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        // tau_qd: the diagonal at GS + d, (0,1), (0,2), (1,2) at GS + 2 + q + d
-        const int qc = c == 1 ? t.d1 : t.d2;
-        const int slot = c == 0 ? GS + t.d : GS + 2 + qc + t.d;
-        R f[NP], g[NP], gw[2];
+      for (int c = 0; c < (VISC ? 3 : 1); ++c) {
+        const int qc = c == 0 ? t.d : (c == 1 ? t.d1 : t.d2);
+        R q[NP], g[NP];
 #pragma unroll
-        for (int m = 0; m < NP; ++m) f[m] = sF[slot * EB + ad[m]];
-        // ghosts: half the neighbour's flux; at a wall 2 f* - f: the own stresses at
-        // an isothermal no-slip wall; the own normal stress and the modelled shear
-        // stress at a wall-model wall
+        for (int m = 0; m < NP; ++m) q[m] = sF[(1 + qc) * EB + ad[m]];
+        if (MIXED) {
+          line_derivative<N, R, true>(A.basis, q, R(0), R(0), g);
+          if (c == 0)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const bool wall = nb[h] < 0;
-          const R of_n = !wall ? R(0.5) : (wm && c > 0 ? (h ? R(-1) : R(1)) : R(0));
-          const R of_o = !wall ? R(0) : (wm && c > 0 ? R(-1) : R(1));
-          gw[h] = of_n * fn[h][c] + of_o * f[h ? N : 0];
+            for (int m = 0; m < NP; ++m) dun[m] = g[m];
+          g[0] -= R(0.5) * gh[0][c];
+          g[N] += R(0.5) * gh[1][c];
+        } else {
+          line_derivative<N, R, false>(A.basis, q, gh[0][c], gh[1][c], g);
         }
-        line_derivative<N, R, false>(A.basis, f, gw[0], gw[1], g);
+        if (VISC)
 #pragma unroll
-        for (int m = 0; m < NP; ++m) acc[1 + c][m] -= g[m];
+          for (int m = 0; m < NP; ++m) sF[(GS + 3 * qc + t.d) * EB + ad[m]] = g[m];
       }
-      settle(acc);
-    } else if constexpr (VISC) {
-      // the stresses' work, u . tau_d (a wall's own does no work: ghost -f)
-      const LineArgs& A = again(args);
-      const int lane = again(wtid) - 64 * L::LW;
-#pragma unroll
-      for (int q = 0; q < FL; ++q) {
-        const LineTask<N> t = face_line<N>(lane, q);
-        R f[NP], g[NP];
-#pragma unroll
-        for (int m = 0; m < NP; ++m) f[m] = sF[(GS + 6 + t.d) * EB + t.node(m)];
-        const R g0 = pl.neighbour(t.d, 0) < 0 ? -f[0] : R(0.5) * fn[q][0];
-        const R g1 = pl.neighbour(t.d, 1) < 0 ? -f[N] : R(0.5) * fn[q][1];
-        line_derivative<N, R, false>(A.basis, f, g0, g1, g);
-#pragma unroll
-        for (int m = 0; m < NP; ++m) eh[q][m] += g[m];
-      }
-      settle(eh);
     }
+    settle(acc);
+  } else if (VISC) {
+    // heat flux: it needs the temperature's derivative along the line only
+    // (half value; a wall's ghost is 2 q* - q: the own heat flux at an isothermal
+    // wall, none at an adiabatic one)
+    const LineArgs& A = again(args);
+    const int lane = again(wtid) - 64 * L::LW;
+#pragma unroll
+    for (int q = 0; q < FL; ++q) {
+      const LineTask<N> t = face_line<N>(lane, q);
+      const int nb[2] = {pl.neighbour(t.d, 0), pl.neighbour(t.d, 1)};
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        fn[q][h] = load_once(&(static_cast<const R*>(A.ffv) + static_cast<long long>(nb[h] >= 0 ? nb[h] : e) * (6 * 4 * NF) +
+                               ((2 * t.d + 1 - h) * 4 + 3) * NF)[static_cast<unsigned>(t.ab)]);
+      R T[NP], g[NP];
+#pragma unroll
+      for (int m = 0; m < NP; ++m) T[m] = sF[Fd::TS * EB + t.node(m)];
+      const int gt = Fd::GT + t.d * NF + t.ab;
+      line_derivative<N, R, MIXED>(A.basis, T, sF[gt], sF[gt + L::LINES], g);
+      const double sk = 0.5 * A.ph.kappa * (t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz));
+#pragma unroll
+      for (int m = 0; m < NP; ++m) g[m] *= static_cast<R>(sk * A.basis.inv_w[m]);
+      if (A.ph.suth)
+#pragma unroll
+        for (int m = 0; m < NP; ++m) g[m] *= sF[Fd::MU + t.node(m)];
+      const R qw = pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL ? R(-1) : R(1);
+      line_derivative<N, R, false>(A.basis, g, (nb[0] < 0 ? qw : R(0)) * g[0], (nb[1] < 0 ? qw : R(0)) * g[N], eh[q]);
+    }
+    settle(eh);
+  }
+  if (VISC) {
+    phase_end();
 
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- sums of the three directions, scaling, output -----------------------
-    // the next element's first loads are in flight over the exchange (the own
-    // state stays in registers for the update: read again here it would mostly
-    // come from HBM)
-    double un[ROUNDS][5];
-    if (PERSIST) {
-      const LineArgs& A = again(args);
-      const long long stride = A.mesh.nE * NN;
-      const int en = e + step_e < end_e ? e + step_e : e;
-      fetch_nodes<N>(A.U, stride, en, tl, un);
-      if constexpr (FACE && !VISC && !EC) fetch_faces<N>(A.U, stride, Place(A.mesh, en), en, again(wtid) - 64 * L::LW, sn);
-    }
-    phase_end();
-    if constexpr (!FACE) {
-      const LineTask<N> t(again(wtid));
-      R* o = sF + (MIXED ? 4 : 5) * t.d * EB;
-      const double p_ref = MIXED ? sW[NP] : 0.0, e_ref = MIXED ? sW[NP + 1] : 0.0;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) {
-        const int l = t.node(m);
-        if (MIXED)
-          reinterpret_cast<double*>(sF + (12 + 2 * t.d) * EB)[l] =
-              static_cast<double>(acc[4][m]) + e_ref * static_cast<double>(acc[0][m]) + p_ref * static_cast<double>(dun[m]);
-        else
-          o[4 * EB + l] = acc[4][m];
-        o[l] = MIXED && m == 0 ? acc[0][m] + fm[0] : (MIXED && m == N ? acc[0][m] + fm[1] : acc[0][m]);
-        o[(1 + t.d) * EB + l] = acc[1][m];
-        o[(1 + t.d1) * EB + l] = acc[2][m];
-        o[(1 + t.d2) * EB + l] = acc[3][m];
-      }
-    } else if constexpr (VISC) {
-      const int lane = again(wtid) - 64 * L::LW;
-#pragma unroll
-      for (int q = 0; q < FL; ++q) {
-        const LineTask<N> t = face_line<N>(lane, q);
-#pragma unroll
-        for (int m = 0; m < NP; ++m) sF[((MIXED ? 18 : 15) + t.d) * EB + t.node(m)] = eh[q][m];
-      }
-    }
-    phase_end();
-    double g1[ROUNDS][5], u1[ROUNDS][5];  // Ut or the new G, and the new U
+    // ---- node phase: velocity gradients -> half viscous fluxes (in place) ---
     {
       const LineArgs& A = again(args);
+      const int ts = again(tid);
 #pragma unroll
       for (int r = 0; r < ROUNDS; ++r) {
-        const unsigned n = node_of<N>(tl, r);
-        const int i = n % NP, j = (n / NP) % NP, k = n / NF;
-        const int l = L::at(i, j, k);
-        const double c[3] = {-2.0 * (pl.sx * sW[i]), -2.0 * (pl.sy * sW[j]), -2.0 * (pl.sz * sW[k])};
+        const unsigned n = ts + r * BS;
+        if (n < NN) {
+          const int i = n % NP, j = (n / NP) % NP, k = n / NF;
+          const int l = L::at(i, j, k);
+          const R c0 = static_cast<R>(pl.sx * sW[i]), c1 = static_cast<R>(pl.sy * sW[j]), c2 = static_cast<R>(pl.sz * sW[k]);
+          R mu = static_cast<R>(A.ph.mu);  // half fluxes: the gradients are those of half velocities
+          if (A.ph.suth) mu *= sF[Fd::MU + l];
+          R gr[9];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            gr[3 * c] = c0 * sF[(GS + 3 * c) * EB + l];
+            gr[3 * c + 1] = c1 * sF[(GS + 1 + 3 * c) * EB + l];
+            gr[3 * c + 2] = c2 * sF[(GS + 2 + 3 * c) * EB + l];
+          }
+          const R dd = R(2.0 / 3.0) * (gr[0] + gr[4] + gr[8]);
+          const R t00 = mu * (gr[0] + gr[0] - dd), t11 = mu * (gr[4] + gr[4] - dd), t22 = mu * (gr[8] + gr[8] - dd);
+          const R t01 = mu * (gr[1] + gr[3]), t02 = mu * (gr[2] + gr[6]), t12 = mu * (gr[5] + gr[7]);
+          const R uu = R(2) * sF[EB + l], vv = R(2) * sF[2 * EB + l], ww = R(2) * sF[3 * EB + l];
+          sF[GS * EB + l] = t00;
+          sF[(GS + 1) * EB + l] = t11;
+          sF[(GS + 2) * EB + l] = t22;
+          sF[(GS + 3) * EB + l] = t01;
+          sF[(GS + 4) * EB + l] = t02;
+          sF[(GS + 5) * EB + l] = t12;
+          sF[(GS + 6) * EB + l] = uu * t00 + vv * t01 + ww * t02;
+          sF[(GS + 7) * EB + l] = uu * t01 + vv * t11 + ww * t12;
+          sF[(GS + 8) * EB + l] = uu * t02 + vv * t12 + ww * t22;
+        }
+      }
+    }
+    phase_end();
+  }
+
+  // G of this element is in flight over the rest
+  __builtin_amdgcn_sched_barrier(0);
+  const int tl = again(tid);
+  double gA[ROUNDS][5];
+  if (RK) {
+    const LineArgs& A = again(args);
+    const long long stride = A.mesh.nE * NN;
+    // (the first stage has no G: it reads U's rows again, mostly from cache)
+    const double* G = A.st.read_G ? A.out : A.U;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+      for (int v = 0; v < 5; ++v)
+        gA[r][v] = load_once(&(G + v * stride + static_cast<long long>(e) * NN)[node_of<N>(tl, r)]);
+  }
+
+  // ---- line phase: divergence of the viscous flux --------------------------
+  if constexpr (VISC && !FACE) {
+    const LineArgs& A = again(args);
+    const LineTask<N> t(again(wtid));
+    const int nb[2] = {pl.neighbour(t.d, 0), pl.neighbour(t.d, 1)};
+    const bool wm = pick3(A.mesh.bc[0], A.mesh.bc[1], A.mesh.bc[2], t.d) == DG_BC_WALL_MODEL;
+    int ad[NP];
+#pragma unroll
+    for (int m = 0; m < NP; ++m) ad[m] = t.node(m);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      // tau_qd: the diagonal at GS + d, (0,1), (0,2), (1,2) at GS + 2 + q + d
+      const int qc = c == 1 ? t.d1 : t.d2;
+      const int slot = c == 0 ? GS + t.d : GS + 2 + qc + t.d;
+      R f[NP], g[NP], gw[2];
+#pragma unroll
+      for (int m = 0; m < NP; ++m) f[m] = sF[slot * EB + ad[m]];
+      // ghosts: half the neighbour's flux; at a wall 2 f* - f: the own stresses at
+      // an isothermal no-slip wall; the own normal stress and the modelled shear
+      // stress at a wall-model wall
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool wall = nb[h] < 0;
+        const R of_n = !wall ? R(0.5) : (wm && c > 0 ? (h ? R(-1) : R(1)) : R(0));
+        const R of_o = !wall ? R(0) : (wm && c > 0 ? R(-1) : R(1));
+        gw[h] = of_n * fn[h][c] + of_o * f[h ? N : 0];
+      }
+      line_derivative<N, R, false>(A.basis, f, gw[0], gw[1], g);
+#pragma unroll
+      for (int m = 0; m < NP; ++m) acc[1 + c][m] -= g[m];
+    }
+    settle(acc);
+  } else if constexpr (VISC) {
+    // the stresses' work, u . tau_d (a wall's own does no work: ghost -f)
+    const LineArgs& A = again(args);
+    const int lane = again(wtid) - 64 * L::LW;
+#pragma unroll
+    for (int q = 0; q < FL; ++q) {
+      const LineTask<N> t = face_line<N>(lane, q);
+      R f[NP], g[NP];
+#pragma unroll
+      for (int m = 0; m < NP; ++m) f[m] = sF[(GS + 6 + t.d) * EB + t.node(m)];
+      const R g0 = pl.neighbour(t.d, 0) < 0 ? -f[0] : R(0.5) * fn[q][0];
+      const R g1 = pl.neighbour(t.d, 1) < 0 ? -f[N] : R(0.5) * fn[q][1];
+      line_derivative<N, R, false>(A.basis, f, g0, g1, g);
+#pragma unroll
+      for (int m = 0; m < NP; ++m) eh[q][m] += g[m];
+    }
+    settle(eh);
+  }
+
+  __builtin_amdgcn_sched_barrier(0);
+  // ---- sums of the three directions, scaling, output -----------------------
+  phase_end();
+  if constexpr (!FACE) {
+    const LineTask<N> t(again(wtid));
+    R* o = sF + (MIXED ? 4 : 5) * t.d * EB;
+    const double p_ref = MIXED ? sW[NP] : 0.0, e_ref = MIXED ? sW[NP + 1] : 0.0;
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+      const int l = t.node(m);
+      if (MIXED)
+        reinterpret_cast<double*>(sF + (12 + 2 * t.d) * EB)[l] =
+            static_cast<double>(acc[4][m]) + e_ref * static_cast<double>(acc[0][m]) + p_ref * static_cast<double>(dun[m]);
+      else
+        o[4 * EB + l] = acc[4][m];
+      o[l] = MIXED && m == 0 ? acc[0][m] + fm[0] : (MIXED && m == N ? acc[0][m] + fm[1] : acc[0][m]);
+      o[(1 + t.d) * EB + l] = acc[1][m];
+      o[(1 + t.d1) * EB + l] = acc[2][m];
+      o[(1 + t.d2) * EB + l] = acc[3][m];
+    }
+  } else if constexpr (VISC) {
+    const int lane = again(wtid) - 64 * L::LW;
+#pragma unroll
+    for (int q = 0; q < FL; ++q) {
+      const LineTask<N> t = face_line<N>(lane, q);
+#pragma unroll
+      for (int m = 0; m < NP; ++m) sF[((MIXED ? 18 : 15) + t.d) * EB + t.node(m)] = eh[q][m];
+    }
+  }
+  phase_end();
+  double g1[ROUNDS][5], u1[ROUNDS][5];  // Ut or the new G, and the new U
+  {
+    const LineArgs& A = again(args);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const unsigned n = node_of<N>(tl, r);
+      const int i = n % NP, j = (n / NP) % NP, k = n / NF;
+      const int l = L::at(i, j, k);
+      const double c[3] = {-2.0 * (pl.sx * sW[i]), -2.0 * (pl.sy * sW[j]), -2.0 * (pl.sz * sW[k])};
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        double ut = 0.0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          double f;
+          if (!MIXED)
+            f = sF[(5 * d + v) * EB + l];
+          else if (v < 4)
+            f = sF[(4 * d + v) * EB + l];
+          else
+            f = reinterpret_cast<const double*>(sF + (12 + 2 * d) * EB)[l];
+          if (VISC && v == 4) f -= static_cast<double>(sF[((MIXED ? 18 : 15) + d) * EB + l]);
+          ut = d == 0 ? c[0] * f : ut + c[d] * f;
+        }
+        if (RK) {
+          g1[r][v] = A.st.read_G ? A.st.A * gA[r][v] + A.st.dt * ut : A.st.dt * ut;
+          u1[r][v] = u[r][v] + A.st.B * g1[r][v];
+        } else {
+          g1[r][v] = ut;
+        }
+      }
+    }
+  }
+  {
+    const LineArgs& A = again(args);
+    const long long stride = A.mesh.nE * NN, base = static_cast<long long>(e) * NN;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const unsigned n = again(tid) + r * BS;
+      if (NN % BS == 0 || n < NN)
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
-          double ut = 0.0;
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            double f;
-            if (!MIXED)
-              f = sF[(5 * d + v) * EB + l];
-            else if (v < 4)
-              f = sF[(4 * d + v) * EB + l];
-            else
-              f = reinterpret_cast<const double*>(sF + (12 + 2 * d) * EB)[l];
-            if (VISC && v == 4) f -= static_cast<double>(sF[((MIXED ? 18 : 15) + d) * EB + l]);
-            ut = d == 0 ? c[0] * f : ut + c[d] * f;
-          }
-          if (RK) {
-            g1[r][v] = A.st.read_G ? A.st.A * gA[r][v] + A.st.dt * ut : A.st.dt * ut;
-            u1[r][v] = u[r][v] + A.st.B * g1[r][v];
-          } else {
-            g1[r][v] = ut;
-          }
+          store_once(&(A.out + v * stride + base)[n], g1[r][v]);
+          if (RK) store_once(&(A.U_out + v * stride + base)[n], u1[r][v]);
         }
-      }
     }
-    if constexpr (PERSIST) {
-      // the next element's primitives before this one's stores: a load is waited
-      // for together with all stores issued before it
-      settle(g1);
-      if (RK) settle(u1);
-      if constexpr (EC) fetch_su(again(args), e + step_e < end_e ? e + step_e : e);
-      phase_end();
-      const double s0[5] = {1, 0, 0, 0, 1};
-      primitives_to_lds<N, R, VISC, EC>(again(args), head, sF, again(tid), un, s0);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int r = 0; r < ROUNDS; ++r)
-#pragma unroll
-        for (int v = 0; v < 5; ++v) u[r][v] = un[r][v];
-    }
-    {
-      const LineArgs& A = again(args);
-      const long long stride = A.mesh.nE * NN, base = static_cast<long long>(e) * NN;
-#pragma unroll
-      for (int r = 0; r < ROUNDS; ++r) {
-        const unsigned n = again(tid) + r * BS;
-        if (NN % BS == 0 || n < NN)
-#pragma unroll
-          for (int v = 0; v < 5; ++v) {
-            store_once(&(A.out + v * stride + base)[n], g1[r][v]);
-            if (RK) store_once(&(A.U_out + v * stride + base)[n], u1[r][v]);
-          }
-      }
-    }
-    e += step_e;
-  } while (PERSIST && e < end_e);
+  }
 }
 
 template <int N, typename R, bool RK, bool VISC, bool EC>
 __global__ __launch_bounds__(Line<N>::BS) __attribute__((amdgpu_waves_per_eu(line_waves<N, R, EC>()))) void k_rhs_line(LineArgs) {
   using L = Line<N>;
-  constexpr bool PERSIST = line_persists<N, R>();
   extern __shared__ double lds[];
   const LineArgsPtr args = (LineArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  const int tid = threadIdx.x;
-  // elements of this workgroup: those of its XCD (workgroup index modulo 8) in
-  // steps of the XCD's workgroups, so that an XCD's workgroups sweep one
-  // contiguous range together
-  const int blk = static_cast<int>(blockIdx.x);
-  int e, step_e = 0, end_e = 0;
-  if constexpr (PERSIST) {
-    const int nE = static_cast<int>(again(args).mesh.nE), grid = static_cast<int>(gridDim.x), xcd = blk & 7;
-    const int q8 = nE >> 3, r8 = nE & 7;
-    const int begin = xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8;
-    end_e = begin + q8 + (xcd < r8 ? 1 : 0);
-    e = begin + (blk >> 3);
-    step_e = (grid + 7 - xcd) >> 3;
-    if (e >= end_e) return;
-  } else {
-    e = xcd_remap(blk, gridDim.x);
-  }
+  const int tid = threadIdx.x, blk = static_cast<int>(blockIdx.x);
+  const int e = xcd_remap(blk, gridDim.x);
   // line lane number of this lane; face lanes are those of the last FW waves.  At
   // N = 7 which of the four waves that is changes from workgroup to workgroup, so
   // that not all face waves share a SIMD.
   const int turn = L::UNIFORM ? ((blk >> 3) + (blk >> 8)) & 3 : 0;
   const int wtid = L::UNIFORM ? (tid + 64 * turn) & 255 : tid;
   if (__builtin_amdgcn_readfirstlane(wtid) >= 64 * L::LW)
-    rhs_line_phases<N, R, RK, VISC, EC, true>(args, lds, e, step_e, end_e, tid, wtid);
+    rhs_line_phases<N, R, RK, VISC, EC, true>(args, lds, e, tid, wtid);
   else
-    rhs_line_phases<N, R, RK, VISC, EC, false>(args, lds, e, step_e, end_e, tid, wtid);
+    rhs_line_phases<N, R, RK, VISC, EC, false>(args, lds, e, tid, wtid);
 }
 
 template <int N, typename R, bool EC, bool RK>
 hipError_t line_n(const LineArgs& a, hipStream_t s) {
-  // persistent: as many workgroups as run at once (two per CU), each fetching its
-  // next element while it works on one
-  const long long most = line_persists<N, R>() ? 512 : a.mesh.nE;
-  const dim3 grid(static_cast<unsigned>(a.mesh.nE < most ? a.mesh.nE : most)), block(Line<N>::BS);
+  const dim3 grid(static_cast<unsigned>(a.mesh.nE)), block(Line<N>::BS);
   const size_t lds = Fields<N, R, EC>::bytes(a.ph);
   if (a.ph.viscous)
     hipLaunchKernelGGL((k_rhs_line<N, R, RK, true, EC>), grid, block, lds, s, a);

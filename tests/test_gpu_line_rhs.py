@@ -1,7 +1,6 @@
 """The line-lane right-hand side (GPU) at the sizes where its work split can go
 wrong: fewer elements than XCDs, element counts that are no multiple of the
-workgroups (at N = 7 a workgroup works on several elements in turn, from 513
-elements on), every degree, walls of both kinds on each axis, with and without
+XCDs, every degree, walls of both kinds on each axis, with and without
 viscosity, Sutherland's law, the right-hand side alone and as an RK step.
 
 With the entropy-conserving pair also states of smaller spreads, where a line's
