@@ -78,26 +78,27 @@ STORED_GRADIENT_BYTES_PER_DOF = 392.0
 # 20, RK update 20, scaling 15.
 ALG_FLOPS_PER_DOF_STAGE = 940.0
 # FP64 flops per DOF and stage counted with rocprofv3 (SQ_INSTS_VALU_{ADD,MUL,
-# FMA,TRANS}_F64 x 64 lanes, FMA twice) on k_rhs + k_face_flux of this
+# FMA,TRANS}_F64 x 64 lanes, FMA twice) on k_rhs_line + k_face_flux of this
 # workload; valid only for the kernel sources they were counted on.
-COUNTED_FLOPS = {"sources_sha256_prefix": "d24ddbf48a2f0125", "per_dof_stage": 1302.25 + 219.375}
+COUNTED_FLOPS = {"sources_sha256_prefix": "b6862983a27cf09f", "per_dof_stage": 1014.750 + 151.375}
 
-# HBM bytes per launch of k_rhs<7,double> on this workload, from rocprofv3
+# HBM bytes per launch of k_rhs_line<7,double> on this workload, from rocprofv3
 # counter passes (profiles/k_rhs_k_face_flux_tgv_n7_32x32x32.md): reads
-# 128 x 13,968,395.1 TCC_EA0_RDREQ_128B + 64 x 2,077.0 RDREQ_64B, writes
-# WRITE_SIZE 1,310,764.8 KiB.  Valid only for the kernel sources it was
+# 128 x 13,973,355 TCC_EA0_RDREQ_128B + 64 x 4,858 RDREQ_64B, writes
+# WRITE_SIZE 1,310,736 KiB.  Valid only for the kernel sources it was
 # counted on; reported as null once they change.
-COUNTED_TRAFFIC = {"sources_sha256_prefix": "d24ddbf48a2f0125", "bytes_per_launch": 3130310656.0}
-TRAFFIC_SOURCES = ("fwd_kernels.hip", "dg_device.hpp", "dg_internal.hpp")
+COUNTED_TRAFFIC = {"sources_sha256_prefix": "b6862983a27cf09f", "bytes_per_launch": 3131094614.0}
+TRAFFIC_SOURCES = ("fwd_kernels.hip", "line_device.hpp", "line_kg_f64.hip", "dg_device.hpp", "dg_internal.hpp")
 # The same for k_rhs_curv<7,double,true,true,false> on the curved workload
 # (profiles/k_rhs_curv_k_face_flux_curv_tgv_n7_32x32x32_curved.md): reads
-# 128 x 35,124,061.3 RDREQ_128B + 64 x 1,876.9 RDREQ_64B, writes 1,310,738.8 KiB;
+# 128 x 31,045,503 RDREQ_128B + 64 x 5,286 RDREQ_64B, writes 1,310,721 KiB;
 # and for its mixed-precision instance k_rhs_curv<7,float,true,true,false>:
-# reads 128 x 27,055,205.1 RDREQ_128B + 64 x 4,193.1 RDREQ_64B, writes
-# 1,310,720.3 KiB.
-COUNTED_TRAFFIC_CURVED = {"sources_sha256_prefix": "f059d7093f7e0d5b", "bytes_per_launch": 5838196499.0}
-COUNTED_TRAFFIC_CURVED_MIXED = {"sources_sha256_prefix": "f059d7093f7e0d5b", "bytes_per_launch": 4805512198.0}
-TRAFFIC_SOURCES_CURVED = ("curv_kernels.hip", "dg_device.hpp", "dg_internal.hpp")
+# reads 128 x 30,714,656 RDREQ_128B + 64 x 11,096 RDREQ_64B, writes
+# 1,310,723 KiB.
+COUNTED_TRAFFIC_CURVED = {"sources_sha256_prefix": "220916735b940acc", "bytes_per_launch": 5316341687.0}
+COUNTED_TRAFFIC_CURVED_MIXED = {"sources_sha256_prefix": "220916735b940acc", "bytes_per_launch": 5274366843.0}
+TRAFFIC_SOURCES_CURVED = ("curv_line.hpp", "curv_flux.hpp", "line_device.hpp", "curv_kg_f64.hip", "curv_kg_f32.hip",
+                          "dg_device.hpp", "dg_internal.hpp")
 
 
 def counted_traffic(counted=COUNTED_TRAFFIC, sources=TRAFFIC_SOURCES):
@@ -656,7 +657,7 @@ def main():
         "repeats_ns_per_dof_stage": fp64["repeats_ns_per_dof_stage"],
         "roofline": {
             "bound": "hbm",
-            "kernel": "k_rhs (fused right-hand side + RK stage)",
+            "kernel": "k_rhs_line (fused right-hand side + RK stage)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

@@ -9,18 +9,18 @@
 //             the forward BR1 gradients of U (recomputed in LDS, as in the
 //             forward right-hand side), then
 //             gbar = cotangent of the lifted gradients (12 per node) and the
-//             part of Ubar that does not pass through the lifting:
-//               * volume split form: for each line pair (i, m),
-//                 Pbar_i += -2 s_d J1(P_i, P_m)^T (D_im lam_i + D_mi lam_m),
-//                 J1 = d f#(a, b) / d a of the symmetric two-point flux
-//                 (Kennedy-Gruber, or Chandrashekar's with its logarithmic
-//                 means differentiated on the branch the forward takes);
-//               * viscous volume term: Fvbar_d(m) = s_d sum_i D_im lam_i, then
-//                 the transpose of f_v,d(u, grad) -> (ubar, gbar);
+//             part of Ubar that does not pass through the lifting.  In the weak form
+//             (line_device.hpp), with Q = diag(w) D and l_i = s_d lam_i / w_i:
+//               * volume split form: for each line pair i < m, both nodes take
+//                 J1^T (-2 Q_im (l_i - l_m)), J1 = d f#(a, b) / d a of the symmetric
+//                 two-point flux (Kennedy-Gruber, or Chandrashekar's with its
+//                 logarithmic means differentiated on the branch the forward takes);
+//               * viscous volume term: Fvbar_d = -(weak derivative of l, the
+//                 neighbours' l as ghosts), then the transpose of
+//                 f_v,d(u, grad) -> (ubar, gbar);
 //               * each face node's numerical flux, which enters both sides'
-//                 equations, with the combined cotangent
-//                 phi = -(sc_o s_o lam_o + sc_n s_n lam_n)  (sc = +-1/w_end);
-//                 the own physical flux with -sc_o s_o lam_o;
+//                 equations, with the combined cotangent phi = -+(l_o - l_n) (the own
+//                 physical flux cancels with the diagonal of the volume sum);
 //               * the primitive map P(U) transposed.
 //   k_vjp_b : gbar (+ neighbour gbar at face nodes) -> qbar of q = (u, v, w, T)
 //             through the transposed BR1 lifting, then Ubar += (dq/dU)^T qbar.
@@ -355,6 +355,15 @@ __device__ inline const VjpArgs& again(VjpArgsPtr p) {
 // (entropy-conserving pair: beta in place of p), T, lam (5); raw gradients GR + 3 q + d;
 // viscous flux cotangents FV + 3 c + d.  At the end the lines' sums (6 per direction) take
 // the place of the latter two, the faces' primitive cotangents END that of T and lam.
+//
+// What bounds it (N = 5, 48 x 32 x 48 elements, Kennedy-Gruber pair: 1.46 ms; with one lane
+// per node 1.80): 3.1 GB of HBM traffic (0.49 ms for a triad), vector instructions issue
+// 47 % of the time (398 M wave instructions), LDS is busy 42 %, and the neighbours' values
+// at the line ends (20 loads per face lane, each of 64 addresses in as many cache
+// lines) hold up both.  Without the pairs it is 1.5 % faster, without the stores of
+// gbar 10 %.  A second load of the neighbours' lam by the line lanes cost 0.08 ms, three
+// workgroups per CU instead of two (24 fields, pairs in blocks) 0.13, workgroups that
+// loop over elements and fetch the next one early 0.2.
 template <int N>
 struct VjpShape {
   using L = Line<N>;

@@ -144,7 +144,9 @@ __global__ __launch_bounds__(CurvCfg<N>::BS) void k_metrics(const double* __rest
 //          face plane for one of u, v, w, T; the other wave(s): the remaining such lines;
 //   faces  a line lane, now lane of two face nodes: physical gradients, the two
 //          contravariant fluxes; its wave stores whole rows.
-// What bounds it: @@
+// What bounds it (N = 7, 32^3 elements, FP64; with one lane per boundary node 0.53 ms): 0.46
+// ms, 2.15 GB of HBM traffic (0.34 ms for a triad), vector instructions issue 34 % of the
+// time, LDS busy 33 %; four workgroups (40 KB LDS) per CU.
 // Mixed precision stores FP32 and computes in FP64 with the FP32 entries of Q, as the
 // axis-aligned kernel does and for its reason.
 template <int N>

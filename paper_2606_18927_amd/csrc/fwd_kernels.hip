@@ -49,13 +49,13 @@ __device__ inline const FaceArgs& again(FaceArgsPtr p) {
 //          two velocity components each;
 //   faces  a line lane, now lane of two face nodes, forms the two fluxes; its wave
 //          stores whole rows.
-// What bounds it (N = 7, 32^3 elements, FP64; 0.23 - 0.26 ms, with one lane per face
-// node that read three whole lines of four fields 0.31): HBM moves 0.81 GB (0.13 ms
-// at the rate of a triad), vector instructions issue 36 % of the time (51 M wave
-// instructions, before 92 M), LDS is busy 28 % (43 M cycles, before 79 M); the rest is
-// the latency of the two load - LDS - compute chains of the five workgroups (29 KB
-// LDS) of a CU.  The sums are settled before the barriers: sunk past them they need
-// 122 instead of 65 registers, and N = 5 runs 1.3x slower on half the waves.
+// What bounds it (N = 7, 32^3 elements, FP64; 0.27 ms, mixed 0.23 ms; with one lane per
+// face node that read three whole lines of four fields 0.31 and 0.28 ms): HBM moves
+// 1.26 GB (0.20 ms for a triad), vector instructions issue 34 % of the time (51 M wave
+// instructions, before 89 M), LDS is busy 28 % (43 M cycles, before 79 M); the rest is
+// the latency of the load - LDS - compute chains of the five workgroups (29 KB LDS) of a
+// CU.  The sums are settled before the barriers: sunk past them they need 122 instead
+// of 65 registers, and N = 5 runs 1.3x slower on half the waves.
 // Mixed precision stores FP32 and computes in FP64 (without packed instructions FP32
 // is no faster) with the FP32 entries of Q: the rounding of a row's entries is a
 // systematic error of a gradient (row sum times mean velocity), and the two

@@ -1,15 +1,19 @@
 // Right-hand side (and fused RK stage) with line lanes, for gfx950.
 //
-// What bounds it (N = 7, 32^3 elements; counters of the RK instance): vector
-// instructions issue 47 % of the time (225 M wave instructions, 163 M of them
-// FP64; with one lane per node and every node reading its lines from LDS the
-// same stage took 0.98 ms and its LDS was busy 55 % of the time, here 0.78 ms and
-// 25 %), HBM moves 3.4 GB; a CU holds two workgroups (74 KB LDS, 252 registers: the
-// whole line and its sums), so eight waves have to hide each other's LDS and
-// barrier latencies.
+// What bounds it (N = 7, 32^3 elements, RK instance, per launch; with one lane per
+// node and every node reading its lines from LDS in brackets):
+//                       time us        HBM GB   vector instr. 10^6   their issue   LDS busy
+//   FP64                783  (986)     3.13     224  (355)           50 %          27 % (55 %)
+//   mixed               662  (838)     2.93     260                  69 %          23 % (44 %)
+//   entropy-cons. FP64 1038 (1651)     3.13     357  (671)           68 %          22 % (36 %)
+//   entropy-cons. mixed 822 (1351)     2.93     388                  91 %          20 %
+// A triad moves 3.13 GB in 0.49 ms.  In FP64 a CU holds two workgroups (77 KB LDS, 246
+// registers: the whole line and its sums): eight waves have to hide each other's memory,
+// LDS and barrier latencies; the entropy-conserving pair is bound by its instructions.
+// (Workgroups that loop over elements and fetch the next one early: 4 - 7 % slower; two
+// lanes per line: twice as slow, only one workgroup of six waves fits a CU.)
 //
-// One workgroup works on one element at a time.  Two kinds of phases alternate,
-// with the nodal fields in LDS between them:
+// One workgroup works on one element.  Two kinds of phases alternate, with the nodal fields in LDS between them:
 //
 //   node phases  one lane per node: recover the primitives of U; lifted velocity
 //                gradients -> viscous fluxes; sum the three directions and write
@@ -76,6 +80,16 @@ struct Line {
   }
 };
 
+// Faces of a line that its face lane takes.  The Roe flux of one face is as long as
+// half a line's pairs are together, so with it the line lanes take the upper ones
+// themselves where the face waves would be the last: N = 7 has one face wave beside three
+// line waves (24^3 step 6.88 ms without, 6.03 with), N = 3 six pairs per line; N = 5 has as
+// many face waves as line waves.
+template <int N, bool EC>
+__host__ __device__ constexpr int line_faces() {
+  return EC && N != 5 ? 1 : 2;
+}
+
 // LDS fields (of EB values of type R) of a workgroup.  Halves of rho, u, v, w
 // (0..3); 4, 5: halves of p and e, entropy-conserving pair beta and |u|^2 / 4; with
 // it in mixed precision pi / 2; then T.  From GS on the raw velocity gradients
@@ -96,7 +110,10 @@ struct Fields {
   static constexpr int COUNT = MIXED ? 21 : 18;
   static constexpr int ENDS = COUNT * L::EB;
   static constexpr int GT = ENDS + (L::UNIFORM ? 0 : 16 * L::LINES);
-  static constexpr int MU = GT + 2 * L::LINES;
+  // (where the lane that forms them also reads them back, in registers: at N = 5 three
+  // workgroups with Sutherland's law fit a CU without the ghost temperatures in LDS)
+  static constexpr bool KEEP_T = !L::UNIFORM && line_faces<N, EC>() == 2;
+  static constexpr int MU = GT + (KEEP_T ? 0 : 2 * L::LINES);
   static constexpr int OWN = (L::UNIFORM ? GS + 6 : GS) * L::EB;  // 5 FP64 values per boundary node
   static constexpr int NB = n_face_nodes<N>();
   static_assert(!MIXED || OWN + 10 * NB <= (L::UNIFORM ? COUNT : GS + 9) * L::EB, "boundary states fit");
@@ -292,18 +309,12 @@ __device__ __forceinline__ void settle(R (&x)[A][B]) {
     for (int b = 0; b < B; ++b) asm volatile("" : "+v"(x[a][b]));
 }
 
-// Waves per SIMD the registers are bounded for: what LDS lets a CU hold.
+// Waves per SIMD the registers are bounded for: what LDS lets a CU hold (N = 7: 77 KB
+// in FP64, 45 KB mixed), or what the entropy-conserving pair needs without spilling
+// (N = 3 and 5 in FP64 spilled 40 - 90 values at one wave more).
 template <int N, typename R, bool EC>
 __host__ __device__ constexpr int line_waves() {
   return sizeof(R) == 8 ? (N == 7 ? 2 : (N == 5 ? (EC ? 2 : 3) : (EC ? 2 : 4))) : (N == 7 || EC ? 3 : 4);
-}
-
-// Faces of a line that its face lane takes.  The Roe flux is as long as a line's
-// pairs are together, so with it the line lanes take the upper ones themselves where
-// the face waves would be the last (N = 5 has as many face waves as line waves).
-template <int N, bool EC>
-__host__ __device__ constexpr int line_faces() {
-  return EC && N != 5 ? 1 : 2;
 }
 
 // A phase boundary: a workgroup barrier that no instruction is scheduled across
@@ -720,6 +731,7 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
   phase_end();
 
   // ---- line phase: flux differencing; faces (on the other wave(s)) ---------
+  R gt[2];  // ghost temperatures
   const auto face = [&](const LineTask<N>& t, int h, const double (&s)[5]) {
     R gv[3], gT, fs[5];
     face_values<N, R, EC>(again(args), sF, t, h, pl.neighbour(t.d, h) < 0, s, gv, gT, fs);
@@ -727,7 +739,10 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
     for (int k = 0; k < 3; ++k) sF[Fd::end_at(t.d, 8 * h + k, t.ab)] = gv[k];
 #pragma unroll
     for (int k = 0; k < 5; ++k) sF[Fd::end_at(t.d, 8 * h + 3 + k, t.ab)] = fs[k];
-    sF[Fd::GT + h * L::LINES + t.d * NF + t.ab] = gT;
+    if constexpr (Fd::KEEP_T)
+      gt[h] = gT;
+    else
+      sF[Fd::GT + h * L::LINES + t.d * NF + t.ab] = gT;
   };
   if constexpr (FACE) {
     const LineArgs& A = again(args);
@@ -994,8 +1009,10 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       R T[NP], g[NP];
 #pragma unroll
       for (int m = 0; m < NP; ++m) T[m] = sF[Fd::TS * EB + t.node(m)];
-      const int gt = Fd::GT + t.d * NF + t.ab;
-      line_derivative<N, R, MIXED>(A.basis, T, sF[gt], sF[gt + L::LINES], g);
+      if constexpr (!Fd::KEEP_T)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) gt[h] = sF[Fd::GT + h * L::LINES + t.d * NF + t.ab];
+      line_derivative<N, R, MIXED>(A.basis, T, gt[0], gt[1], g);
       const double sk = 0.5 * A.ph.kappa * (t.d == 0 ? pl.sx : (t.d == 1 ? pl.sy : pl.sz));
 #pragma unroll
       for (int m = 0; m < NP; ++m) g[m] *= static_cast<R>(sk * A.basis.inv_w[m]);
