@@ -51,9 +51,19 @@ struct CurvFields {
   static_assert(!MIXED || OWN + 10 * NB <= (GS + 12) * L::EB, "boundary states fit");
   static_assert(!MIXED || 20 * L::LINES <= COUNT * L::EB, "the faces' FP64 terms fit");
   static constexpr int HEAD = 16;  // FP64: 1 / w_i, then p_ref, e_ref, beta_ref, T_ref
-  static constexpr size_t BYTES = HEAD * sizeof(double) + sizeof(R) * static_cast<size_t>(GT + 2 * L::LINES);
-  static constexpr int BLOCK = N == 7 ? 4 : L::NP;  // nodes of a line held in registers
-  static constexpr int WAVES = MIXED ? 3 : (N == 3 && !EC ? 3 : 2);
+  // faces of a line that its face lane takes (line_faces; mixed precision holds their FP64 terms)
+  static constexpr int HF = line_faces<N, EC || (MIXED && N == 7)>();
+  // Ghost temperatures in the face lane's registers (as Fields), except where registers and
+  // not LDS bound the workgroups of a CU (N = 5 entropy-conserving in FP64: 3 % slower so).
+  static constexpr bool KEEP_T = !L::UNIFORM && HF == 2 && (MIXED || !EC);
+  static constexpr size_t BYTES =
+      HEAD * sizeof(double) + sizeof(R) * static_cast<size_t>(GT + (KEEP_T ? 0 : 2 * L::LINES));
+  // Nodes of a line held in registers, and the waves per SIMD that the registers are bounded
+  // for: what LDS lets a CU hold, unless the bound spills more than a few values.  N = 5 in
+  // FP64 fits a third workgroup with half lines (16^3 elements: 590 -> 535 us a step), mixed
+  // entropy-conserving a fourth (at 0.001 / 0.4 of the sound speed 616 -> 573, 1071 -> 1011 us).
+  static constexpr int BLOCK = N == 7 ? 4 : (N == 5 && !MIXED && !EC ? 3 : L::NP);
+  static constexpr int WAVES = MIXED ? (N == 7 || (N == 3 && EC) ? 3 : 4) : (N == 7 || EC ? 2 : (N == 5 ? 3 : 4));
   __device__ static int end_at(int d, int k, int ab) {
     return L::UNIFORM ? (GS + 3 * (k >> 3) + d) * L::EB + (k & 7) * L::NF + ab : ENDS + k * L::LINES + d * L::NF + ab;
   }
@@ -393,9 +403,10 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
   R* const sF = reinterpret_cast<R*>(head + Fd::HEAD);
   const Place pl(again(args).mesh, e, false);
   R eh[FL][NP];             // face lanes: the diffusive part of the lines' energy sums
-  constexpr int HF = line_faces<N, EC || (MIXED && N == 7)>(), FF = FACE ? FL : 1, H0 = FACE ? 0 : HF, H1 = FACE ? HF : 2;  // own faces
+  constexpr int HF = Fd::HF, FF = FACE ? FL : 1, H0 = FACE ? 0 : HF, H1 = FACE ? HF : 2;  // own faces
   double fe[FF][2][5];      // mixed precision: the faces' parts of the sums
   R acc[NV][NP];            // line lanes: sums of the line's nodes; mixed: [5] sum D U~
+  R gt[2];                  // ghost temperatures
   {
     const LineArgs& A = again(args);
     const long long stride = A.mesh.nE * NN;
@@ -484,7 +495,10 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
       if constexpr (!MIXED)
 #pragma unroll
         for (int k = 0; k < 5; ++k) sF[Fd::end_at(t.d, 8 * h + 3 + k, t.ab)] = fs[k];
-      sF[Fd::GT + h * LINES + t.d * NF + t.ab] = gT;
+      if constexpr (Fd::KEEP_T)
+        gt[h] = gT;
+      else
+        sF[Fd::GT + h * LINES + t.d * NF + t.ab] = gT;
     };
     if constexpr (FACE) {
       const LineArgs& B = again(args);
@@ -655,8 +669,10 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
       R T[NP], g[NP];
 #pragma unroll
       for (int m = 0; m < NP; ++m) T[m] = sF[Fd::TS * EB + t.node(m)];
-      const int gt = Fd::GT + t.d * NF + t.ab;
-      line_derivative<N, R, MIXED>(A.basis, T, sF[gt], sF[gt + LINES], g);
+      if constexpr (!Fd::KEEP_T)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) gt[h] = sF[Fd::GT + h * LINES + t.d * NF + t.ab];
+      line_derivative<N, R, MIXED>(A.basis, T, gt[0], gt[1], g);
 #pragma unroll
       for (int m = 0; m < NP; ++m) sF[(GS + 9 + t.d) * EB + t.node(m)] = g[m];
     }

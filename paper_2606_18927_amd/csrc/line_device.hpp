@@ -311,10 +311,13 @@ __device__ __forceinline__ void settle(R (&x)[A][B]) {
 
 // Waves per SIMD the registers are bounded for: what LDS lets a CU hold (N = 7: 77 KB
 // in FP64, 45 KB mixed), or what the entropy-conserving pair needs without spilling
-// (N = 3 and 5 in FP64 spilled 40 - 90 values at one wave more).
+// more than a few values (N = 5 in FP64 spilled 40 - 90 at one wave more).  With that
+// pair N = 3 in FP64 takes three waves and 10 spilled values before two and none
+// (48^3 elements: 6.25 -> 5.14 ms a step; rough states 8.81 -> 7.92), N = 5 mixed
+// four, which its registers just fit (32^3: 3.30 -> 3.13 ms; rough 6.11 -> 5.44).
 template <int N, typename R, bool EC>
 __host__ __device__ constexpr int line_waves() {
-  return sizeof(R) == 8 ? (N == 7 ? 2 : (N == 5 ? (EC ? 2 : 3) : (EC ? 2 : 4))) : (N == 7 || EC ? 3 : 4);
+  return sizeof(R) == 8 ? (N == 7 ? 2 : (N == 5 ? (EC ? 2 : 3) : (EC ? 3 : 4))) : (N == 7 ? 3 : 4);
 }
 
 // A phase boundary: a workgroup barrier that no instruction is scheduled across
