@@ -80,14 +80,14 @@ ALG_FLOPS_PER_DOF_STAGE = 940.0
 # FP64 flops per DOF and stage counted with rocprofv3 (SQ_INSTS_VALU_{ADD,MUL,
 # FMA,TRANS}_F64 x 64 lanes, FMA twice) on k_rhs_line + k_face_flux of this
 # workload; valid only for the kernel sources they were counted on.
-COUNTED_FLOPS = {"sources_sha256_prefix": "9931f4cc6be264b4", "per_dof_stage": 1014.750 + 151.375}
+COUNTED_FLOPS = {"sources_sha256_prefix": "11e01f93e423ea0a", "per_dof_stage": 1014.750 + 151.375}
 
 # HBM bytes per launch of k_rhs_line<7,double> on this workload, from rocprofv3
 # counter passes (profiles/k_rhs_k_face_flux_tgv_n7_32x32x32.md): reads
 # 128 x 13,973,355 TCC_EA0_RDREQ_128B + 64 x 4,858 RDREQ_64B, writes
 # WRITE_SIZE 1,310,736 KiB.  Valid only for the kernel sources it was
 # counted on; reported as null once they change.
-COUNTED_TRAFFIC = {"sources_sha256_prefix": "9931f4cc6be264b4", "bytes_per_launch": 3131094614.0}
+COUNTED_TRAFFIC = {"sources_sha256_prefix": "11e01f93e423ea0a", "bytes_per_launch": 3131094614.0}
 TRAFFIC_SOURCES = ("fwd_kernels.hip", "line_device.hpp", "line_kg_f64.hip", "dg_device.hpp", "dg_internal.hpp")
 # The same for k_rhs_curv<7,double,true,true,false> on the curved workload
 # (profiles/k_rhs_curv_k_face_flux_curv_tgv_n7_32x32x32_curved.md): reads
@@ -95,8 +95,8 @@ TRAFFIC_SOURCES = ("fwd_kernels.hip", "line_device.hpp", "line_kg_f64.hip", "dg_
 # and for its mixed-precision instance k_rhs_curv<7,float,true,true,false>:
 # reads 128 x 30,714,656 RDREQ_128B + 64 x 11,096 RDREQ_64B, writes
 # 1,310,723 KiB.
-COUNTED_TRAFFIC_CURVED = {"sources_sha256_prefix": "7b1e3d6adc41e21a", "bytes_per_launch": 5316341687.0}
-COUNTED_TRAFFIC_CURVED_MIXED = {"sources_sha256_prefix": "7b1e3d6adc41e21a", "bytes_per_launch": 5274366843.0}
+COUNTED_TRAFFIC_CURVED = {"sources_sha256_prefix": "09e4f3c9e51deef7", "bytes_per_launch": 5316341687.0}
+COUNTED_TRAFFIC_CURVED_MIXED = {"sources_sha256_prefix": "09e4f3c9e51deef7", "bytes_per_launch": 5274366843.0}
 TRAFFIC_SOURCES_CURVED = ("curv_line.hpp", "curv_flux.hpp", "line_device.hpp", "curv_kg_f64.hip", "curv_kg_f32.hip",
                           "dg_device.hpp", "dg_internal.hpp")
 

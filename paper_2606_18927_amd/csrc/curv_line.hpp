@@ -61,7 +61,8 @@ struct CurvFields {
   // Nodes of a line held in registers, and the waves per SIMD that the registers are bounded
   // for: what LDS lets a CU hold, unless the bound spills more than a few values.  N = 5 in
   // FP64 fits a third workgroup with half lines (16^3 elements: 590 -> 535 us a step), mixed
-  // entropy-conserving a fourth (at 0.001 / 0.4 of the sound speed 616 -> 573, 1071 -> 1011 us).
+  // entropy-conserving a fourth (density noise of 0.1 / 40 %: 616 -> 573, 1071 -> 1011 us).
+  // Entropy-conserving in FP64, N = 3 spills 38 for a third (24^3: 804 -> 755, 1347 -> 1495).
   static constexpr int BLOCK = N == 7 ? 4 : (N == 5 && !MIXED && !EC ? 3 : L::NP);
   static constexpr int WAVES = MIXED ? (N == 7 || (N == 3 && EC) ? 3 : 4) : (N == 7 || EC ? 2 : (N == 5 ? 3 : 4));
   __device__ static int end_at(int d, int k, int ab) {

@@ -311,9 +311,10 @@ __device__ __forceinline__ void settle(R (&x)[A][B]) {
 
 // Waves per SIMD the registers are bounded for: what LDS lets a CU hold (N = 7: 77 KB
 // in FP64, 45 KB mixed), or what the entropy-conserving pair needs without spilling
-// more than a few values (N = 5 in FP64 spilled 40 - 90 at one wave more).  With that
-// pair N = 3 in FP64 takes three waves and 10 spilled values before two and none
-// (48^3 elements: 6.25 -> 5.14 ms a step; rough states 8.81 -> 7.92), N = 5 mixed
+// more than a few values (N = 5 in FP64 spills 44 at one wave more: smooth states
+// 3.38 -> 3.10 ms a step at 32^3, rough ones, with spills inside the loop over pairs,
+// 9.08 -> 13.63).  With that pair N = 3 in FP64 takes three waves and 10 spilled values
+// before two and none (48^3: 6.25 -> 5.14 ms a step; rough 8.81 -> 7.92), N = 5 mixed
 // four, which its registers just fit (32^3: 3.30 -> 3.13 ms; rough 6.11 -> 5.44).
 template <int N, typename R, bool EC>
 __host__ __device__ constexpr int line_waves() {
