@@ -43,7 +43,7 @@ __device__ inline void roe_dissipation_normal(const double L[5], double EL, cons
   double ut[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) ut[c] = wl * L[1 + c] + wr * R[1 + c];
-  const double H = wl * (EL + L[4]) * iL + wr * (ER + R[4]) * iR;
+  const double H = quot(wl * (EL + L[4]), L[0], iL) + quot(wr * (ER + R[4]), R[0], iR);
   const double q2 = ut[0] * ut[0] + ut[1] * ut[1] + ut[2] * ut[2];
   const double a2 = (gamma - 1.0) * (H - 0.5 * q2);
   const double a = sqrt_nr(a2), ia2 = rcp_nr(a2);
@@ -54,11 +54,11 @@ __device__ inline void roe_dissipation_normal(const double L[5], double EL, cons
 #pragma unroll
   for (int c = 0; c < 3; ++c) du[c] = R[1 + c] - L[1 + c];
   const double dun = du[0] * n[0] + du[1] * n[1] + du[2] * n[2];
-  const double al1 = 0.5 * (dp - rho * a * dun) * ia2;
-  const double al5 = 0.5 * (dp + rho * a * dun) * ia2;
-  const double al2 = (R[0] - L[0]) - dp * ia2;
+  const double al1 = 0.5 * quot(dp - rho * a * dun, a2, ia2);
+  const double al5 = 0.5 * quot(dp + rho * a * dun, a2, ia2);
+  const double al2 = (R[0] - L[0]) - quot(dp, a2, ia2);
   const double unl = L[1] * n[0] + L[2] * n[1] + L[3] * n[2], unr = R[1] * n[0] + R[2] * n[1] + R[3] * n[2];
-  const double cl = sqrt_nr(gamma * L[4] * iL), cr = sqrt_nr(gamma * R[4] * iR);
+  const double cl = sqrt_nr(quot(gamma * L[4], L[0], iL)), cr = sqrt_nr(quot(gamma * R[4], R[0], iR));
   const double l1 = hh_abs(un - a, unl - cl, unr - cr);
   const double l5 = hh_abs(un + a, unl + cl, unr + cr);
   const double l2 = fabs(un);

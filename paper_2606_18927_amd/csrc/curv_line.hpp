@@ -327,7 +327,8 @@ __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const 
     for (int c = 0; c < 3; ++c) vo[c] = 2.0 * sF[(1 + c) * EB + l];
     q2o = vo[0] * vo[0] + vo[1] * vo[1] + vo[2] * vo[2];
     if (EC) {
-      po = 0.5 * so[0] * rcp_nr(sF[4 * EB + l]);
+      const double be = sF[4 * EB + l];
+      po = quot(0.5 * so[0], be, rcp_nr(be));
       so[4] = po / A.ph.gm1 + 0.5 * so[0] * q2o;
     } else {
       po = 2.0 * sF[4 * EB + l];
@@ -343,8 +344,8 @@ __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const 
   double F[5];
   const double smag2 = s[0] * s[0] + s[1] * s[1] + s[2] * s[2];
   if constexpr (EC) {
-    const double A6[6] = {so[0], vo[0], vo[1], vo[2], 0.5 * so[0] * rcp_nr(po), q2o};
-    const double B6[6] = {sn[0], vn[0], vn[1], vn[2], 0.5 * sn[0] * rcp_nr(pn), q2n};
+    const double A6[6] = {so[0], vo[0], vo[1], vo[2], quot(0.5 * so[0], po, rcp_nr(po)), q2o};
+    const double B6[6] = {sn[0], vn[0], vn[1], vn[2], quot(0.5 * sn[0], pn, rcp_nr(pn)), q2n};
     ec_flux_contra(A6, B6, s[0], s[1], s[2], A.ph.gm1, F);
     if (!A.ph.central) {
       const double smag = sqrt_nr(smag2), ism = rcp_nr(smag);
@@ -364,7 +365,8 @@ __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const 
   } else {
     const double rho = 0.5 * (so[0] + sn[0]), u = 0.5 * (vo[0] + vn[0]), v = 0.5 * (vo[1] + vn[1]), w = 0.5 * (vo[2] + vn[2]);
     const double p = 0.5 * (po + pn);
-    const double e = 0.5 * (so[4] * rcp_nr(so[0]) + sn[4] * irn);
+    const double iro = rcp_nr(so[0]);
+    const double e = 0.5 * (so[4] * iro + sn[4] * irn);
     const double U = u * s[0] + v * s[1] + w * s[2], m = rho * U;
     F[0] = m;
     F[1] = m * u + p * s[0];
@@ -372,9 +374,9 @@ __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const 
     F[3] = m * w + p * s[2];
     F[4] = m * e + p * U;
     if (!A.ph.central) {
-      const double smag = sqrt_nr(smag2), gR = A.ph.gamma * A.ph.R;
-      const double lo = fabs(vo[0] * s[0] + vo[1] * s[1] + vo[2] * s[2]) + sqrt_nr(gR * To) * smag;
-      const double ln = fabs(vn[0] * s[0] + vn[1] * s[1] + vn[2] * s[2]) + sqrt_nr(gR * Tn) * smag;
+      const double smag = sqrt_nr(smag2), go = A.ph.gamma * po, gn = A.ph.gamma * pn;
+      const double lo = fabs(vo[0] * s[0] + vo[1] * s[1] + vo[2] * s[2]) + sqrt_nr(quot(go, so[0], iro)) * smag;
+      const double ln = fabs(vn[0] * s[0] + vn[1] * s[1] + vn[2] * s[2]) + sqrt_nr(quot(gn, sn[0], irn)) * smag;
       const double hl = (h ? 0.5 : -0.5) * (lo >= ln ? lo : ln);
 #pragma unroll
       for (int c = 0; c < 5; ++c) F[c] -= hl * (sn[c] - so[c]);
@@ -470,7 +472,7 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
         sF[3 * EB + l] = static_cast<R>(0.5 * vz);
         if (EC) {
           const double ip = rcp_nr(p);
-          sF[4 * EB + l] = static_cast<R>(0.5 * s[0] * ip - beta_ref);
+          sF[4 * EB + l] = static_cast<R>((MIXED ? 0.5 * s[0] * ip : quot(0.5 * s[0], p, ip)) - beta_ref);
           sF[5 * EB + l] = static_cast<R>(0.25 * q2);
           if (MIXED) sF[6 * EB + l] = static_cast<R>(0.5 * (s[0] * (p - p_ref) * ip));
         } else {

@@ -251,6 +251,14 @@ __device__ inline double rcp_nr(double x) {
   return fma(r, e, r);
 }
 
+// a / b from r = rcp_nr(b): the product corrected by its remainder, which the plain
+// product's second rounding would leave in (measured in 80-bit floats: with p = rho rcp(2
+// beta) the Roe flux's pressure jump carried twice the rounding of a division).
+__device__ inline double quot(double a, double b, double r) {
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+
 // sqrt(x) for x > 0 of moderate size: the hardware estimate of 1 / sqrt(x) and
 // one coupled and one residual Newton step.
 __device__ inline double sqrt_nr(double x) {
@@ -290,7 +298,8 @@ __device__ inline void ec_means(double ra, double rb, double ba, double bb, doub
 __device__ inline double hh_abs(double lam, double lam_L, double lam_R) {
   double delta = fmax(lam - lam_L, lam_R - lam);
   delta = delta > 0.0 ? delta : 0.0;
-  return fabs(lam) < delta ? (lam * lam + delta * delta) * (0.5 * rcp_nr(delta)) : fabs(lam);
+  const double b = delta + delta;
+  return fabs(lam) < delta ? quot(lam * lam + delta * delta, b, rcp_nr(b)) : fabs(lam);
 }
 
 // Viscous flux along d: g[3 q + b] = d q / d x_b for q in (u, v, w, T);

@@ -372,7 +372,7 @@ __device__ __forceinline__ void primitives_to_lds(const LineArgs& A, double* con
       sF[3 * EB + l] = static_cast<R>(0.5 * vz);
       if (EC) {
         const double ip = rcp_nr(p);
-        sF[4 * EB + l] = static_cast<R>(0.5 * s[0] * ip - beta_ref);
+        sF[4 * EB + l] = static_cast<R>((MIXED ? 0.5 * s[0] * ip : quot(0.5 * s[0], p, ip)) - beta_ref);
         sF[5 * EB + l] = static_cast<R>(0.25 * q2);
         if (MIXED) sF[6 * EB + l] = static_cast<R>(0.5 * (s[0] * (p - p_ref) * ip));
       } else {
@@ -405,16 +405,16 @@ __device__ inline void roe_line(const double (&Lp)[5], double EL, const double (
   const double wl = sl * isum, wr = sr * isum;
   const double iL = rcp_nr(Lp[0]), iR = rcp_nr(Rp[0]);
   const double u = wl * Lp[1] + wr * Rp[1], v = wl * Lp[2] + wr * Rp[2], w = wl * Lp[3] + wr * Rp[3];
-  const double H = wl * (EL + Lp[4]) * iL + wr * (ER + Rp[4]) * iR;
+  const double H = quot(wl * (EL + Lp[4]), Lp[0], iL) + quot(wr * (ER + Rp[4]), Rp[0], iR);
   const double q2 = u * u + v * v + w * w;
   const double a2 = (gamma - 1.0) * (H - 0.5 * q2);
   const double a = sqrt_nr(a2), ia2 = rcp_nr(a2);
   const double rho = sl * sr;
   const double dp = Rp[4] - Lp[4], du = Rp[1] - Lp[1], dv = Rp[2] - Lp[2], dw = Rp[3] - Lp[3];
-  const double al1 = 0.5 * (dp - rho * a * du) * ia2;
-  const double al5 = 0.5 * (dp + rho * a * du) * ia2;
-  const double al2 = (Rp[0] - Lp[0]) - dp * ia2;
-  const double cl = sqrt_nr(gamma * Lp[4] * iL), cr = sqrt_nr(gamma * Rp[4] * iR);
+  const double al1 = 0.5 * quot(dp - rho * a * du, a2, ia2);
+  const double al5 = 0.5 * quot(dp + rho * a * du, a2, ia2);
+  const double al2 = (Rp[0] - Lp[0]) - quot(dp, a2, ia2);
+  const double cl = sqrt_nr(quot(gamma * Lp[4], Lp[0], iL)), cr = sqrt_nr(quot(gamma * Rp[4], Rp[0], iR));
   const double l1 = hh_abs(u - a, Lp[1] - cl, Rp[1] - cr);
   const double l5 = hh_abs(u + a, Lp[1] + cl, Rp[1] + cr);
   const double l2 = fabs(u);
@@ -521,9 +521,9 @@ __device__ __forceinline__ void face_values(const LineArgs& A, const R* sF, cons
     const double sg = h ? 0.5 : -0.5;
     if constexpr (EC) {
       const double pl = sF[t.first] * rcp_nr(sF[4 * EB + t.first]);
-      const double po = ro * rcp_nr(f4), r2 = ro + ro, q2o = 4.0 * f5;
+      const double po = quot(ro, f4, rcp_nr(f4)), r2 = ro + ro, q2o = 4.0 * f5;
       const double a[4] = {r2, vo[0] + vo[0], vo[1] + vo[1], vo[2] + vo[2]};
-      const double bn = 0.5 * sn[0] * rcp_nr(pn);
+      const double bn = quot(0.5 * sn[0], pn, rcp_nr(pn));
       const double b[4] = {wall ? r2 : sn[0], gv[0] + gv[0], gv[1] + gv[1], gv[2] + gv[2]};
       double f[5];
       ec_pair(a, f4, q2o, b, wall ? f4 : bn, wall ? q2o : q2n, A.ph.gm1, pl, f);
@@ -543,8 +543,8 @@ __device__ __forceinline__ void face_values(const LineArgs& A, const R* sF, cons
       for (int v = 0; v < 5; ++v) fs[v] = sg * (wall ? f[v] : f[v] - 0.5 * D[v]);
     } else {
       const double ph0 = sF[4 * EB + t.first];
-      const double gR = A.ph.gamma * A.ph.R;
-      const double so = fabs(vo[0] + vo[0]) + sqrt_nr(gR * T), s1 = fabs(vn[0]) + sqrt_nr(gR * Tn), r2 = ro + ro;
+      const double r2 = ro + ro, g2 = A.ph.gamma * (f4 + f4), gn = A.ph.gamma * pn;
+      const double so = fabs(vo[0] + vo[0]) + sqrt_nr(quot(g2, r2, rcp_nr(r2))), s1 = fabs(vn[0]) + sqrt_nr(quot(gn, sn[0], irn));
       const double lam = wall || A.ph.central ? 0.0 : 0.25 * (so >= s1 ? so : s1);
       const double rm = ro + (wall ? ro : 0.5 * sn[0]), un = vo[0] + gv[0], m = rm * un;
       const double pm = (f4 - ph0) + ((wall ? f4 : 0.5 * pn) - ph0), em = f5 + (wall ? f5 : 0.5 * (sn[4] * irn));
@@ -575,7 +575,7 @@ __device__ __forceinline__ void face_values(const LineArgs& A, const R* sF, cons
       const double fo[5] = {so[1], so[1] * vo[0] + po, so[1] * vo[1], so[1] * vo[2], (so[4] + po) * vo[0]};
       const double a4[4] = {so[0], vo[0], vo[1], vo[2]}, b4[4] = {sn[0], vn[0], vn[1], vn[2]};
       double f[5], D[5] = {0, 0, 0, 0, 0};
-      ec_pair(a4, 0.5 * so[0] * rcp_nr(po), q2o, b4, 0.5 * sn[0] * rcp_nr(pn), q2n, A.ph.gm1, 0.0, f);
+      ec_pair(a4, quot(0.5 * so[0], po, rcp_nr(po)), q2o, b4, quot(0.5 * sn[0], pn, rcp_nr(pn)), q2n, A.ph.gm1, 0.0, f);
       if (!A.ph.central) {
         const double Po[5] = {so[0], vo[0], vo[1], vo[2], po}, Pn[5] = {sn[0], vn[0], vn[1], vn[2], pn};
         double X[5], Y[5];
