@@ -375,8 +375,8 @@ __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const 
     F[4] = m * e + p * U;
     if (!A.ph.central) {
       const double smag = sqrt_nr(smag2), go = A.ph.gamma * po, gn = A.ph.gamma * pn;
-      const double lo = fabs(vo[0] * s[0] + vo[1] * s[1] + vo[2] * s[2]) + sqrt_nr(quot(go, so[0], iro)) * smag;
-      const double ln = fabs(vn[0] * s[0] + vn[1] * s[1] + vn[2] * s[2]) + sqrt_nr(quot(gn, sn[0], irn)) * smag;
+      const double lo = fabs(vo[0] * s[0] + vo[1] * s[1] + vo[2] * s[2]) + sqrt_edge(quot(go, so[0], iro)) * smag;
+      const double ln = fabs(vn[0] * s[0] + vn[1] * s[1] + vn[2] * s[2]) + sqrt_edge(quot(gn, sn[0], irn)) * smag;
       const double hl = (h ? 0.5 : -0.5) * (lo >= ln ? lo : ln);
 #pragma unroll
       for (int c = 0; c < 5; ++c) F[c] -= hl * (sn[c] - so[c]);

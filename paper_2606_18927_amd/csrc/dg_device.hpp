@@ -270,6 +270,14 @@ __device__ inline double sqrt_nr(double x) {
   return fma(fma(-g, g, x), h, g);
 }
 
+// The same where x may be zero or infinite, which are their own roots (the steps meet
+// 0 times infinity there): the sound speed of a state without pressure.
+__device__ inline double sqrt_edge(double x) {
+  constexpr int ZERO = 0x60, INFINITE = 0x200;  // class bits: -0 and +0, +infinity
+  const double r = sqrt_nr(x);
+  return __builtin_amdgcn_class(x, ZERO | INFINITE) ? x : r;
+}
+
 // Means of the entropy-conserving flux for one pair: rho_ln and 1 / beta_ln
 // (logarithmic means) and p^ = {{rho}} / (2 {{beta}}).  The logarithmic mean of
 // positive a, b is (a - b) / (ln a - ln b) = (a + b) / (2 F), F = atanh(f) / f,

@@ -544,7 +544,7 @@ __device__ __forceinline__ void face_values(const LineArgs& A, const R* sF, cons
     } else {
       const double ph0 = sF[4 * EB + t.first];
       const double r2 = ro + ro, g2 = A.ph.gamma * (f4 + f4), gn = A.ph.gamma * pn;
-      const double so = fabs(vo[0] + vo[0]) + sqrt_nr(quot(g2, r2, rcp_nr(r2))), s1 = fabs(vn[0]) + sqrt_nr(quot(gn, sn[0], irn));
+      const double so = fabs(vo[0] + vo[0]) + sqrt_edge(quot(g2, r2, rcp_nr(r2))), s1 = fabs(vn[0]) + sqrt_edge(quot(gn, sn[0], irn));
       const double lam = wall || A.ph.central ? 0.0 : 0.25 * (so >= s1 ? so : s1);
       const double rm = ro + (wall ? ro : 0.5 * sn[0]), un = vo[0] + gv[0], m = rm * un;
       const double pm = (f4 - ph0) + ((wall ? f4 : 0.5 * pn) - ph0), em = f5 + (wall ? f5 : 0.5 * (sn[4] * irn));

@@ -277,3 +277,34 @@ def test_full_size_conservation_over_run(big):
         scale = (wq * np.abs(U[v])).sum()
         say("integral", v, i0, i1)
         assert abs(i1 - i0) < 1e-12 * scale
+
+
+@pytest.mark.parametrize("N", [3, 5, 7])
+@pytest.mark.parametrize("curved", [False, True])
+def test_nodes_without_pressure(N, curved):
+    """A state whose pressure vanishes at some nodes is reported, and its sound speed there
+    is 0, not NaN: the right-hand side is the oracle's (same criterion)."""
+    from oracle import curvilinear as cv
+    from oracle.physics import Gas
+    need_gpu()
+    say("no pressure", N, curved)
+    n, rng = (2, 3, 2), np.random.default_rng(11 * N)
+    g = Gas(gamma=1.4, R=1.0, mu=0.01, Pr=0.72)
+    if curved:
+        X = workloads.warped_nodes(dgsem.lgl(N)[0], n, amp=0.05)
+        mesh, spec = cv.CurvMesh(N, torch.as_tensor(X)), dgsem.MeshSpec(N, None, ("periodic",) * 3, 1.0, nodes=X)
+    else:
+        faces = tuple(random_faces(n[d], 0.0, 2.0 + d, rng) for d in range(3))
+        mesh, spec = Mesh(N, faces), dgsem.MeshSpec(N, faces, ("periodic",) * 3, 1.0)
+    U = random_state(mesh, g.gamma, g.R, rng)
+    bare = torch.as_tensor(rng.random(tuple(U.shape[1:])) < 0.2)
+    for v in range(1, 5):
+        U[v][bare] = 0.0
+    ref = (cv.rhs if curved else rhs)(U, mesh, g).numpy()
+    assert np.all(np.isfinite(ref))
+    S = dgsem.Solver(spec, g.gamma, g.R, g.mu, g.Pr)
+    got = S.eval_rhs(to_dev(U.numpy())).cpu().numpy()
+    with pytest.raises(dgsem.DgsemError) as ei:
+        S.sync()
+    assert ei.value.status == dgsem.DG_ENONPHYS
+    assert np.all(rel_l2(got, ref) < TOL)
