@@ -70,6 +70,11 @@ struct CurvFields {
   }
 };
 
+template <typename R>
+struct FaceReads {  // (fetch_face)
+  static constexpr int COUNT = sizeof(R) == 8 ? 11 : 8;
+};
+
 // Metric component c at node idx in the sweep precision: FP64 or its FP32 copy, stored
 // after the ten FP64 fields.
 template <typename R>
@@ -261,10 +266,11 @@ __device__ inline void curv_rows(const LineArgs& A, const R* sF, const double* h
   }
 }
 
-// What a face lane reads of one face: the neighbour's state and the face normal.
+// What a face lane reads of one face: the neighbour's state, the face normal and (FP64, on a
+// lower face; on an upper one it is the face normal) the own metric vector there.
 template <int N, typename R>
 __device__ __forceinline__ void fetch_face(const LineArgs& A, long long stride, const Place& pl, int e, const LineTask<N>& t,
-                                           int h, double (&s)[8]) {
+                                           int h, double (&s)[FaceReads<R>::COUNT]) {
   const int nb = pl.neighbour(t.d, h);
   const unsigned on = t.end_node(h ? N : 0), nn = t.end_node(h ? 0 : N);
   const double* p = A.U + static_cast<long long>(nb >= 0 ? nb : e) * Line<N>::NN;
@@ -286,14 +292,23 @@ __device__ __forceinline__ void fetch_face(const LineArgs& A, long long stride, 
     const double* g = A.mesh.geo + ge * Line<N>::NN;
 #pragma unroll
     for (int c = 0; c < 3; ++c) s[5 + c] = (g + (3 * t.d + c) * stride)[gn];
+    if (h == 0) {
+      const double* go = A.mesh.geo + static_cast<long long>(e) * Line<N>::NN;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) s[8 + c] = (go + (3 * t.d + c) * stride)[on];
+    }
   }
 }
 
 // One face node: the ghost velocities (halves) and temperature, and -+ half the surface
 // flux; mixed precision: the jumps to them, and -+ half (surface flux - own flux).
+// The weak form drops the own flux with the own metric vector M, where the strong form
+// has it with the face normal s on both sides.  The two differ by the rounding of the two
+// elements' metric terms, but the flux holds the pressure: f(M - s) is added (without it the
+// momentum's rounding error at Ma = 0.1 is 5, 17 and 21 times larger at N = 3, 5, 7).
 template <int N, typename R, bool EC>
 __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const LineTask<N>& t, int h, bool wall,
-                                          const double (&sn)[8], R (&gv)[3], R& gT, double (&fs)[5]) {
+                                          const double (&sn)[FaceReads<R>::COUNT], R (&gv)[3], R& gT, double (&fs)[5]) {
   using L = Line<N>;
   using Fd = CurvFields<N, R, EC>;
   constexpr int EB = L::EB;
@@ -388,7 +403,14 @@ __device__ __forceinline__ void curv_face(const LineArgs& A, const R* sF, const 
   for (int v = 0; v < 5; ++v) {
     const double ps = v >= 1 && v <= 3 ? po * s[v - 1] : (v == 4 ? po * Uo : 0.0);
     const double wf = v >= 1 && v <= 3 ? ps : 0.0;  // impermeable wall: the interior pressure only
-    const double own = Fd::MIXED ? so[v] * Uo + ps : 0.0;
+    double own = 0.0;
+    if constexpr (Fd::MIXED) {
+      own = so[v] * Uo + ps;
+    } else if (h == 0) {
+      const double m[3] = {s[0] - sn[8], s[1] - sn[9], s[2] - sn[10]};
+      const double Um = vo[0] * m[0] + vo[1] * m[1] + vo[2] * m[2];
+      own = so[v] * Um + (v >= 1 && v <= 3 ? po * m[v - 1] : (v == 4 ? po * Um : 0.0));
+    }
     fs[v] = sg * ((wall ? wf : F[v]) - own);
   }
 }
@@ -413,7 +435,7 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
   {
     const LineArgs& A = again(args);
     const long long stride = A.mesh.nE * NN;
-    double u[ROUNDS][5], sn[EC ? 1 : FL][2][8];  // (entropy-conserving pair: the first line's)
+    double u[ROUNDS][5], sn[EC ? 1 : FL][2][FaceReads<R>::COUNT];  // (entropy-conserving pair: the first line's)
     R M[NP][3];
     fetch_nodes<N>(A.U, stride, e, tid, u);
     if constexpr (FACE) {
@@ -490,7 +512,7 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
     phase_end();
 
     // ---- line phase: flux differencing; faces (on the other wave(s)) -----------
-    const auto face = [&](const LineTask<N>& t, int h, const double (&s)[8], double (&fs)[5]) {
+    const auto face = [&](const LineTask<N>& t, int h, const double (&s)[FaceReads<R>::COUNT], double (&fs)[5]) {
       R gv[3], gT;
       curv_face<N, R, EC>(again(args), sF, t, h, pl.neighbour(t.d, h) < 0, s, gv, gT, fs);
 #pragma unroll
@@ -510,11 +532,11 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
         // one line after the other (the Roe flux is long), the next one's values in
         // flight meanwhile
         const long long st = B.mesh.nE * NN;
-        double cur[HF][8], nxt[HF][8], fs[HF][5];
+        double cur[HF][FaceReads<R>::COUNT], nxt[HF][FaceReads<R>::COUNT], fs[HF][5];
 #pragma unroll
         for (int h = 0; h < HF; ++h)
 #pragma unroll
-          for (int v = 0; v < 8; ++v) cur[h][v] = sn[0][h][v];
+          for (int v = 0; v < FaceReads<R>::COUNT; ++v) cur[h][v] = sn[0][h][v];
 #pragma unroll 1
         for (int q = 0; q < FL; ++q) {
           const LineTask<N> t = face_line<N>(lane, q), tn = face_line<N>(lane, q + 1 < FL ? q + 1 : q);
@@ -537,7 +559,7 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
 #pragma unroll
             for (int h = 0; h < HF; ++h)
 #pragma unroll
-              for (int v = 0; v < 8; ++v) cur[h][v] = nxt[h][v];
+              for (int v = 0; v < FaceReads<R>::COUNT; ++v) cur[h][v] = nxt[h][v];
         }
       } else {
 #pragma unroll
