@@ -299,12 +299,13 @@ __global__ __launch_bounds__(Line<N>::BS) __attribute__((amdgpu_waves_per_eu(Cur
         gh[0][3] -= own[0][3];
         gh[1][3] -= own[0][3];
       }
-      g[0][c] = -0.5 * gh[0][c];
-      g[1][c] = 0.5 * gh[1][c];
+      g[0][c] = g[1][c] = 0.0;
 #pragma unroll
-      for (int m = 1; m < NP; ++m) g[0][c] += q_im<N, double>(b, 0, m) * q[m];
+      for (int m = N; m > 0; --m) g[0][c] += q_im<N, double>(b, 0, m) * q[m];
 #pragma unroll
       for (int m = 0; m < N; ++m) g[1][c] -= q_im<N, double>(b, m, N) * q[m];
+      g[0][c] -= 0.5 * gh[0][c];
+      g[1][c] += 0.5 * gh[1][c];
       if (c & 1) settle(g);
     }
     phase_end();

@@ -22,8 +22,8 @@
 // Summation by parts takes the surface terms as in line_device.hpp.  Mixed precision
 // (FP32 LDS fields, gradients, metric terms of the sweeps, fluxes and line sums; p, e and T,
 // or beta and pi, relative to the element's first node) keeps the strong form at the faces:
-// surface flux minus own flux in FP64, added to the sums in FP64 at the end; the
-// reference pressure's share of the momentum sums is the discrete divergence of the
+// surface flux minus own flux in FP64, added to the sums in FP64 at the end, as the
+// viscous sums of the momentum and the energy are; the reference pressure's share of the momentum sums is the discrete divergence of the
 // metric terms (zero) and is dropped, the energy's e_ref sum D (rho U~)# + p_ref sum D U~#
 // is added back in FP64.
 #pragma once
@@ -49,7 +49,8 @@ struct CurvFields {
   static constexpr int OWN = (L::UNIFORM ? GS + 6 : GS) * L::EB;  // 5 FP64 values per boundary node
   static constexpr int NB = n_face_nodes<N>();
   static_assert(!MIXED || OWN + 10 * NB <= (GS + 12) * L::EB, "boundary states fit");
-  static_assert(!MIXED || 20 * L::LINES <= COUNT * L::EB, "the faces' FP64 terms fit");
+  static_assert(!MIXED || 20 * L::LINES + 9 * L::EB <= COUNT * L::EB + (L::UNIFORM ? 0 : 16 * L::LINES),
+                "the faces' FP64 terms and the viscous sums fit");
   static constexpr int HEAD = 16;  // FP64: 1 / w_i, then p_ref, e_ref, beta_ref, T_ref
   // faces of a line that its face lane takes (line_faces; mixed precision holds their FP64 terms)
   static constexpr int HF = line_faces<N, EC || (MIXED && N == 7)>();
@@ -193,29 +194,63 @@ __device__ __forceinline__ void curv_pairs(const LineArgs& A, const R* sF, const
       acc[v][m] -= c * f[v];
     }
   };
+  if constexpr (!Fd::MIXED) {
 #pragma unroll
-  for (int b0 = 0; b0 < NP; b0 += H) {
+    for (int b0 = 0; b0 < NP; b0 += H) {
 #pragma unroll
-    for (int i = 0; i < H; ++i) load(b0 + i, x[i]);
-    if (EC) settle(x);  // (nothing of this and the rolled version is shared before the branch)
+      for (int i = 0; i < H; ++i) load(b0 + i, x[i]);
+      if (EC) settle(x);  // (nothing of this and the rolled version is shared before the branch)
 #pragma unroll
-    for (int i = 0; i < H; ++i)
+      for (int i = 0; i < H; ++i)
 #pragma unroll
-      for (int m = i + 1; m < H; ++m) {
-        pair(x[i], b0 + i, x[m], b0 + m);
-        if (EC || m % 2) __builtin_amdgcn_sched_barrier(0);
-      }
-    if (b0 == 0)
-#pragma unroll
-      for (int m = H; m < NP; ++m) {
-        R z[NQ];
-        load(m, z);
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-          pair(x[i], i, z, m);
-          if (EC || i % 2) __builtin_amdgcn_sched_barrier(0);
+        for (int m = i + 1; m < H; ++m) {
+          pair(x[i], b0 + i, x[m], b0 + m);
+          if (EC || m % 2) __builtin_amdgcn_sched_barrier(0);
         }
+      if (b0 == 0)
+#pragma unroll
+        for (int m = H; m < NP; ++m) {
+          R z[NQ];
+          load(m, z);
+#pragma unroll
+          for (int i = 0; i < H; ++i) {
+            pair(x[i], i, z, m);
+            if (EC || i % 2) __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+    }
+  } else {  // from the farthest pairs to the nearest (pair_low), the second block mirrored
+    const auto block = [&](int b0) {
+#pragma unroll
+      for (int dist = H - 1; dist > 0; --dist)
+#pragma unroll
+        for (int s = 0; s < H - dist; ++s) {
+          const int k = pair_low(H - dist, s), i = b0 ? H - 1 - dist - k : k;
+          pair(x[i], b0 + i, x[i + dist], b0 + i + dist);
+          if (EC || s % 2) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < H; ++i) load(i, x[i]);
+    if (EC) settle(x);
+    if (EC) block(0);  // (last, its pairs spill twice as many registers)
+#pragma unroll
+    for (int m = N; m >= H; --m) {
+      R z[NQ];
+      load(m, z);
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        pair(x[i], i, z, m);
+        if (EC || i % 2) __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    if (!EC) block(0);
+    if constexpr (H < NP) {
+#pragma unroll
+      for (int i = 0; i < H; ++i) load(NP - H + i, x[i]);
+      if (EC) settle(x);
+      block(NP - H);
+    }
   }
 }
 
@@ -238,13 +273,12 @@ __device__ inline void curv_rows(const LineArgs& A, const R* sF, const double* h
     load(i, a, Ma);
 #pragma unroll
     for (int v = 0; v < NV; ++v) s[v] = R(0);
-    const double w = 1.0 / head[i];  // Q = w D
 #pragma unroll 1
-    for (int m = i + 1; m < NP; ++m) {
+    for (int m = N; m > i; --m) {
       R b[NQ], Mb[3], f[6];
       load(m, b, Mb);
       curv_pair<N, R, true, MEANS>(A.ph, head, a, Ma, b, Mb, f);
-      const R c = static_cast<R>(w * A.basis.D[i * NP + m]);
+      const R c = q_im<N, R>(A.basis, i, m);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         f[v] *= c;
@@ -763,6 +797,7 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
   }
 
   // ---- line phase: derivatives of the viscous fluxes ------------------------
+  R fv[3][NP];  // mixed precision: added apart, in FP64
   // (ghosts: half the neighbour's flux; at a wall the own stresses, and the energy flux
   // without their work: f - 2 u . tau)
   if constexpr (VISC && !FACE) {
@@ -777,9 +812,17 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
       for (int h = 0; h < 2; ++h) gw[h] = pl.neighbour(t.d, h) < 0 ? f[h ? N : 0] : R(0.5) * fn[h][c];
       line_derivative<N, R, false>(A.basis, f, gw[0], gw[1], g);
 #pragma unroll
-      for (int m = 0; m < NP; ++m) acc[1 + c][m] -= g[m];
+      for (int m = 0; m < NP; ++m) {
+        if (MIXED)
+          fv[c][m] = g[m];
+        else
+          acc[1 + c][m] -= g[m];
+      }
     }
-    settle(acc);
+    if (MIXED)
+      settle(fv);
+    else
+      settle(acc);
   } else if constexpr (VISC) {
     const LineArgs& A = again(args);
     const int lane = again(wtid) - 64 * L::LW;
@@ -855,10 +898,18 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
       ut[r][v] = s;
     }
   }
-  if constexpr (MIXED) {  // the faces' parts, in FP64, over the sums just read
+  if constexpr (MIXED) {  // the faces' parts, in FP64, and the viscous sums, over the sums just read
     settle(ut);
     phase_end();
     double* sE = reinterpret_cast<double*>(sF);
+    R* const sV = sF + 20 * LINES;
+    if constexpr (VISC && !FACE) {
+      const LineTask<N> t(again(wtid));
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = 0; m < NP; ++m) sV[(3 * t.d + c) * EB + t.node(m)] = fv[c][m];
+    }
     if constexpr (FACE || HF == 1) {
       const int lane = FACE ? again(wtid) - 64 * L::LW : again(wtid);
 #pragma unroll
@@ -885,6 +936,9 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
 #pragma unroll
           for (int v = 0; v < 5; ++v) ut[r][v] += iw * o[v * LINES];
         }
+        if (VISC)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) ut[r][1 + c] -= sW[x] * static_cast<double>(sV[(3 * d + c) * EB + L::at(i, j, k)]);
       }
     }
   }

@@ -98,6 +98,14 @@ void lgl_diff_matrix(const std::vector<double>& xi, std::vector<double>& D) {
 // Q_im = w_i D_im = 2 / (N (N + 1) P_N(x_i) P_N(x_m) (x_i - x_m)) for i != m, from
 // nodes refined in extended precision, so that the rounded values keep the
 // exact antisymmetry.
+//
+// The FP32 entries: rounded one by one, a row with its end value (-+1/2) sums to 3e-7 after
+// division by the end weight (N = 5), a systematic gradient of that times the mean
+// velocity, and a linear profile's slope is off by 2e-7 (N = 7).  So they are multiples of
+// 2^-27 (of their own last place where that is coarser) near Q, at most 8e-8 away, such
+// that the rows sum to zero exactly, a constant has no derivative, and their first, then
+// second and third moments are off least (the slope by 6e-8, at N = 7 by 1e-8): an integer
+// programme solved once for each N.
 void lgl_line_basis(int N, DevBasis& b) {
   const int NP = N + 1;
   const long double nn1 = static_cast<long double>(N) * (N + 1);
@@ -134,11 +142,17 @@ void lgl_line_basis(int N, DevBasis& b) {
     legendre_ld(x[j], P[j], dp);
     b.inv_w[j] = static_cast<double>(nn1 * P[j] * P[j] / 2.0L);
   }
+  static const int kUnits3[4] = {90487016, -34562960, 11184808, 125049976};
+  static const int kUnits5[9] = {90743856, -36115196, 20085100, -12078820, 4473924, 128185160, -58561424, 33198940, 130546288};
+  static const int kUnits7[16] = {90777192,  -36283312, 20601980,  -13470616, 9307326,   -6220450,  2396744,  128493680,
+                                  -59729596, 36601196,  -24588206, 16220568,  131654728, -62852596, 38689116, 132249128};
+  const int* const units = N == 3 ? kUnits3 : (N == 5 ? kUnits5 : kUnits7);
   for (int i = 0; i <= N / 2; ++i)
     for (int m = i + 1; m <= N - i; ++m) {
       const long double q = 2.0L / (nn1 * P[i] * P[m] * (x[i] - x[m]));
-      b.Q[i * N - i * (i - 1) + m - i - 1] = static_cast<double>(q);
-      b.Qf[i * N - i * (i - 1) + m - i - 1] = static_cast<float>(q);
+      const int k = i * N - i * (i - 1) + m - i - 1;
+      b.Q[k] = static_cast<double>(q);
+      b.Qf[k] = std::ldexp(static_cast<float>(units[k]), -27);
     }
 }
 

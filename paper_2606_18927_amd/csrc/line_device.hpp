@@ -44,7 +44,8 @@
 // Mixed precision (R = float): the LDS fields, gradients, viscous fluxes, pair
 // fluxes and line sums are FP32; U, G, the primitive recovery, the jumps across
 // faces (lifting corrections, Lax-Friedrichs terms as FP64 differences of the two
-// sides, the whole Roe flux), the sum over directions and the RK update stay FP64.
+// sides, the whole Roe flux), the sum of a direction's parts (flux differences, surface
+// terms, viscous sums) and over directions, and the RK update stay FP64.
 // p, e (entropy-conserving pair: beta, and pi = rho (p - p_ref) / p) and T enter
 // relative to the element's first node.  There the faces keep the strong form (own
 // end value plus jump), so that no FP32 difference of large values is formed; the
@@ -100,14 +101,21 @@ __host__ __device__ constexpr int line_faces() {
 // states of the boundary nodes (for the faces) into the gradient fields that are left.
 // At the end the directions' sums: FP64 5 d + v (0..14) and their diffusive energy
 // parts (15 + d); mixed precision 4 d + (mass, momentum), the energy sums as FP64
-// (12 + 2 d), the diffusive parts (18 + d).  Behind the fields: the line ends' ghost
-// temperatures, mu(T) / mu (Sutherland's law only).
+// (12 + 2 d), the diffusive parts (18 + d), the surface terms and the viscous sums apart.
+// Behind the fields: the line ends' ghost temperatures, mu(T) / mu (Sutherland's law only).
 template <int N, typename R, bool EC>
 struct Fields {
   using L = Line<N>;
   static constexpr bool MIXED = sizeof(R) == 4;
   static constexpr int TS = EC && MIXED ? 7 : 6, GS = TS + 1;
-  static constexpr int COUNT = MIXED ? 21 : 18;
+  // Mixed precision sums in FP32 and adds the sums in FP64: a direction's flux differences,
+  // its surface terms and, with the Kennedy-Gruber pair, its viscous sums (VS + 3 d + c).
+  // At N = 5 and 7 these nine fields would cost a CU a workgroup and follow in a second round
+  // (N = 5, 24^3: 1015 us a step with 30 fields, 985 so; all in one FP32 sum 945, with
+  // the rounding error of the larger parts in the smaller ones).
+  static constexpr bool SPLIT = MIXED && !EC, TWICE = SPLIT && N != 3;
+  static constexpr int VS = TWICE ? 0 : 21;
+  static constexpr int COUNT = !MIXED ? 18 : (SPLIT && !TWICE ? 30 : 21);
   static constexpr int ENDS = COUNT * L::EB;
   static constexpr int GT = ENDS + (L::UNIFORM ? 0 : 16 * L::LINES);
   // (where the lane that forms them also reads them back, in registers: at N = 5 three
@@ -121,8 +129,15 @@ struct Fields {
   __device__ static int end_at(int d, int k, int ab) {
     return L::UNIFORM ? (GS + 3 * (k >> 3) + d) * L::EB + (k & 7) * L::NF + ab : ENDS + k * L::LINES + d * L::NF + ab;
   }
+  // component v of the surface term at end h of a line, in mixed precision at the end: where
+  // the faces put it, or behind the sums (over the ghost temperatures and mu(T) / mu)
+  __device__ static int surface_at(int d, int h, int v, int ab) {
+    return L::UNIFORM ? COUNT * L::EB + (5 * h + v) * L::LINES + d * L::NF + ab : end_at(d, 8 * h + 3 + v, ab);
+  }
   static size_t bytes(const DevPhys& p) {
-    return HEAD * sizeof(double) + sizeof(R) * (static_cast<size_t>(MU) + (p.viscous && p.suth ? L::EB : 0));
+    const size_t used = static_cast<size_t>(MU) + (p.viscous && p.suth ? L::EB : 0);
+    const size_t sums = MIXED && L::UNIFORM ? static_cast<size_t>(COUNT) * L::EB + 10 * L::LINES : 0;
+    return HEAD * sizeof(double) + sizeof(R) * (used > sums ? used : sums);
   }
 };
 
@@ -165,26 +180,35 @@ __device__ inline R q_im(const DevBasis& b, int i, int m) {
     return b.Q[id];
 }
 
+// The s-th of the n pairs at one distance, by its lower node: from the line's two ends
+// inwards.  All sums over pairs run from the farthest pairs (small Q) to the nearest, and
+// the end values come last: the partial sums stay small, and the rounding of row N - i
+// mirrors that of row i.  (Row by row from node 0, constant flow plus noise in FP32:
+// twice the rounding error in the first rows, and a mean error of the line's sum of 3e-10
+// of the flux, now below 5e-11, which a long run accumulates as a loss of mass.)
+__device__ constexpr int pair_low(int n, int s) { return s & 1 ? n - 1 - (s >> 1) : s >> 1; }
+
 // g_i = sum_{m != i} Q_im q_m plus the two ghost values; with STRONG the ghost
 // values are the jumps to them from the own end values.
 template <int N, typename R, bool STRONG>
 __device__ inline void line_derivative(const DevBasis& b, const R (&q)[N + 1], R ghost_lo, R ghost_hi, R (&g)[N + 1]) {
 #pragma unroll
   for (int i = 0; i <= N; ++i) g[i] = R(0);
-  g[0] = R(-0.5) * ghost_lo;
-  g[N] = R(0.5) * ghost_hi;
-  if (STRONG) {
-    g[0] -= R(0.5) * q[0];
-    g[N] += R(0.5) * q[N];
-  }
 #pragma unroll
-  for (int i = 0; i < N; ++i)
+  for (int dist = N; dist > 0; --dist)
 #pragma unroll
-    for (int m = i + 1; m <= N; ++m) {
+    for (int s = 0; s <= N - dist; ++s) {
+      const int i = pair_low(N + 1 - dist, s), m = i + dist;
       const R c = q_im<N, R>(b, i, m);
       g[i] += c * q[m];
       g[m] -= c * q[i];
     }
+  if (STRONG) {
+    g[0] -= R(0.5) * q[0];
+    g[N] += R(0.5) * q[N];
+  }
+  g[0] -= R(0.5) * ghost_lo;
+  g[N] += R(0.5) * ghost_hi;
 }
 
 // The line of a line lane: direction d, position ab in the face
@@ -649,9 +673,8 @@ __device__ inline void ec_rows(const LineArgs& A, const R* sF, const double* hea
       if constexpr (NFLD == 7) x[6] = sF[6 * EB + l];
     };
     load(i, a);
-    const double w = 1.0 / head[i];  // Q = w D
 #pragma unroll 1
-    for (int m = i + 1; m < NP; ++m) {
+    for (int m = N; m > i; --m) {
       R b[NFLD], f[5];
       load(m, b);
       if constexpr (NFLD == 7) {
@@ -661,7 +684,7 @@ __device__ inline void ec_rows(const LineArgs& A, const R* sF, const double* hea
         const double y[4] = {b[0] + b[0], b[1] + b[1], b[2] + b[2], b[3] + b[3]};
         ec_pair<LONG>(x, a[4], 4.0 * a[5], y, b[4], 4.0 * b[5], A.ph.gm1, pl, f);
       }
-      const R c = static_cast<R>(w * A.basis.D[i * NP + m]);
+      const R c = q_im<N, R>(A.basis, i, m);
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         f[v] *= c;
@@ -825,9 +848,10 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
         f[4] = un * (rho * (q[5][i] + q[5][m]) + (MIXED ? pm : pm + p0));
       };
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
+      for (int dist = N; dist > 0; --dist) {
 #pragma unroll
-        for (int m = i + 1; m <= N; ++m) {
+        for (int s = 0; s <= N - dist; ++s) {
+          const int i = pair_low(NP - dist, s), m = i + dist;
           R f[5];
           pair(i, m, f);
           const R c = q_im<N, R>(A.basis, i, m);
@@ -903,9 +927,10 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       } else {
         settle(q);  // (nothing of the versions is shared, and held, before the branch)
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
+        for (int dist = N; dist > 0; --dist) {
 #pragma unroll
-          for (int m = i + 1; m <= N; ++m) {
+          for (int s = 0; s <= N - dist; ++s) {
+            const int i = pair_low(NP - dist, s), m = i + dist;
             R f[5];
             pair(i, m, f);
             const R c = q_im<N, R>(A.basis, i, m);
@@ -914,8 +939,9 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
               acc[v][i] += c * f[v];
               acc[v][m] -= c * f[v];
             }
-            if (m % 2) __builtin_amdgcn_sched_barrier(0);
+            if (s % 2) __builtin_amdgcn_sched_barrier(0);
           }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       if (MIXED) {
@@ -934,7 +960,8 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
 
   // ---- line phase: gradients ------------------------------------------------
   R fn[FACE ? FL : 2][3];  // face lanes: (line, end); line lanes: (end, component)
-  R dun[NP], fm[2];        // mixed precision: sum D u / 2 and the faces' mass parts
+  R dun[NP], fs[2][5];     // mixed precision: sum D u / 2; surface terms (N = 7)
+  R fv[3][NP];             // viscous sums, where they are added apart (SPLIT)
   if constexpr (!FACE) {
     const LineArgs& A = again(args);
     const LineTask<N> t(again(wtid));
@@ -944,10 +971,15 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) gh[h][c] = sF[Fd::end_at(t.d, 8 * h + c, t.ab)];
-      fm[h] = sF[Fd::end_at(t.d, 8 * h + 3, t.ab)];
-      if (!MIXED) acc[0][h ? N : 0] += fm[h];
+      if (!MIXED || L::UNIFORM)
 #pragma unroll
-      for (int v = 1; v < 5; ++v) acc[v][h ? N : 0] += sF[Fd::end_at(t.d, 8 * h + 3 + v, t.ab)];
+        for (int v = 0; v < 5; ++v) {
+          const R s = sF[Fd::end_at(t.d, 8 * h + 3 + v, t.ab)];
+          if (MIXED)
+            fs[h][v] = s;
+          else
+            acc[v][h ? N : 0] += s;
+        }
     }
     if (VISC) {
       // the neighbours' normal viscous flux at the ends, in flight over the next phases
@@ -1115,9 +1147,17 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
       }
       line_derivative<N, R, false>(A.basis, f, gw[0], gw[1], g);
 #pragma unroll
-      for (int m = 0; m < NP; ++m) acc[1 + c][m] -= g[m];
+      for (int m = 0; m < NP; ++m) {
+        if (Fd::SPLIT)
+          fv[c][m] = g[m];
+        else
+          acc[1 + c][m] -= g[m];
+      }
     }
-    settle(acc);
+    if (Fd::SPLIT)
+      settle(fv);
+    else
+      settle(acc);
   } else if constexpr (VISC) {
     // the stresses' work, u . tau_d (a wall's own does no work: ghost -f)
     const LineArgs& A = again(args);
@@ -1139,6 +1179,15 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
 
   __builtin_amdgcn_sched_barrier(0);
   // ---- sums of the three directions, scaling, output -----------------------
+  const auto viscous_sums = [&](const LineTask<N>& t) {
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+      R* o = sF + (Fd::VS + 3 * t.d) * EB + t.node(m);
+      o[t.d * EB] = fv[0][m];
+      o[t.d1 * EB] = fv[1][m];
+      o[t.d2 * EB] = fv[2][m];
+    }
+  };
   phase_end();
   if constexpr (!FACE) {
     const LineTask<N> t(again(wtid));
@@ -1152,11 +1201,20 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
             static_cast<double>(acc[4][m]) + e_ref * static_cast<double>(acc[0][m]) + p_ref * static_cast<double>(dun[m]);
       else
         o[4 * EB + l] = acc[4][m];
-      o[l] = MIXED && m == 0 ? acc[0][m] + fm[0] : (MIXED && m == N ? acc[0][m] + fm[1] : acc[0][m]);
+      o[l] = acc[0][m];
       o[(1 + t.d) * EB + l] = acc[1][m];
       o[(1 + t.d1) * EB + l] = acc[2][m];
       o[(1 + t.d2) * EB + l] = acc[3][m];
     }
+    if (MIXED && L::UNIFORM)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          const int k = v == 1 ? 1 + t.d : (v == 2 ? 1 + t.d1 : (v == 3 ? 1 + t.d2 : v));
+          sF[Fd::surface_at(t.d, h, k, t.ab)] = fs[h][v];
+        }
+    if (Fd::SPLIT && !Fd::TWICE && VISC) viscous_sums(t);
   } else if constexpr (VISC) {
     const int lane = again(wtid) - 64 * L::LW;
 #pragma unroll
@@ -1167,38 +1225,78 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
     }
   }
   phase_end();
-  double g1[ROUNDS][5], u1[ROUNDS][5];  // Ut or the new G, and the new U
-  {
-    const LineArgs& A = again(args);
+  double ut[ROUNDS][5];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const unsigned n = node_of<N>(tl, r);
+    const int i = n % NP, j = (n / NP) % NP, k = n / NF;
+    const int l = L::at(i, j, k);
+    const double c[3] = {-2.0 * (pl.sx * sW[i]), -2.0 * (pl.sy * sW[j]), -2.0 * (pl.sz * sW[k])};
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        double f;
+        if (!MIXED)
+          f = sF[(5 * d + v) * EB + l];
+        else if (v < 4)
+          f = sF[(4 * d + v) * EB + l];
+        else
+          f = reinterpret_cast<const double*>(sF + (12 + 2 * d) * EB)[l];
+        if (VISC && v == 4) f -= static_cast<double>(sF[((MIXED ? 18 : 15) + d) * EB + l]);
+        ut[r][v] = d == 0 ? c[0] * f : ut[r][v] + c[d] * f;
+      }
+    }
+    if constexpr (MIXED) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int x = d == 0 ? i : (d == 1 ? j : k);
+        if (x == 0 || x == N) {
+          const int ab = d == 0 ? j + NP * k : (d == 1 ? i + NP * k : i + NP * j);
+          const R* o = sF + Fd::surface_at(d, x == N ? 1 : 0, 0, ab);
+          // (in the faces' place components are in the line frame: 0, along, across, 4)
+#pragma unroll
+          for (int v = 0; v < 5; ++v) {
+            const int w = L::UNIFORM || v % 4 == 0 ? v : 1 + (v - 1 - d + 3) % 3;
+            ut[r][v] += c[d] * static_cast<double>(o[w * L::LINES]);
+          }
+        }
+      }
+    }
+  }
+  if constexpr (Fd::SPLIT && VISC) {
+    if constexpr (Fd::TWICE) {
+      settle(ut);
+      phase_end();
+      if constexpr (!FACE) viscous_sums(LineTask<N>(again(wtid)));
+      phase_end();
+    }
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
       const unsigned n = node_of<N>(tl, r);
       const int i = n % NP, j = (n / NP) % NP, k = n / NF;
-      const int l = L::at(i, j, k);
-      const double c[3] = {-2.0 * (pl.sx * sW[i]), -2.0 * (pl.sy * sW[j]), -2.0 * (pl.sz * sW[k])};
+      const R* o = sF + Fd::VS * EB + L::at(i, j, k);
+      const double c[3] = {2.0 * (pl.sx * sW[i]), 2.0 * (pl.sy * sW[j]), 2.0 * (pl.sz * sW[k])};
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int v = 0; v < 3; ++v) ut[r][1 + v] += c[d] * static_cast<double>(o[(3 * d + v) * EB]);
+    }
+  }
+  double g1[ROUNDS][5], u1[ROUNDS][5];  // Ut or the new G, and the new U
+  {
+    const LineArgs& A = again(args);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        double ut = 0.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          double f;
-          if (!MIXED)
-            f = sF[(5 * d + v) * EB + l];
-          else if (v < 4)
-            f = sF[(4 * d + v) * EB + l];
-          else
-            f = reinterpret_cast<const double*>(sF + (12 + 2 * d) * EB)[l];
-          if (VISC && v == 4) f -= static_cast<double>(sF[((MIXED ? 18 : 15) + d) * EB + l]);
-          ut = d == 0 ? c[0] * f : ut + c[d] * f;
-        }
         if (RK) {
-          g1[r][v] = A.st.read_G ? A.st.A * gA[r][v] + A.st.dt * ut : A.st.dt * ut;
+          g1[r][v] = A.st.read_G ? A.st.A * gA[r][v] + A.st.dt * ut[r][v] : A.st.dt * ut[r][v];
           u1[r][v] = u[r][v] + A.st.B * g1[r][v];
         } else {
-          g1[r][v] = ut;
+          g1[r][v] = ut[r][v];
         }
       }
-    }
   }
   {
     const LineArgs& A = again(args);

@@ -11,7 +11,7 @@ import pytest
 from paper_2606_18927_amd import dgsem, workloads
 
 from _extended import Operator, box_nodes
-from _gpu import need_gpu, say, to_dev
+from _gpu import need_gpu, say, state, to_dev
 
 pytestmark = pytest.mark.gpu
 P = "periodic"
@@ -72,3 +72,75 @@ def test_curved_elements(N, flux):
     say(e, plain, e / plain)
     k = 5 if flux == "ec_roe" else 4
     assert np.all(e[:k] <= 1.5 * plain[:k])
+
+
+# ------------------------------------------------------------- mixed precision
+
+@pytest.mark.parametrize("N", [3, 5, 7])
+def test_mixed_uniform_flow(N):
+    """In a uniform flow whose fluxes are powers of two every product of the FP32 sums is
+    exact, and the coefficients' rows sum to zero exactly: the right-hand side is zero."""
+    need_gpu()
+    say("uniform flow", N)
+    n = SIZES[N]
+    faces = tuple(np.cumsum(np.concatenate([[0.0], 0.5 + np.arange(k) / k])) for k in n)
+    U = np.empty((5, n[2], n[1], n[0], N + 1, N + 1, N + 1))
+    U[:4] = np.array([1.0, 1.0, -0.5, 0.25]).reshape(4, 1, 1, 1, 1, 1, 1)
+    U[4] = R / (GAMMA - 1) + 0.5 * (1.0 + 0.25 + 0.0625)
+    S = dgsem.Solver(dgsem.MeshSpec(N, faces, (P, P, P), 1.0), GAMMA, R, MU, PR, precision="mixed")
+    got = S.eval_rhs(to_dev(U)).cpu().numpy()
+    S.sync()
+    assert np.all(got == 0.0), np.abs(got).max()
+
+
+def test_mixed_run_keeps_mass():
+    """4000 steps of an inviscid channel flow, N = 5, 8^3 elements.  Each of the N (N + 1)
+    additions of a line's mass sum (values below 1) rounds by at most 2^-25, with no
+    preferred sign: a standard deviation of 2^-25 sqrt(N (N + 1) / 3) for the line, and of the
+    sums over lines and steps by adding variances.  Four of them are allowed; a mean
+    error of the sums would grow with the number of steps instead of its root."""
+    need_gpu()
+    N, n, steps = 5, 8, 4000
+    x, w = dgsem.lgl(N)
+    faces = [np.linspace(0, 2 * np.pi, n + 1), np.linspace(-1, 1, n + 1), np.linspace(0, np.pi, n + 1)]
+    y = 0.5 * (faces[1][:-1, None] + faces[1][1:, None]) + 0.5 * np.diff(faces[1])[:, None] * x
+    shape = (n, n, n, N + 1, N + 1, N + 1)
+    prof = np.broadcast_to((1.5 * (1 - y * y)).reshape(1, n, 1, 1, N + 1, 1), shape)
+    rng = np.random.default_rng(3)
+    v = [prof + 0.05 * rng.uniform(-1, 1, shape)] + [0.05 * rng.uniform(-1, 1, shape) for _ in range(2)]
+    U = np.stack([np.ones(shape), *v, R / (GAMMA - 1) + 0.5 * sum(q * q for q in v)])
+    dt = 0.1 / (2 * N + 1) / (11 * n / 2)
+    S = dgsem.Solver(dgsem.MeshSpec(N, tuple(faces), (P, "wall", P), 1.0), GAMMA, R, 0.0, PR, precision="mixed",
+                     viscous=False)
+    S.set_state(to_dev(U))
+    S.rk_step(dt, steps)
+    S.sync()
+    W = w[:, None, None] * w[None, :, None] * w[None, None, :] / 8 / n ** 3  # of the volume
+    drift = abs(((S.get_state().cpu().numpy().reshape(U.shape)[0] - 1.0) * W).sum())
+    line = 2.0 ** -25 * np.sqrt(N * (N + 1) / 3)
+    s = [2 * n / (f[-1] - f[0]) for f in faces]
+    rate = np.sqrt(sum((w ** 2).sum() ** 2 * n ** 3 * (2 * sd * line / 8 / n ** 3) ** 2 for sd in s))
+    bound = 4 * rate * dt * np.sqrt(steps)
+    say("mass drift", drift, "bound", bound)
+    assert drift < bound
+
+
+def test_mixed_channel_energy_after_500_steps():
+    """The kinetic energy of the 48x32x48 channel after 500 steps, mixed against FP64.
+    With the sums' rounding errors free of a mean it is 6e-12 off; a mean error of 3e-10 of
+    the flux made it 1.6e-10."""
+    need_gpu()
+    wl = workloads.WORKLOADS["channel_n5_48x32x48"]
+    U, dt = state(wl)
+    J = {}
+    for prec in ("fp64", "mixed"):
+        S = dgsem.solver_for(wl, precision=prec)
+        S.set_state(to_dev(U))
+        S.rk_step(dt, 500)
+        S.sync()
+        J[prec] = S.kinetic_energy(S.get_state()).item()
+        say(prec, J[prec])
+        del S
+    e = abs(J["mixed"] - J["fp64"]) / J["fp64"]
+    say("J", e)
+    assert e < 4e-11
