@@ -693,6 +693,7 @@ __device__ __forceinline__ void curv_phases(const LineArgsPtr args, double* cons
 #pragma unroll
       for (int c = 0; c < 3; ++c) gh[h][c] = sF[Fd::end_at(t.d, 8 * h + c, t.ab)];
     }
+    if (L::UNIFORM) wave_reuse();  // (the ends' values lie in the gradient fields)
     if (VISC) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {

@@ -232,6 +232,7 @@ __global__ __launch_bounds__(Line<N>::BS) __attribute__((amdgpu_waves_per_eu(Fac
       gl[r] = sF[k.ghost];
       gr[r] = sF[k.ghost + 3 * NF];
     }
+    if (L::FW == 1) wave_reuse();  // (the ghosts' place takes the results)
     const DevBasis& b = again(args).basis;
 #pragma unroll
     for (int r = 0; r < Fs::ROUNDS; ++r) {

@@ -353,6 +353,14 @@ __device__ __forceinline__ void phase_end() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// After this lanes of a wave overwrite in LDS what other lanes of it read before.  The
+// hardware keeps a wave's LDS accesses in order, this the compiler, which could prove a lane's
+// own accesses apart; it costs no instruction.
+__device__ __forceinline__ void wave_reuse() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Node phase: primitives of the states u into the LDS fields (mixed precision:
 // relative to the state s0 of the element's first node, and the boundary nodes' own
 // states).
@@ -981,6 +989,7 @@ __device__ __forceinline__ void rhs_line_phases(const LineArgsPtr args, double* 
             acc[v][h ? N : 0] += s;
         }
     }
+    if (L::UNIFORM) wave_reuse();  // (the ends' values lie in the gradient fields)
     if (VISC) {
       // the neighbours' normal viscous flux at the ends, in flight over the next phases
 #pragma unroll
