@@ -163,3 +163,46 @@ def test_reverse_step_in_place():
         assert torch.equal(st[0][s], want)
     S.sync()
     assert torch.equal(same, want)
+
+
+@pytest.mark.parametrize("N,n,wavy,opts", [
+    (3, (3, 1, 2), False, {"suth": True}),
+    (3, (2, 2, 2), True, {}),
+    (5, (1, 3, 2), False, {}),
+    (5, (2, 2, 1), True, {"suth": True}),
+    (5, (2, 1, 2), False, {"viscous": False}),
+    (7, (2, 1, 3), False, {}),
+    (7, (1, 2, 2), True, {"suth": True}),
+    (7, (1, 2, 1), False, {"viscous": False, "central": True}),
+])
+@pytest.mark.parametrize("flux,precision,spread", [
+    ("kg_llf", "fp64", 0.2), ("ec_roe", "fp64", 0.2), ("ec_roe", "fp64", 0.02), ("ec_roe", "fp64", 0.002),
+    ("kg_llf", "mixed", 0.2), ("ec_roe", "mixed", 0.2), ("ec_roe", "mixed", 0.02)])
+def test_curved_rk_steps(N, n, wavy, opts, flux, precision, spread):
+    """Three RK steps on warped elements and between wavy walls, as in test_rhs_and_rk_step:
+    the increment against the oracle's, with the states' rounding in the bound."""
+    from oracle import curvilinear as cv
+    from paper_2606_18927_amd import workloads
+    need_gpu()
+    say("curved rk case", N, n, wavy, opts, flux, precision, spread)
+    make = workloads.wavy_channel_nodes if wavy else workloads.warped_nodes
+    X, bc = make(dgsem.lgl(N)[0], n, amp=0.05), (P, "wall", P) if wavy else (P, P, P)
+    mesh = cv.CurvMesh(N, torch.as_tensor(X), bc=bc, T_wall=1.1)
+    suth = (1.0, 0.4) if opts.get("suth") else None
+    g = Gas(gamma=1.4, R=1.0, mu=0.02, Pr=0.72, sutherland=suth is not None, T_ref=1.0, S=0.4)
+    U = random_state(mesh, g.gamma, g.R, np.random.default_rng(80 + N), p_amp=spread, rho_amp=spread)
+    kw = {"viscous": opts.get("viscous", True), "central_only": opts.get("central", False), "flux": flux}
+    ref = cv.rhs(U, mesh, g, **kw).numpy()
+    dt = 1e-3 / max(np.abs(ref[v]).max() / np.abs(U[v].numpy()).max() for v in range(5))
+    S = dgsem.Solver(dgsem.MeshSpec(N, None, bc, 1.1, nodes=X), g.gamma, g.R, g.mu, g.Pr, precision=precision,
+                     sutherland=suth, **kw)
+    S.set_state(to_dev(U.numpy()))
+    S.rk_step(dt, 3)
+    S.sync()
+    want = cv.rk_step(U, mesh, g, dt, 3, **kw).numpy() - U.numpy()
+    got = S.get_state().cpu().numpy().reshape(want.shape) - U.numpy()
+    tol = BOUND[precision] + 4 * 2.3e-16 * np.array(
+        [np.linalg.norm(U[v].numpy()) / np.linalg.norm(want[v]) for v in range(5)])
+    e = rel_l2(got, want)
+    say("curved rk", e, tol)
+    assert np.all(e < tol)
