@@ -122,7 +122,9 @@ typedef struct {
   int precision;      /* DG_FP64, or DG_MIXED: FP32 lifting, volume fluxes,
                          line sums and Lax-Friedrichs surface fluxes; FP64
                          state, primitive recovery, lifting corrections, the
-                         Roe surface flux and RK accumulation; p, e and T enter
+                         Roe surface flux, the sum of a direction's inviscid,
+                         surface and viscous parts (each a FP32 value) and RK
+                         accumulation; p, e and T enter
                          the FP32 parts relative to a per-element reference
                          value (the surface fluxes as FP64 differences of the
                          two sides)                                            */
@@ -151,8 +153,7 @@ dg_status dg_lgl(int N, double* xi, double* w);
  * Errors: DG_EINVAL (null pointers, non-monotone faces, bad bc, gamma <= 1,
  * R <= 0, mu < 0, Pr <= 0, empty mesh, unknown precision, flux or viscosity
  * law, Sutherland's law with T_ref <= 0 or S < 0),
- * DG_EUNSUPPORTED (N not in {3, 5, 7}; DG_FLUX_EC_ROE, DG_BC_WALL_MODEL or
- * DG_VISC_SUTHERLAND with mixed precision).                                  */
+ * DG_EUNSUPPORTED (N not in {3, 5, 7}; DG_FLUX_EC_ROE with DG_MIXED_NOREF).   */
 dg_status dg_init_mesh(const dg_mesh_desc* mesh, const dg_physics* phys, void* hip_stream,
                        dg_ctx** out);
 
@@ -167,11 +168,11 @@ dg_status dg_n_dof(const dg_ctx* ctx, long long* n_dof);
  * and upload the tables.  May be called again to rebind.                      */
 dg_status dg_bind_workspace(dg_ctx* ctx, void* dev_ptr, size_t bytes, int with_adjoint);
 
-/* Copy a state (layout above) into the context and clear the RK register:
- * the initial value U(t0) of the semi-discrete system dU/dt = L(U) (paper
- * Sec. 2.2) that dg_rk_step advances.  U_dev (device, 5 n_dof doubles, caller
- * owned) is read on the context's stream.  Errors: DG_EINVAL (null pointer),
- * DG_ESTATE (no workspace bound).                                            */
+/* Copy a state (layout above) into the context: the initial value U(t0) of the
+ * semi-discrete system dU/dt = L(U) (paper Sec. 2.2) that dg_rk_step advances.
+ * (The RK register is left as it is: a step's first stage does not read it.)
+ * U_dev (device, 5 n_dof doubles, caller owned) is read on the context's
+ * stream.  Errors: DG_EINVAL (null pointer), DG_ESTATE (no workspace bound).  */
 dg_status dg_set_state(dg_ctx* ctx, const double* U_dev);
 
 /* Copy the context's current state (the RK solution of paper Sec. 4 after
@@ -244,8 +245,10 @@ dg_status dg_eval_rhs_vjp(dg_ctx* ctx, const double* U_dev, const double* lam_de
  * lamG += B_s lamU, lamU += dt (dL/dU(U_{n,s}))^T lamG, lamG <- A_s lamG
  * (recomputes the five stage states internally in the context's precision;
  * the VJPs are FP64).  Device arrays of 5 n_dof doubles, caller owned;
- * lamU_n may alias lamU_np1.  Errors: DG_EINVAL, DG_ESTATE (no adjoint
- * workspace), DG_EUNSUPPORTED (curved elements, wall model).                */
+ * lamU_n may alias lamU_np1 or U_n; it is worked in, so that after an
+ * error of the call it holds neither the old nor the new cotangent.  Errors:
+ * DG_EINVAL, DG_ESTATE (no adjoint workspace), DG_EUNSUPPORTED (curved
+ * elements, wall model).                                                    */
 dg_status dg_rk_step_vjp(dg_ctx* ctx, const double* U_n_dev, double t, double dt,
                          const double* lamU_np1_dev, double* lamU_n_dev);
 
@@ -264,8 +267,9 @@ dg_status dg_rk_record_stages(dg_ctx* ctx, const double* U0_dev, double t, doubl
 
 /* dg_rk_step_vjp with the step's five stage states read from stages_dev (the
  * 25 n_dof doubles dg_rk_record_stages wrote for that step) instead of
- * recomputed: lamU_n = dJ/dU_n from lamU_np1.  Needs a workspace bound
- * with_adjoint; FP64 arithmetic.                                             */
+ * recomputed: lamU_n = dJ/dU_n from lamU_np1 (lamU_n as above; it may also lie
+ * in stages_dev, which is read to the end before it is written).  Needs a
+ * workspace bound with_adjoint; FP64 arithmetic.                             */
 dg_status dg_rk_step_vjp_stages(dg_ctx* ctx, const double* stages_dev, double t, double dt,
                                 const double* lamU_np1_dev, double* lamU_n_dev);
 

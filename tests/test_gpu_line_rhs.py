@@ -206,3 +206,37 @@ def test_curved_rk_steps(N, n, wavy, opts, flux, precision, spread):
     e = rel_l2(got, want)
     say("curved rk", e, tol)
     assert np.all(e < tol)
+
+
+@pytest.mark.parametrize("kind", ["fp64", "mixed", "ec_roe", "curved", "curved_mixed", "graph"])
+def test_set_state_after_a_run_that_broke_down(kind):
+    """The RK register of an earlier run, here NaN, does not enter the steps after set_state:
+    its first stage does not read it.  Bitwise the state of a fresh solver."""
+    from paper_2606_18927_amd import workloads
+    need_gpu()
+    N, n = 5, (2, 1, 2)
+    curved = kind.startswith("curved")
+    faces = tuple(np.linspace(0.0, 1.0 + d, n[d] + 1) for d in range(3))
+    X = workloads.warped_nodes(dgsem.lgl(N)[0], n, amp=0.05) if curved else None
+    spec = dgsem.MeshSpec(N, None if curved else faces, (P, P, P), 1.0, nodes=X)
+    kw = {"precision": "mixed" if kind.endswith("mixed") else "fp64", "flux": "ec_roe" if kind == "ec_roe" else "kg_llf"}
+    U = to_dev(random_state(Mesh(N, faces), 1.4, 1.0, np.random.default_rng(9)).numpy())
+
+    def steps(S):
+        S.set_state(U)
+        if kind == "graph":
+            S.rk_graph_build(1e-4, 2)
+            S.rk_graph_launch(1)
+        else:
+            S.rk_step(1e-4, 2)
+        S.sync()
+        return S.get_state()
+
+    S = dgsem.Solver(spec, 1.4, 1.0, 0.01, 0.72, **kw)
+    S.set_state(torch.full_like(U, float("nan")))
+    S.rk_step(1e-4, 1)
+    with pytest.raises(dgsem.DgsemError):
+        S.sync()
+    got = steps(S)
+    assert torch.isfinite(got).all()
+    assert torch.equal(got, steps(dgsem.Solver(spec, 1.4, 1.0, 0.01, 0.72, **kw)))
