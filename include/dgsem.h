@@ -107,7 +107,7 @@ typedef struct {
                          unit normal, scaled by its length); the wall model
                          and the adjoint, lifting or kinetic-energy calls give
                          DG_EUNSUPPORTED.  The workspace holds the metric
-                         terms, 10 FP64 values per DOF (+ 10 FP32 values in
+                         terms, 10 FP64 values per DOF (+ 9 FP32 values in
                          mixed precision) and the FP64 ones again per node
                          on the element boundary.  A non-positive Jacobian at any node
                          makes dg_bind_workspace fail with DG_EINVAL.          */

@@ -35,23 +35,21 @@
 namespace dg {
 namespace {
 
-// abar += (d f#_d(a, b) / d a)^T mu, a and b primitive (rho, u, v, w, p, e).
-template <int d>
+// abar += (d f#(a, b) / d a)^T mu, a and b primitive (rho, u, v, w, p, e), u along the line.
 __device__ inline void kg_vjp(const double a[6], const double b[6], const double mu[5],
                               double abar[6]) {
   const double rho = 0.5 * (a[0] + b[0]);
   const double u0 = 0.5 * (a[1] + b[1]), u1 = 0.5 * (a[2] + b[2]), u2 = 0.5 * (a[3] + b[3]);
   const double p = 0.5 * (a[4] + b[4]);
   const double e = 0.5 * (a[5] + b[5]);
-  const double ud = d == 0 ? u0 : (d == 1 ? u1 : u2);
-  const double mass = rho * ud;
+  const double mass = rho * u0;
   const double S = mu[0] + u0 * mu[1] + u1 * mu[2] + u2 * mu[3] + e * mu[4];
-  abar[0] += 0.5 * ud * S;
+  abar[0] += 0.5 * u0 * S;
   abar[1] += 0.5 * mass * mu[1];
   abar[2] += 0.5 * mass * mu[2];
   abar[3] += 0.5 * mass * mu[3];
-  abar[1 + d] += 0.5 * (rho * S + p * mu[4]);
-  abar[4] += 0.5 * (mu[1 + d] + ud * mu[4]);
+  abar[1] += 0.5 * (rho * S + p * mu[4]);
+  abar[4] += 0.5 * (mu[1] + u0 * mu[4]);
   abar[5] += 0.5 * mass * mu[4];
 }
 
@@ -73,12 +71,11 @@ __device__ inline void prim_vjp(const double s[5], const double Pb[6], double Tb
   Ub[4] += ph.gm1 * pb + ir * Pb[5];
 }
 
-// abar += lb d(|u_d| + c)/dP, c = sqrt(gamma p / rho).
-template <int d>
+// abar += lb d(|u| + c)/dP, c = sqrt(gamma p / rho).
 __device__ inline void speed_vjp(const double a[6], double lb, const DevPhys& ph, double abar[6]) {
   const double c = sqrt(ph.gamma * a[4] / a[0]);
-  const double ud = a[1 + d];
-  abar[1 + d] += lb * (ud > 0.0 ? 1.0 : (ud < 0.0 ? -1.0 : 0.0));
+  const double ud = a[1];
+  abar[1] += lb * (ud > 0.0 ? 1.0 : (ud < 0.0 ? -1.0 : 0.0));
   abar[4] += lb * 0.5 * c / a[4];
   abar[0] -= lb * 0.5 * c / a[0];
 }
@@ -119,13 +116,12 @@ __device__ inline void ln_mean_factors(double f, double& G, double& dG, double& 
   }
 }
 
-// abar += (d f#_EC(a, b) / d a)^T mu for Chandrashekar's flux along d, a and b
+// abar += (d f#_EC(a, b) / d a)^T mu for Chandrashekar's flux along the line, a and b
 // = (rho, u, v, w, p, beta), beta = rho / (2 p); abar[5] is the cotangent of
 // beta (p enters the flux only through beta).  With um = {{u}},
-// q2m = {{|u|^2}}, F1 = rho_ln um_d, p^ = {{rho}} / (2 {{beta}}) and
+// q2m = {{|u|^2}}, F1 = rho_ln um_0, p^ = {{rho}} / (2 {{beta}}) and
 // kappa = 1 / (2 (gamma - 1)), mu . f# = F1 A + p^ Bp where
-//   A = mu_0 + mu_m . um + mu_4 (kappa / beta_ln - q2m / 2 + |um|^2),  Bp = mu_{1+d} + mu_4 um_d.
-template <int d>
+//   A = mu_0 + mu_m . um + mu_4 (kappa / beta_ln - q2m / 2 + |um|^2),  Bp = mu_1 + mu_4 um_0.
 __device__ inline void ec_vjp(const double a[6], const double b[6], const double mu[5],
                               double gm1, double abar[6]) {
   const double sr = a[0] + b[0], sb = a[5] + b[5];
@@ -139,20 +135,20 @@ __device__ inline void ec_vjp(const double a[6], const double b[6], const double
   const double um[3] = {0.5 * (a[1] + b[1]), 0.5 * (a[2] + b[2]), 0.5 * (a[3] + b[3])};
   const double q2m = 0.5 * (a[1] * a[1] + a[2] * a[2] + a[3] * a[3] + b[1] * b[1] + b[2] * b[2] + b[3] * b[3]);
   const double um2 = um[0] * um[0] + um[1] * um[1] + um[2] * um[2];
-  const double F1 = rho_ln * um[d];
+  const double F1 = rho_ln * um[0];
   const double kap = 0.5 / gm1;
   const double A = mu[0] + mu[1] * um[0] + mu[2] * um[1] + mu[3] * um[2] +
                    mu[4] * (kap * ibl - 0.5 * q2m + um2);
-  const double Bp = mu[1 + d] + mu[4] * um[d];
+  const double Bp = mu[1] + mu[4] * um[0];
   // d rho_ln / d rho_a = G / 2 + rho_b G' / sr;  d (1 / beta_ln) / d beta_a = -2 ib^2 F + 4 beta_b ib^3 F'
   const double drl = 0.5 * G + b[0] * dG * ir;
   const double dibl = ib * ib * (-2.0 * F + 4.0 * b[5] * ib * dF);
-  abar[0] += A * um[d] * drl + 0.5 * ib * Bp;
+  abar[0] += A * um[0] * drl + 0.5 * ib * Bp;
   abar[5] += F1 * mu[4] * kap * dibl - 0.5 * sr * ib * ib * Bp;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     double sk = F1 * (mu[1 + k] + 2.0 * mu[4] * um[k]);
-    if (k == d) sk += mu[4] * p_hat + A * rho_ln;
+    if (k == 0) sk += mu[4] * p_hat + A * rho_ln;
     abar[1 + k] += 0.5 * sk - 0.5 * F1 * mu[4] * a[1 + k];
   }
 }
@@ -190,7 +186,6 @@ __device__ inline void hh_vjp(double lam, double lamL, double lamR, double gb, d
 // (rho, u, v, w, p, e): reverse mode of the Roe dissipation (the forward
 // quantities of that function, then their cotangents in reverse order), own =
 // L when own_L; E = rho e carries the total-energy cotangent into rho and e.
-template <int d>
 __device__ inline void roe_vjp(const double so[5], const double sn[5], bool own_L,
                                const double phi[5], const DevPhys& ph, double Pb[6]) {
   const double* sL = own_L ? so : sn;
@@ -222,15 +217,15 @@ __device__ inline void roe_vjp(const double so[5], const double sn[5], bool own_
   const double a2 = ph.gm1 * (H - 0.5 * q2);
   const double a = sqrt(a2);
   const double rho = sl * sr;
-  const double un = ut[d];
+  const double un = ut[0];
   const double dp = R[4] - L[4];
-  const double dud = R[1 + d] - L[1 + d];
+  const double dud = R[1] - L[1];
   const double i2a2 = 0.5 / a2;
   const double al1 = (dp - rho * a * dud) * i2a2, al5 = (dp + rho * a * dud) * i2a2;
   const double al2 = (R[0] - L[0]) - dp / a2;
   const double cl = sqrt(ph.gamma * L[4] / L[0]), cr = sqrt(ph.gamma * R[4] / R[0]);
-  const double l1 = hh_abs(un - a, L[1 + d] - cl, R[1 + d] - cr);
-  const double l5 = hh_abs(un + a, L[1 + d] + cl, R[1 + d] + cr);
+  const double l1 = hh_abs(un - a, L[1] - cl, R[1] - cr);
+  const double l5 = hh_abs(un + a, L[1] + cl, R[1] + cr);
   const double l2 = fabs(un);
   const double t1 = l1 * al1, t5 = l5 * al5, t2 = l2 * al2, ts = l2 * rho;
   const double T = t1 + t2 + t5;
@@ -242,21 +237,21 @@ __device__ inline void roe_vjp(const double so[5], const double sn[5], bool own_
   double Tb = g[0], tsb = 0.0, udtb = g[4] * ts, utb[3], udt = 0.0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const double sh = c == d ? 0.0 : R[1 + c] - L[1 + c];
+    const double sh = c == 0 ? 0.0 : R[1 + c] - L[1 + c];
     udt += ut[c] * sh;
     Tb += g[1 + c] * ut[c];
     utb[c] = g[1 + c] * T + udtb * sh;
     tsb += g[1 + c] * sh;
-    // the shear jump (c != d): ts d(D_{1+c})/d du_c + ut_c d(D_4)/d du_c
-    const double dub = c == d ? 0.0 : g[1 + c] * ts + udtb * ut[c];
+    // the shear jump (c != 0): ts d(D_{1+c})/d du_c + ut_c d(D_4)/d du_c
+    const double dub = c == 0 ? 0.0 : g[1 + c] * ts + udtb * ut[c];
     Rb[1 + c] += dub;
     Lb[1 + c] -= dub;
   }
-  double t5b = g[1 + d] * a + g[4] * (H + un * a) + Tb;
-  double t1b = -g[1 + d] * a + g[4] * (H - un * a) + Tb;
+  double t5b = g[1] * a + g[4] * (H + un * a) + Tb;
+  double t1b = -g[1] * a + g[4] * (H - un * a) + Tb;
   const double t2b = g[4] * 0.5 * q2 + Tb;
   tsb += g[4] * udt;
-  double ab = (g[1 + d] + g[4] * un) * (t5 - t1);
+  double ab = (g[1] + g[4] * un) * (t5 - t1);
   double Hb = g[4] * (t1 + t5);
   double unb = g[4] * a * (t5 - t1);
   double q2b = g[4] * 0.5 * t2;
@@ -265,12 +260,12 @@ __device__ inline void roe_vjp(const double so[5], const double sn[5], bool own_
   const double al2b = t2b * l2, al5b = t5b * l5, al1b = t1b * l1;
   unb += un > 0.0 ? l2b : (un < 0.0 ? -l2b : 0.0);
   double b5 = 0.0, bL5 = 0.0, bR5 = 0.0, b1 = 0.0, bL1 = 0.0, bR1 = 0.0;
-  hh_vjp(un + a, L[1 + d] + cl, R[1 + d] + cr, t5b * al5, b5, bL5, bR5);
-  hh_vjp(un - a, L[1 + d] - cl, R[1 + d] - cr, t1b * al1, b1, bL1, bR1);
+  hh_vjp(un + a, L[1] + cl, R[1] + cr, t5b * al5, b5, bL5, bR5);
+  hh_vjp(un - a, L[1] - cl, R[1] - cr, t1b * al1, b1, bL1, bR1);
   unb += b5 + b1;
   ab += b5 - b1;
-  Lb[1 + d] += bL5 + bL1;
-  Rb[1 + d] += bR5 + bR1;
+  Lb[1] += bL5 + bL1;
+  Rb[1] += bR5 + bR1;
   const double clb = bL5 - bL1, crb = bR5 - bR1;
   Lb[4] += clb * cl / (2.0 * L[4]);
   Lb[0] -= clb * cl / (2.0 * L[0]);
@@ -284,11 +279,11 @@ __device__ inline void roe_vjp(const double so[5], const double sn[5], bool own_
   rhob += dal * a * dud;
   ab += dal * rho * dud;
   const double dudb = dal * rho * a;
-  Rb[1 + d] += dudb;
-  Lb[1 + d] -= dudb;
+  Rb[1] += dudb;
+  Lb[1] -= dudb;
   Rb[4] += dpb;
   Lb[4] -= dpb;
-  utb[d] += unb;
+  utb[0] += unb;
   double slb = rhob * sr, srb = rhob * sl;
   a2b += ab / (2.0 * a);
   Hb += a2b * ph.gm1;
@@ -580,11 +575,11 @@ __device__ __forceinline__ void face_vjp(const DevPhys& ph, const double (&P)[6]
     const double Ae[6] = {P[0], P[1], P[2], P[3], P[4], 0.5 * P[0] / P[4]};
     const double Be[6] = {Pn[0], Pn[1], Pn[2], Pn[3], Pn[4], 0.5 * Pn[0] / Pn[4]};
     double Pbe[6] = {0, 0, 0, 0, 0, 0};
-    ec_vjp<0>(Ae, Be, phi, ph.gm1, Pbe);
+    ec_vjp(Ae, Be, phi, ph.gm1, Pbe);
     fold_beta(Ae, Pbe, Pb);
-    if (!ph.central) roe_vjp<0>(so, sn, up, phi, ph, Pb);
+    if (!ph.central) roe_vjp(so, sn, up, phi, ph, Pb);
   } else {
-    kg_vjp<0>(P, Pn, phi, Pb);
+    kg_vjp(P, Pn, phi, Pb);
     if (!ph.central) {
       const double co = fabs(P[1]) + sqrt(ph.gamma * P[4] / P[0]);
       const double cn = fabs(Pn[1]) + sqrt(ph.gamma * Pn[4] / Pn[0]);
@@ -603,7 +598,7 @@ __device__ __forceinline__ void face_vjp(const DevPhys& ph, const double (&P)[6]
       Pb[2] += P[0] * Ud[2];
       Pb[3] += P[0] * Ud[3];
       Pb[5] += P[0] * Ud[4];
-      if (own_active) speed_vjp<0>(P, lb, ph, Pb);
+      if (own_active) speed_vjp(P, lb, ph, Pb);
     }
   }
 }

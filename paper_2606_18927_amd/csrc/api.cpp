@@ -85,9 +85,9 @@ Layout layout(const dg_ctx* c) {
   L.G = take(state);
   L.ffv = c->phys.viscous ? take(fbytes) : off;
   L.tauw = c->wall_model ? take(static_cast<size_t>(c->n_wall_faces) * 3 * NP * NP * sizeof(double)) : off;
-  // FP64 metric terms, and their FP32 copy for the mixed-precision sweeps
+  // FP64 metric terms and 1/J, and an FP32 copy of the terms for the mixed-precision sweeps
   L.geo = c->curvilinear
-              ? take(10 * dof * (sizeof(double) + (c->phys.precision == DG_FP64 ? 0 : sizeof(float))))
+              ? take(dof * (10 * sizeof(double) + (c->phys.precision == DG_FP64 ? 0 : 9 * sizeof(float))))
               : off;
   // the ten FP64 fields once more at the boundary nodes, contiguous per element
   // for the face-flux kernel and the surface terms

@@ -123,13 +123,12 @@ __global__ __launch_bounds__(CurvCfg<N>::BS) void k_metrics(const double* __rest
       for (int c = 0; c < 9; ++c) geoF[c * nE * NFN + of] = Ja[c];
       geoF[9 * nE * NFN + of] = 1.0 / J;
     }
-    // FP32 copy for the mixed-precision sweeps, after the ten FP64 fields
+    // FP32 copy of the metric terms for the mixed-precision sweeps, after the ten FP64 fields
     // (the workspace holds it only in mixed-precision contexts)
     if (with_f32) {
       float* const g32 = reinterpret_cast<float*>(geo + 10 * stride);
 #pragma unroll
       for (int c = 0; c < 9; ++c) g32[c * stride + o] = static_cast<float>(Ja[c]);
-      g32[9 * stride + o] = static_cast<float>(1.0 / J);
     }
   }
 }

@@ -12,17 +12,15 @@ template <int N>
 struct Cfg;
 template <>
 struct Cfg<3> {
-  // EPB elements per workgroup of BS lanes; FACE_WAVES: waves per SIMD the
-  // face-flux kernel is register-bounded for
-  static constexpr int EPB = 2, BS = 192, FACE_WAVES = 4;
+  static constexpr int EPB = 2, BS = 192;
 };
 template <>
 struct Cfg<5> {
-  static constexpr int EPB = 1, BS = 256, FACE_WAVES = 8;
+  static constexpr int EPB = 1, BS = 256;
 };
 template <>
 struct Cfg<7> {
-  static constexpr int EPB = 1, BS = 512, FACE_WAVES = 8;
+  static constexpr int EPB = 1, BS = 512;
 };
 
 // LDS block of one element and field: x-rows padded by one entry.
@@ -62,8 +60,6 @@ __device__ inline void elem_coords(long long e, const DevMesh& m, int& ex, int& 
   ey = static_cast<int>(t - static_cast<unsigned>(ez) * ny);
 }
 
-// Face neighbour of element (ex, ey, ez) across its lower (up = false) or
-// upper face normal to d; -1 on a wall.
 // a[d] for a per-lane d from three uniform values held in registers: a
 // per-lane index into the by-value mesh argument (or a select between its
 // fields, which the compiler folds into one) is a dependent memory load.
@@ -74,6 +70,8 @@ __device__ inline int pick3(int a0, int a1, int a2, int d) {
   return d == 0 ? a0 : (d == 1 ? a1 : a2);
 }
 
+// Face neighbour of element (ex, ey, ez) across its lower (up = false) or
+// upper face normal to d; -1 on a wall.
 __device__ inline long long neighbour(const DevMesh& m, int ex, int ey, int ez, int d, bool up) {
   const int nd = pick3(m.n[0], m.n[1], m.n[2], d);
   const int bcd = pick3(m.bc[0], m.bc[1], m.bc[2], d);
@@ -153,39 +151,13 @@ struct FaceTask {
   __device__ int own_node() const { return oi + (N + 1) * (oj + (N + 1) * ok); }
 };
 
-// Face node number t (0 <= t < n_face_nodes) of an element -> (i, j, k): the
-// two k planes first, then the boundary ring of each interior k plane.
-template <int N>
-__host__ __device__ inline void face_node_of(int t, int& i, int& j, int& k) {
-  constexpr int NP = N + 1, NF = NP * NP, RING = 4 * N;
-  if (t < 2 * NF) {
-    k = t < NF ? 0 : N;
-    const int ab = t < NF ? t : t - NF;
-    i = ab % NP;
-    j = ab / NP;
-    return;
-  }
-  const int r = t - 2 * NF;
-  k = 1 + r / RING;
-  const int q = r % RING;
-  if (q < NP) {
-    i = q; j = 0;
-  } else if (q < 2 * NP) {
-    i = q - NP; j = N;
-  } else if (q < 2 * NP + N - 1) {
-    i = 0; j = q - 2 * NP + 1;
-  } else {
-    i = N; j = q - (2 * NP + N - 1) + 1;
-  }
-}
-
 template <int N>
 __host__ __device__ constexpr int n_face_nodes() {
   return 2 * (N + 1) * (N + 1) + (N - 1) * 4 * N;
 }
 
-// Inverse of face_node_of: the face node number of a node on the element's
-// boundary.
+// Face node number (0 <= t < n_face_nodes) of a node on the element's boundary:
+// the two k planes first, then the boundary ring of each interior k plane.
 template <int N>
 __host__ __device__ constexpr int face_node_index(int i, int j, int k) {
   constexpr int NP = N + 1, NF = NP * NP, RING = 4 * N;
@@ -308,24 +280,6 @@ __device__ inline double hh_abs(double lam, double lam_L, double lam_R) {
   delta = delta > 0.0 ? delta : 0.0;
   const double b = delta + delta;
   return fabs(lam) < delta ? quot(lam * lam + delta * delta, b, rcp_nr(b)) : fabs(lam);
-}
-
-// Viscous flux along d: g[3 q + b] = d q / d x_b for q in (u, v, w, T);
-// returns (tau_1d, tau_2d, tau_3d, u_a tau_ad + kappa dT/dx_d).
-template <int d, typename R>
-__device__ inline void viscous_flux(R u, R v, R w, const R g[12], R mu, R kappa, R f[4]) {
-  const R div = g[0] + g[4] + g[8];
-  R t0 = mu * (g[0 * 3 + d] + g[d * 3 + 0]);
-  R t1 = mu * (g[1 * 3 + d] + g[d * 3 + 1]);
-  R t2 = mu * (g[2 * 3 + d] + g[d * 3 + 2]);
-  const R dd = R(2.0 / 3.0) * mu * div;
-  if (d == 0) t0 -= dd;
-  if (d == 1) t1 -= dd;
-  if (d == 2) t2 -= dd;
-  f[0] = t0;
-  f[1] = t1;
-  f[2] = t2;
-  f[3] = u * t0 + v * t1 + w * t2 + kappa * g[9 + d];
 }
 
 template <int N>
