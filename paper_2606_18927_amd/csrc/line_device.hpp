@@ -498,7 +498,8 @@ __device__ inline void ec_pair(const double (&a)[4], double ba, double qa, const
 //   1 / beta_ln - 1 / beta_ref = (2 (F - 1) - (dbeta_a + dbeta_b) / beta_ref) / sb,
 // F = atanh f / f of the beta pair, so no FP32 difference of O(p_ref) terms is formed;
 // f = f#_EC - (0, p_ref, 0, 0, F_rho e_ref + p_ref {{u}}).  SERIES: both logarithmic
-// means by their series (f^2 below 1e-2, dropped terms below 2e-10).
+// means by their series (f^2 below 1e-2, dropped terms below 1.1e-9 in F, 3e-10 in G, where
+// an FP32 rounding of the means is 6e-8).
 template <bool SERIES>
 __device__ inline void ec_pair_ref(const float* a, const float* b, float kap, float beta_ref, float ibr, float (&f)[5]) {
   const float sr = a[0] + b[0], sdb = a[4] + b[4];
