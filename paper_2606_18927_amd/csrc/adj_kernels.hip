@@ -53,15 +53,15 @@ __device__ inline void kg_vjp(const double a[6], const double b[6], const double
   abar[5] += 0.5 * mass * mu[4];
 }
 
-// Ubar += (dP/dU)^T Pbar + (dT/dU)^T Tbar, P = (rho, u, v, w, p, e), T = p/(rho R).
-__device__ inline void prim_vjp(const double s[5], const double Pb[6], double Tb,
-                                const DevPhys& ph, double Ub[5]) {
-  const double ir = 1.0 / s[0];
-  const double u = s[1] * ir, v = s[2] * ir, w = s[3] * ir;
+// Ubar += (dP/dU)^T Pbar + (dT/dU)^T Tbar at the primitives P = (rho, u, v, w, p, e),
+// T = p/(rho R).  P are the values that the fluxes were transposed at: the terms in e of
+// rho's cotangent, hundreds of velocities squared at Ma = 0.1, cancel between the pairs and
+// here only for the same e (with e formed again from rho e: 2.5 times the rounding error).
+__device__ inline void prim_vjp(const double P[6], const double Pb[6], double Tb, const DevPhys& ph, double Ub[5]) {
+  const double ir = 1.0 / P[0];
+  const double u = P[1], v = P[2], w = P[3], e = P[5];
   const double q2 = u * u + v * v + w * w;
-  const double p = ph.gm1 * (s[4] - 0.5 * s[0] * q2);
-  const double e = s[4] * ir;
-  const double T = p * ph.inv_R * ir;
+  const double T = P[4] * ph.inv_R * ir;
   const double pb = Pb[4] + Tb * ir * ph.inv_R;
   const double rb = Pb[0] - Tb * T * ir;
   Ub[0] += rb - ir * (u * Pb[1] + v * Pb[2] + w * Pb[3]) + 0.5 * ph.gm1 * q2 * pb - e * ir * Pb[5];
@@ -349,7 +349,7 @@ __device__ inline const VjpArgs& again(VjpArgsPtr p) {
 // phase takes one node per lane.  LDS fields (of EB values): halves of rho, u, v, w, p, e
 // (entropy-conserving pair: beta in place of p), T, lam (5); raw gradients GR + 3 q + d;
 // viscous flux cotangents FV + 3 c + d.  At the end the lines' sums (6 per direction) take
-// the place of the latter two, the faces' primitive cotangents END that of T and lam.
+// the place of the latter two, the faces' cotangents END that of T and lam.
 //
 // What bounds it (N = 5, 48 x 32 x 48 elements, Kennedy-Gruber pair: 1.46 ms; with one lane
 // per node 1.80): 3.1 GB of HBM traffic (0.49 ms for a triad), vector instructions issue
@@ -364,9 +364,9 @@ struct VjpShape {
   using L = Line<N>;
   static constexpr int LW = L::LW, BS = N == 7 ? 512 : 128 * LW;
   static constexpr int T = 6, LAM = 7, GR = 12, FV = 24, SUM = 12;
-  static constexpr int END = 6 * L::EB >= 12 * L::LINES ? T * L::EB : 36 * L::EB;
+  static constexpr int END = 6 * L::EB >= 10 * L::LINES ? T * L::EB : 36 * L::EB;
   static constexpr int HEAD = 8;  // 1 / w_i
-  static constexpr size_t BYTES = 8 * (HEAD + 36 * L::EB + (END == 36 * L::EB ? 12 * L::LINES : 0));
+  static constexpr size_t BYTES = 8 * (HEAD + 36 * L::EB + (END == 36 * L::EB ? 10 * L::LINES : 0));
   static constexpr int BLOCK = N == 7 ? 4 : L::NP;  // nodes of a line held in registers
 };
 
@@ -549,19 +549,23 @@ __device__ inline void line_rows_ec(const DevBasis& b, const double* sF, const d
   }
 }
 
-// Cotangents of the own primitives Pb = (rho, u, v, w, p, e), line frame, through one
-// face's convective flux F*: P own primitives, lo own lam, sn and ln of the neighbour,
+// Cotangent of the own state Ub, line frame, through one face's convective flux F*: P own
+// primitives (rho, u, v, w, p, e), lo own lam, sn and ln of the neighbour,
 // so_iw and sn_iw the two elements' s_d / w_end.  The own side is L of an upper face.
 // (In the weak form the own physical flux cancels with the diagonal of the volume sum.)
+// The dissipation's cotangent belongs to the conservative state: through those of (rho, e)
+// it would cancel again in rho, behind the rounding of e times the wave speed.
 template <bool EC>
 __device__ __forceinline__ void face_vjp(const DevPhys& ph, const double (&P)[6], const double (&lo)[5],
                                          const double (&sn)[5], const double (&ln)[5], bool wall, bool up, double so_iw,
-                                         double sn_iw, double (&Pb)[6]) {
+                                         double sn_iw, double (&Ub)[5]) {
+  double Pb[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll
-  for (int q = 0; q < 6; ++q) Pb[q] = 0.0;
+  for (int v = 0; v < 5; ++v) Ub[v] = 0.0;
   const double sg = up ? -1.0 : 1.0;
   if (wall) {  // F*_c = (0, p_o e_d, 0)
     Pb[4] = sg * so_iw * lo[1];
+    prim_vjp(P, Pb, 0.0, ph, Ub);
     return;
   }
   double phi[5];
@@ -587,20 +591,16 @@ __device__ __forceinline__ void face_vjp(const DevPhys& ph, const double (&P)[6]
       const bool own_active = up ? (co >= cn) : (co > cn);
       // F*_c contains -lam/2 (U_R - U_L)
       const double dU = up ? 0.5 * lam : -0.5 * lam;
-      double lb = 0.0, Ud[5];
+      double lb = 0.0;
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        Ud[v] = dU * phi[v];
+        Ub[v] = dU * phi[v];
         lb -= 0.5 * phi[v] * (up ? sn[v] - so[v] : so[v] - sn[v]);
       }
-      Pb[0] += Ud[0] + P[1] * Ud[1] + P[2] * Ud[2] + P[3] * Ud[3] + P[5] * Ud[4];
-      Pb[1] += P[0] * Ud[1];
-      Pb[2] += P[0] * Ud[2];
-      Pb[3] += P[0] * Ud[3];
-      Pb[5] += P[0] * Ud[4];
       if (own_active) speed_vjp(P, lb, ph, Pb);
     }
   }
+  prim_vjp(P, Pb, 0.0, ph, Ub);
 }
 
 // ROLE 0: line lanes, 1: face lanes, 2: neither (the node phases only).
@@ -612,7 +612,7 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
   double* const sW = head;
   double* const sF = head + S::HEAD;
   double y[NP][6];     // line lanes: cotangents of the line's nodes
-  double pe[2][6];     // face lanes: those through the faces at its ends
+  double ue[2][5];     // face lanes: those of the states at its ends, through the faces
   const Place pl(again(args).mesh, e);
   const bool visc = again(args).ph.viscous != 0;
   {
@@ -681,7 +681,7 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
         }
         const double lo[5] = {sF[S::LAM * EB + p], sF[(S::LAM + 1 + t.d) * EB + p], sF[(S::LAM + 1 + t.d1) * EB + p],
                               sF[(S::LAM + 1 + t.d2) * EB + p], sF[(S::LAM + 4) * EB + p]};
-        face_vjp<EC>(B.ph, P, lo, sn[h], ln[h], wall, h != 0, siw, niw, pe[h]);
+        face_vjp<EC>(B.ph, P, lo, sn[h], ln[h], wall, h != 0, siw, niw, ue[h]);
         const double ir = rcp_nr(sn[h][0]);
         const double v0 = sn[h][1] * ir, v1 = sn[h][2] * ir, v2 = sn[h][3] * ir;
         const double Tn = B.ph.gm1 * (sn[h][4] - 0.5 * (sn[h][1] * v0 + sn[h][2] * v1 + sn[h][3] * v2)) * B.ph.inv_R * ir;
@@ -692,7 +692,7 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
         gq[h][2] = wall ? -0.5 * P[3] : 0.5 * v2;
         gq[h][3] = wall ? 2.0 * B.mesh.T_wall - T : Tn;
       }
-      settle(pe);
+      settle(ue);
       settle(gl);
       settle(gq);
       if (visc) {
@@ -818,12 +818,11 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
     double* o = sF + S::END + t.d * NF + t.ab;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      o[(6 * h) * LINES] = pe[h][0];
-      o[(6 * h + 1 + t.d) * LINES] = pe[h][1];
-      o[(6 * h + 1 + t.d1) * LINES] = pe[h][2];
-      o[(6 * h + 1 + t.d2) * LINES] = pe[h][3];
-      o[(6 * h + 4) * LINES] = pe[h][4];
-      o[(6 * h + 5) * LINES] = pe[h][5];
+      o[(5 * h) * LINES] = ue[h][0];
+      o[(5 * h + 1 + t.d) * LINES] = ue[h][1];
+      o[(5 * h + 1 + t.d1) * LINES] = ue[h][2];
+      o[(5 * h + 1 + t.d2) * LINES] = ue[h][3];
+      o[(5 * h + 4) * LINES] = ue[h][4];
     }
   }
   phase_end();
@@ -845,19 +844,18 @@ __device__ __forceinline__ void vjp_phases(const VjpArgsPtr args, double* const 
       Pb[4] = 0.0;
       fold_beta(Ae, Pbe, Pb);
     }
+    double Ub[5] = {0, 0, 0, 0, 0};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const int x = d == 0 ? i : (d == 1 ? j : k);
       if (x == 0 || x == N) {
         const int ab = d == 0 ? j + NP * k : (d == 1 ? i + NP * k : i + NP * j);
-        const double* o = sF + S::END + (x == N ? 6 : 0) * LINES + d * NF + ab;
+        const double* o = sF + S::END + (x == N ? 5 : 0) * LINES + d * NF + ab;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) Pb[q] += o[q * LINES];
+        for (int v = 0; v < 5; ++v) Ub[v] += o[v * LINES];
       }
     }
-    const double s[5] = {P[0], P[0] * P[1], P[0] * P[2], P[0] * P[3], P[0] * P[5]};
-    double Ub[5] = {0, 0, 0, 0, 0};
-    prim_vjp(s, Pb, Tb, A.ph, Ub);
+    prim_vjp(P, Pb, Tb, A.ph, Ub);
     const long long stride = A.mesh.nE * NN;
 #pragma unroll
     for (int v = 0; v < 5; ++v) store_once(&(A.ubar + v * stride + static_cast<long long>(e) * NN)[n], Ub[v]);
@@ -970,10 +968,11 @@ __global__ __launch_bounds__(Cfg<N>::BS) void k_vjp_b(const double* __restrict__
       if (k == 0) qb[c] += sQ[le][4][c][i + NP * j];
       if (k == N) qb[c] += sQ[le][5][c][i + NP * j];
     }
-    double s[5];
+    double s[5], P[6];
     load_state(U, stride, idx, s);
+    to_prim(s, ph, P);
     const double Pb[6] = {0.0, qb[0], qb[1], qb[2], 0.0, 0.0};
-    prim_vjp(s, Pb, qb[3], ph, Ub);
+    prim_vjp(P, Pb, qb[3], ph, Ub);
   }
   if (ACC) {
     // out += scale Ubar; with cot, also the next RK stage cotangent
