@@ -527,12 +527,11 @@ __device__ inline void line_rows_ec(const DevBasis& b, const double* sF, const d
   for (int i = 0; i < N; ++i) {
     double x[11], z[6] = {0, 0, 0, 0, 0, 0};
     vjp_node<N, true>(sF, sW, t, i, c, x);
-    const double w = 1.0 / sW[i];  // Q = w D
 #pragma unroll 1
     for (int m = i + 1; m < NP; ++m) {
       double q[11], f[6] = {0, 0, 0, 0, 0, 0};
       vjp_node<N, true>(sF, sW, t, m, c, q);
-      ec_pair_vjp<MEANS>(x, q, w * b.D[i * NP + m], kap, z, f);
+      ec_pair_vjp<MEANS>(x, q, q_im<N, double>(b, i, m), kap, z, f);
 #pragma unroll
       for (int r = 1; r < NP; ++r) {
         const double sel = r == m ? 1.0 : 0.0;
