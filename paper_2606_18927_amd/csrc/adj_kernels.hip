@@ -351,14 +351,20 @@ __device__ inline const VjpArgs& again(VjpArgsPtr p) {
 // viscous flux cotangents FV + 3 c + d.  At the end the lines' sums (6 per direction) take
 // the place of the latter two, the faces' cotangents END that of T and lam.
 //
-// What bounds it (N = 5, 48 x 32 x 48 elements, Kennedy-Gruber pair: 1.46 ms; with one lane
-// per node 1.80): 3.1 GB of HBM traffic (0.49 ms for a triad), vector instructions issue
-// 47 % of the time (398 M wave instructions), LDS is busy 42 %, and the neighbours' values
+// What bounds it (N = 5, 48 x 32 x 48 elements, Kennedy-Gruber pair: 1.35 ms in reverse RK
+// steps, 1.40 in single calls; with one lane per node 1.62, 1.80): 4.1 GB of HBM traffic
+// (0.64 ms for a triad), vector instructions issue 57 % of the time (405 M wave
+// instructions), LDS is busy 41 %, and the neighbours' values
 // at the line ends (20 loads per face lane, each of 64 addresses in as many cache
 // lines) hold up both.  Without the pairs it is 1.5 % faster, without the stores of
 // gbar 10 %.  A second load of the neighbours' lam by the line lanes cost 0.08 ms, three
 // workgroups per CU instead of two (24 fields, pairs in blocks) 0.13, workgroups that
 // loop over elements and fetch the next one early 0.2.
+// The same shape at the other degrees (us per transposed right-hand side, both kernels; with
+// one lane per node in brackets; entropy-conserving pair with density noise of 0.1 / 5 / 40 %):
+//   N = 3, 32^3, 128 lanes for 64 nodes          291 (345)   445 / 509 / 599 (612 / 1037 / 1036)
+//   N = 5, 24^3                                  402 (451)   481 / 597 / 958 (774 / 1493 / 1494)
+//   N = 7, 16^3, 147 KB LDS, one workgroup a CU  294 (378)   398 / 486 / 771 (553 / 1093 / 1092)
 template <int N>
 struct VjpShape {
   using L = Line<N>;

@@ -13,9 +13,9 @@
 //   nodes  the three directions' sums, Ut = -(1/J) (...), output or RK update.
 //
 // What bounds it (N = 7, 32^3 elements, RK instance, per launch; with one lane per node
-// in brackets): Kennedy-Gruber pair FP64 1215 us (1590), 5.32 GB of HBM traffic (5.84),
-// vector instructions issue 40 % of the time; mixed 924 us (1290), 5.27 GB, 68 %;
-// entropy-conserving pair FP64 1391 us (2860), mixed 1145 us (1750), 88 %.  A triad moves
+// in brackets): Kennedy-Gruber pair FP64 1245 us (1590), 5.39 GB of HBM traffic (5.84),
+// vector instructions issue 40 % of the time; mixed 943 us (1290), 5.27 GB, 69 %;
+// entropy-conserving pair FP64 1419 us (2860), mixed 1190 us (1750), 87 %.  A triad moves
 // 5.3 GB in 0.83 ms: the metric terms, ten values per node against five of the state, are
 // most of the traffic.  FP64 holds two workgroups per CU (81 KB LDS), mixed three.
 //

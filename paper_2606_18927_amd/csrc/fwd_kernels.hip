@@ -57,10 +57,10 @@ __device__ inline const FaceArgs& again(FaceArgsPtr p) {
 // CU.  The sums are settled before the barriers: sunk past them they need 122 instead
 // of 65 registers, and N = 5 runs 1.3x slower on half the waves.
 // Mixed precision stores FP32 and computes in FP64 (without packed instructions FP32
-// is no faster) with the FP32 entries of Q: the rounding of a row's entries is a
-// systematic error of a gradient (row sum times mean velocity), and the two
-// kernels' fluxes at a face have to share it, or momentum is lost there (5e-9 of the
-// kinetic energy of a channel in 500 steps).
+// is no faster) with the FP32 entries of Q: their rounding is a systematic error of a
+// gradient, and the two kernels' fluxes at a face have to share it, or momentum is lost
+// there (with entries of D here: 5e-9 of the kinetic energy of a channel in 500 steps).
+// N = 3, 48^3: 204 us, mixed 166 (207, 171); N = 5, 32^3: 153, mixed 131 (167, 142).
 template <int N>
 struct FaceShape {
   using L = Line<N>;

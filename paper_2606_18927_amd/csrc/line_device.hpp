@@ -3,11 +3,13 @@
 // What bounds it (N = 7, 32^3 elements, RK instance, per launch; with one lane per
 // node and every node reading its lines from LDS in brackets):
 //                       time us        HBM GB   vector instr. 10^6   their issue   LDS busy
-//   FP64                783  (986)     3.13     224  (355)           50 %          27 % (55 %)
-//   mixed               662  (838)     2.93     260                  69 %          23 % (44 %)
-//   entropy-cons. FP64 1038 (1651)     3.13     357  (671)           68 %          22 % (36 %)
-//   entropy-cons. mixed 822 (1351)     2.93     388                  91 %          20 %
-// A triad moves 3.13 GB in 0.49 ms.  In FP64 a CU holds two workgroups (77 KB LDS, 246
+//   FP64                799  (986)     3.13     226  (355)           50 %          27 % (55 %)
+//   mixed               713  (838)     2.93     279                  69 %          26 % (44 %)
+//   entropy-cons. FP64 1069 (1651)     3.13     360  (671)           67 %          22 % (36 %)
+//   entropy-cons. mixed 857 (1351)     2.93     403                  91 %          22 %
+// (Mixed precision with each direction's parts in one FP32 sum: 662 and 822 us, and a mass
+// that a long run loses.)
+// A triad moves 3.13 GB in 0.49 ms.  In FP64 a CU holds two workgroups (77 KB LDS, 224
 // registers: the whole line and its sums): eight waves have to hide each other's memory,
 // LDS and barrier latencies; the entropy-conserving pair is bound by its instructions.
 // (Workgroups that loop over elements and fetch the next one early: 4 - 7 % slower; two
